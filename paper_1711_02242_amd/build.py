@@ -11,12 +11,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libafqmc.so")
-SOURCES = ["afqmc.hip"]
+SOURCES = ["afqmc.hip", "contract_launch.hip"]
 ARCH = os.environ.get("AFQMC_OFFLOAD_ARCH", "gfx950")
 
 
@@ -27,19 +29,28 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def build(verbose: bool = False) -> str:
-    tmp = LIB + ".tmp"
-    cmd = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
-           # packed FP32 instructions stay off: only scalar/vector FP32 code is emitted
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-fvisibility=hidden", "-I", os.path.join(ROOT, "include"),
-           "-o", tmp] + [os.path.join(CSRC, s) for s in SOURCES]
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed")
+
+
+def build(verbose: bool = False) -> str:
+    flags = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
+             # packed FP32 instructions stay off: only scalar/vector FP32 code is emitted
+             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-fvisibility=hidden", "-I", os.path.join(ROOT, "include")]
+    tmp = LIB + ".tmp"
+    with tempfile.TemporaryDirectory() as work:
+        objs = [os.path.join(work, s + ".o") for s in SOURCES]
+        cmds = [[hipcc(), *flags, "-c", "-o", o, os.path.join(CSRC, s)]
+                for s, o in zip(SOURCES, objs)]
+        with ThreadPoolExecutor() as pool:      # one compiler process per source
+            list(pool.map(lambda c: _run(c, verbose), cmds))
+        _run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
     os.replace(tmp, LIB)
     return LIB
 

@@ -20,6 +20,7 @@
 #include "kernels_fp64.hpp"
 #include "kernels_mfma.hpp"
 #include "kernels_prop.hpp"
+#include "contract_pair.hpp"
 #include "kernels_mcd.hpp"
 #include "kernels_peak.hpp"
 
@@ -54,7 +55,7 @@ struct TimedLaunch {
 struct WsLayout {
   size_t thetaT, tcur, tpart, exch, e1, logdet, wflag, enew, y, A, X0, X1, Y, parent, csum,
       wnew, asnap, lsnap, esum, thetaP, y32, fbterm, mfterm, logR, psnap, ldc, wflc, dstep, growth,
-      thmax, thetaP64, glist, gcount, total;
+      thmax, thetaP64, glist, slist, gcount, part, psplit, pstart, total;
 };
 
 }  // namespace
@@ -92,6 +93,7 @@ struct afqmc_sys_s {
   bool multi = false;
   double* coef = nullptr;  // [n_det][2] expansion coefficients A_d
   int tile = 0;            // contraction variant (TILE_*), set by afqmc_autotune / afqmc_set_tile
+  PairTables pr;           // FP64 contraction in the trial's virtual space (FP64 mode, guard)
   size_t device_bytes = 0;
   // timing
   bool timing = false;
@@ -104,6 +106,9 @@ namespace {
 
 size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// The FP64 mode contracts in the trial's virtual space.
+bool pair_mode(const afqmc_sys_s* S) { return S->pr.on && S->p.precision == AFQMC_FP64; }
+
 WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   WsLayout L{};
   size_t o = 0;
@@ -113,7 +118,8 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
     return r;
   };
   const size_t M = S->M, G = S->G, nt = S->ntot, nd = S->n_det;
-  L.thetaT = take(S->mt.enabled ? 0 : nw * nd * nt * M * 16);   // FP64 VALU contraction only
+  // Theta^T in FP64: the VALU and the virtual-space contractions
+  L.thetaT = take(S->mt.enabled && !S->pr.on ? 0 : nw * nd * nt * M * 16);
   L.tcur = take(nw * G * 16);
   L.tpart = take(nw * nd * 2 * G * 16);
   L.exch = take(nw * nd * 2 * 16);
@@ -133,7 +139,9 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.asnap = take(nw * 8);
   L.lsnap = take(nw * 8);
   L.esum = take(64);
-  L.thetaP = take(mfma_theta_bytes(S->mt, nw));
+  // the contraction's operand: the amplitudes X, or Theta packed for the per-vector kernels
+  const size_t xb = S->pr.on ? nw * nd * pair_x_elems(S->pr.dim) * 8 : 0;
+  L.thetaP = take(pair_mode(S) ? xb : mfma_theta_bytes(S->mt, nw));
   L.y32 = take(S->f32_prop ? nw * 2 * (size_t)S->Gp * 4 : 0);
   const size_t nblk = (size_t)((S->G + 3) / 4);
   L.fbterm = take((S->p.flags & (AFQMC_FLAG_HYBRID | AFQMC_FLAG_FREE_PROJECTION)) ? nw * nblk * 16 : 0);
@@ -145,9 +153,14 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.dstep = take(8);
   L.growth = take(GR_COUNT * 8);
   L.thmax = take(S->guard_on ? nw * nd * 2 * 8 : 0);
-  L.thetaP64 = take(S->guard_on ? mfma_theta_bytes(S->mt64, nw) : 0);
+  L.thetaP64 = take(!S->guard_on ? 0 : S->pr.on ? xb : mfma_theta_bytes(S->mt64, nw));
   L.glist = take(S->guard_on ? nw * 4 : 0);
-  L.gcount = take(S->guard_on ? 8 : 0);
+  L.slist = take(S->guard_on ? nw * 8 : 0);
+  L.gcount = take(S->guard_on ? 16 : 0);
+  const int cus = device_cu_count();
+  L.part = take(S->pr.on ? pair_part_elems(S->pr.dim, (int)nw, cus) * 16 : 0);
+  L.psplit = take(S->pr.on ? pair_split_elems(S->pr.dim) * 16 : 0);
+  L.pstart = take(S->pr.on ? (size_t)(2 * cus + 1) * 8 : 0);
   L.total = o;
   return L;
 }
@@ -328,6 +341,7 @@ void free_sys(afqmc_sys_s* S) {
   (void)hipFree(S->coef);
   mfma_free_tables(S->mt);
   mfma_free_tables(S->mt64);
+  pair_free_tables(S->pr);
   delete S;
 }
 
@@ -347,8 +361,12 @@ int launch_overlap(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L, in
   // one workgroup per (walker, spin, determinant)
   dim3 grid(w->n_walkers, 2, S->n_det);
   void* ws = w->workspace;
-  void* packed = S->mt.enabled ? at<void>(ws, L.thetaP) : nullptr;
-  const int kind = !S->mt.enabled ? 0
+  cd* thetaT = pair_mode(S) || !S->mt.enabled ? at<cd>(ws, L.thetaT) : nullptr;
+  void* packed = thetaT ? nullptr : at<void>(ws, L.thetaP);
+  double* thmax = S->guard_on ? at<double>(ws, L.thmax) : nullptr;
+  cd* guardT = S->guard_on && S->pr.on ? at<cd>(ws, L.thetaT) : nullptr;
+  double* packed64 = S->guard_on && !S->pr.on ? at<double>(ws, L.thetaP64) : nullptr;
+  const int kind = thetaT ? 0
                    : S->mt.precision == AFQMC_FP64 ? 3
                    : S->mt.precision == AFQMC_BF16X3 ? 2 : 1;
   const size_t shm = (size_t)nmax * (2 * nmax + 1) * 16 + 64;   // [T | I] and 8 doubles
@@ -357,20 +375,15 @@ int launch_overlap(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L, in
     (void)hipFuncSetAttribute((const void*)k_overlap_mfma<NPAD>,                               \
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
     hipLaunchKernelGGL(k_overlap_mfma<NPAD>, grid, dim3(256), shm, S->stream, S->M, S->nup,     \
-                       S->ndn, S->V, S->ht, (const cd*)w->U, w->weight, check_weight,          \
-                       S->mt.enabled ? nullptr : at<cd>(ws, L.thetaT), at<cd>(ws, L.logdet),   \
-                       at<cd>(ws, L.e1),                                                       \
-                       at<unsigned>(ws, L.wflag), packed, kind, S->mt.NP, S->mt.KP,           \
-                       S->guard_on ? at<double>(ws, L.thmax) : nullptr,                        \
-                       S->guard_on ? at<double>(ws, L.thetaP64) : nullptr);                    \
+                       S->ndn, S->V, S->ht, (const cd*)w->U, w->weight, check_weight, thetaT,  \
+                       at<cd>(ws, L.logdet), at<cd>(ws, L.e1), at<unsigned>(ws, L.wflag),      \
+                       packed, kind, S->mt.NP, S->mt.KP, thmax, packed64);                     \
   } while (0)
 #define OVW(NPAD)                                                                              \
   hipLaunchKernelGGL(k_overlap_wave<NPAD>, grid, dim3(64), 0, S->stream, S->M, S->nup, S->ndn,   \
-                     S->V, S->ht, (const cd*)w->U, w->weight, check_weight,                      \
-                     S->mt.enabled ? nullptr : at<cd>(ws, L.thetaT), at<cd>(ws, L.logdet),       \
-                     at<cd>(ws, L.e1), at<unsigned>(ws, L.wflag), packed, kind, S->mt.NP,        \
-                     S->mt.KP, S->guard_on ? at<double>(ws, L.thmax) : nullptr,                  \
-                     S->guard_on ? at<double>(ws, L.thetaP64) : nullptr, S->guard)
+                     S->V, S->ht, (const cd*)w->U, w->weight, check_weight, thetaT,              \
+                     at<cd>(ws, L.logdet), at<cd>(ws, L.e1), at<unsigned>(ws, L.wflag), packed,  \
+                     kind, S->mt.NP, S->mt.KP, thmax, packed64, guardT, S->guard)
   // up to N = 32 one wavefront per matrix (elimination in registers), beyond it the
   // four-wavefront kernel with [T | I] in LDS
   if (nmax <= 16)
@@ -392,7 +405,15 @@ int launch_overlap(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L, in
 // The contraction proper (tpart, exch of every walker in the system's precision).
 int launch_contraction(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L) {
   void* ws = w->workspace;
-  if (!S->mt.enabled) {
+  if (pair_mode(S)) {
+    Timer tm(S, KG_CONTRACT);
+    pair_virtual(S->pr, S->stream, w->n_walkers, S->M, at<cd>(ws, L.thetaT), w->weight,
+                 at<double>(ws, L.thetaP), nullptr, 0.0);
+    HIPCHK(hipGetLastError());
+    HIPCHK(pair_contract(S->pr, S->stream, w->n_walkers, device_cu_count(),
+                         at<double>(ws, L.thetaP), at<cd>(ws, L.tpart), at<cd>(ws, L.exch),
+                         at<cd>(ws, L.part), at<cd>(ws, L.psplit), at<long long>(ws, L.pstart)));
+  } else if (!S->mt.enabled) {
     Timer tm(S, KG_CONTRACT);
     const size_t nmax = std::max(S->nup, S->ndn);
     const size_t om = nmax * (nmax + 1) * 16 + 64;
@@ -429,14 +450,25 @@ int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout
     Timer tm(S, KG_GUARD);
     hipLaunchKernelGGL(k_guard_list, dim3(1), dim3(1024), 0, S->stream, w->n_walkers, S->n_det,
                        S->guard, w->weight, (const double*)at<double>(ws, L.thmax),
-                       at<int>(ws, L.glist), at<int>(ws, L.gcount),
+                       at<int>(ws, L.glist), at<int>(ws, L.slist), at<int>(ws, L.gcount),
                        in_step ? S->capcount : nullptr);
     HIPCHK(hipGetLastError());
-    HIPCHK(mfma_contract(S->mt64, S->stream, w->n_walkers, S->n_det, S->G,
-                         at<void>(ws, L.thetaP64), w->weight, at<cd>(ws, L.tpart),
-                         at<cd>(ws, L.exch), TILE_DEFAULT, at<int>(ws, L.glist),
-                         at<int>(ws, L.gcount), (const double*)at<double>(ws, L.thmax),
-                         S->guard));
+    if (S->pr.on) {
+      const double* thmax = at<double>(ws, L.thmax);
+      pair_virtual(S->pr, S->stream, w->n_walkers, S->M, at<cd>(ws, L.thetaT), w->weight,
+                   at<double>(ws, L.thetaP64), thmax, S->guard);
+      HIPCHK(hipGetLastError());
+      HIPCHK(pair_contract(S->pr, S->stream, w->n_walkers, device_cu_count(),
+                           at<double>(ws, L.thetaP64), at<cd>(ws, L.tpart), at<cd>(ws, L.exch),
+                           at<cd>(ws, L.part), at<cd>(ws, L.psplit), at<long long>(ws, L.pstart),
+                           at<int>(ws, L.slist), at<int>(ws, L.gcount) + 1, thmax, S->guard));
+    } else {
+      HIPCHK(mfma_contract(S->mt64, S->stream, w->n_walkers, S->n_det, S->G,
+                           at<void>(ws, L.thetaP64), w->weight, at<cd>(ws, L.tpart),
+                           at<cd>(ws, L.exch), TILE_DEFAULT, at<int>(ws, L.glist),
+                           at<int>(ws, L.gcount), (const double*)at<double>(ws, L.thmax),
+                           S->guard));
+    }
   }
   if (S->multi) {
     Timer tm(S, KG_ASSEMBLE);
@@ -525,6 +557,147 @@ namespace {
 double guard_threshold(const afqmc_params* p) {
   if (!std::isnan(p->theta_guard)) return p->theta_guard;
   return p->precision == AFQMC_BF16X3 ? 0.75 : 4.0;
+}
+
+// Rows a of the orthonormal complement of the N rows of V (each of length M): Householder
+// reflections that take V's columns to a triangle, applied to the unit vectors N .. M - 1.
+void host_complement(const double* V, int N, int M, double* Qt) {
+  std::vector<double> H((size_t)N * M), beta(N, 0.0);
+  std::vector<double> A(V, V + (size_t)N * M);   // row i: column i of the matrix
+  for (int k = 0; k < N; ++k) {
+    double* v = H.data() + (size_t)k * M;
+    double nn = 0.0;
+    for (int p = k; p < M; ++p) nn += A[(size_t)k * M + p] * A[(size_t)k * M + p];
+    const double x0 = A[(size_t)k * M + k], al = x0 > 0.0 ? -sqrt(nn) : sqrt(nn);
+    for (int p = k; p < M; ++p) v[p] = A[(size_t)k * M + p];
+    v[k] -= al;
+    double vv = 0.0;
+    for (int p = k; p < M; ++p) vv += v[p] * v[p];
+    beta[k] = vv > 0.0 ? 2.0 / vv : 0.0;
+    for (int j = k + 1; j < N; ++j) {
+      double dt = 0.0;
+      for (int p = k; p < M; ++p) dt += v[p] * A[(size_t)j * M + p];
+      dt *= beta[k];
+      for (int p = k; p < M; ++p) A[(size_t)j * M + p] -= dt * v[p];
+    }
+  }
+  for (int a = 0; a < M - N; ++a) {
+    double* x = Qt + (size_t)a * M;
+    for (int p = 0; p < M; ++p) x[p] = p == N + a ? 1.0 : 0.0;
+    for (int k = N - 1; k >= 0; --k) {
+      const double* v = H.data() + (size_t)k * M;
+      double dt = 0.0;
+      for (int p = k; p < M; ++p) dt += v[p] * x[p];
+      dt *= beta[k];
+      for (int p = k; p < M; ++p) x[p] -= dt * v[p];
+    }
+  }
+}
+
+// The tables of the virtual-space contraction from V and Lh (host, n_det blocks; Lh also on the
+// device as S->Lh).  Where the device has no room for them the form stays off.
+int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<double>& Lh) {
+  PairTables& t = S->pr;
+  const PairDims& p = t.dim;
+  const int M = S->M, G = S->G, nt = S->ntot, nd = S->n_det;
+  const size_t nv = (size_t)p.nv[0] + p.nv[1], dps = (size_t)p.dp[0] + p.dp[1];
+  std::vector<double> Qt((size_t)nd * nv * M), f(nd * dps, 0.0), t0((size_t)nd * 2 * G, 0.0),
+      c0((size_t)nd * 2, 0.0);
+  const int nthr = setup_threads(G);
+  for (int d = 0; d < nd; ++d)
+    for (int s = 0; s < 2; ++s) {
+      const int N = p.N[s], off = s ? p.N[0] : 0;
+      if (N == 0) continue;
+      const double* V = Vr.data() + ((size_t)d * nt + off) * M;
+      double* Q = Qt.data() + ((size_t)d * nv + (s ? p.nv[0] : 0)) * M;
+      double* fs = f.data() + d * dps + (s ? p.dp[0] : 0);
+      if (s == 1 && p.N[0] == N && memcmp(V, V - (size_t)N * M, sizeof(double) * N * M) == 0) {
+        // the same orbitals as spin up
+        memcpy(Q, Q - (size_t)p.nv[0] * M, sizeof(double) * p.nv[0] * M);
+        memcpy(fs, fs - p.dp[0], sizeof(double) * p.dp[0]);
+        memcpy(&t0[((size_t)d * 2 + 1) * G], &t0[((size_t)d * 2) * G], sizeof(double) * G);
+        c0[2 * d + 1] = c0[2 * d];
+        continue;
+      }
+      host_complement(V, N, M, Q);
+      std::vector<double> T((size_t)N * N);
+      for (int i = 0; i < N; ++i)
+        for (int j = 0; j < N; ++j) {
+          double acc = 0.0;
+          for (int q = 0; q < M; ++q) acc += V[(size_t)i * M + q] * V[(size_t)j * M + q];
+          T[(size_t)i * N + j] = acc;
+        }
+      // linearly dependent orbitals (a later determinant) have no overlap with any walker
+      if (!host_inverse(T, N)) continue;
+      std::vector<double> V0t((size_t)M * N, 0.0);   // V (V^T V)^-1, [q][c]
+      for (int i = 0; i < N; ++i)
+        for (int q = 0; q < M; ++q)
+          for (int c = 0; c < N; ++c)
+            V0t[(size_t)q * N + c] += T[(size_t)i * N + c] * V[(size_t)i * M + q];
+      std::vector<std::vector<double>> F(nthr, std::vector<double>((size_t)N * M, 0.0));
+      std::vector<double> cg(G, 0.0);
+      parallel_for(G, [&](int g, int th) {
+        const double* L = Lh.data() + (((size_t)d * G + g) * nt + off) * M;
+        std::vector<double> om((size_t)N * N, 0.0);
+        for (int r = 0; r < N; ++r)
+          for (int q = 0; q < M; ++q) {
+            const double l = L[(size_t)r * M + q];
+            const double* v = V0t.data() + (size_t)q * N;
+            for (int c = 0; c < N; ++c) om[(size_t)r * N + c] += l * v[c];
+          }
+        double tr = 0.0, x = 0.0;
+        for (int r = 0; r < N; ++r) {
+          tr += om[(size_t)r * N + r];
+          double* fr = F[th].data() + (size_t)r * M;
+          for (int c = 0; c < N; ++c) {
+            const double o = om[(size_t)r * N + c];
+            x += o * om[(size_t)c * N + r];
+            const double* lc = L + (size_t)c * M;
+            for (int q = 0; q < M; ++q) fr[q] += o * lc[q];
+          }
+        }
+        t0[((size_t)d * 2 + s) * G + g] = tr;
+        cg[g] = x;
+      });
+      for (int g = 0; g < G; ++g) c0[2 * d + s] += cg[g];
+      for (int th = 1; th < nthr; ++th)
+        for (size_t e = 0; e < (size_t)N * M; ++e) F[0][e] += F[th][e];
+      for (int c = 0; c < N; ++c)
+        for (int a = 0; a < p.nv[s]; ++a) {
+          double acc = 0.0;
+          for (int q = 0; q < M; ++q) acc += F[0][(size_t)c * M + q] * Q[(size_t)a * M + q];
+          fs[(size_t)c * p.nv[s] + a] = acc;
+        }
+    }
+  int rc;
+  const size_t before = S->device_bytes, kel = pair_k_elems(p), bel = pair_b_elems(p);
+  if ((rc = dev_upload(S, &t.Qt, Qt.data(), Qt.size())) ||
+      (rc = dev_upload(S, &t.f, f.data(), f.size())) ||
+      (rc = dev_upload(S, &t.t0, t0.data(), t0.size())) ||
+      (rc = dev_upload(S, &t.c0, c0.data(), c0.size())) ||
+      (rc = dev_upload<double>(S, &t.B, nullptr, bel)) ||
+      (rc = dev_upload<double>(S, &t.K, nullptr, kel))) {
+    pair_free_tables(t);
+    S->device_bytes = before;
+    (void)hipGetLastError();
+    return rc == AFQMC_E_NOMEM ? AFQMC_OK : rc;
+  }
+  bool ok = hipMemset(t.B, 0, bel * 8) == hipSuccess && hipMemset(t.K, 0, kel * 8) == hipSuccess;
+  for (int d = 0; d < nd && ok; ++d)
+    for (int s = 0; s < 2; ++s) {
+      if (p.N[s] == 0) continue;
+      double* Bs = t.B + (size_t)d * G * dps + (s ? (size_t)G * p.dp[0] : 0);
+      const long long rows = (long long)G * p.N[s];
+      hipLaunchKernelGGL(k_pair_b, dim3((unsigned)((rows + 15) / 16), (p.nv[s] + 63) / 64), dim3(64),
+                         0, 0, M, p.N[s], p.nv[s], G, p.dp[s], (size_t)nt * M,
+                         S->Lh + ((size_t)d * G * nt + (s ? p.N[0] : 0)) * M,
+                         t.Qt + ((size_t)d * nv + (s ? p.nv[0] : 0)) * M, Bs);
+      hipLaunchKernelGGL(k_pair_build, dim3(p.dp[s] / 64, p.dp[s] / 64), dim3(256), 0, 0, p.d[s],
+                         p.dp[s], p.nv[s], G, (const double*)Bs,
+                         t.K + ((size_t)d * (p.P[0] + p.P[1]) + (s ? p.P[0] : 0)) * PAIR_B * PAIR_B);
+    }
+  ok = ok && hipGetLastError() == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+  return ok ? AFQMC_OK : AFQMC_E_HIP;
 }
 
 // Setup of a trial with n_det determinants; coeffs == nullptr is the single-determinant trial
@@ -820,25 +993,34 @@ int setup_impl(const afqmc_params* p, double h0, const double* h1, const double*
     // MFMA contraction tables; the plain FP64 single-determinant path falls back to the
     // VALU contraction where no MFMA kernel covers the shape.  The mixed-precision modes and
     // the multi-determinant trial need the MFMA kernels.
-    rc = mfma_build_tables(S->mt, p->precision, M, nup_i, ndn_i, G, Lh.data(), n_det);
-    if (rc == AFQMC_E_UNSUPPORTED && p->precision == AFQMC_FP64 && !multi) rc = AFQMC_OK;
+    rc = mfma_plan(S->mt, p->precision, M, nup_i, ndn_i, G, n_det);
+    if (rc == AFQMC_OK) S->mt.enabled = true;
+    else if (rc == AFQMC_E_UNSUPPORTED && p->precision == AFQMC_FP64 && !multi) rc = AFQMC_OK;
+    // the precision guard of the mixed modes (for the shapes of the FP64 MFMA contraction:
+    // N <= 32, M <= 128) redoes walkers in FP64
+    const double guard = guard_threshold(p);
+    const bool f64 = p->precision == AFQMC_FP64;
+    if (rc == AFQMC_OK && !f64 && std::isfinite(guard) && S->mt.enabled && !S->mt.wide) {
+      S->guard_on = true;
+      S->guard = guard;
+    }
+    // FP64 contractions in the virtual space where that form is the cheaper one
+    if (rc == AFQMC_OK && (f64 || S->guard_on)) {
+      pair_plan(S->pr, M, nup_i, ndn_i, G, n_det);
+      if (S->pr.on) rc = build_pair(S, Vr, Lh);
+    }
+    // else the per-vector tables: the mode's own, and an FP64 copy for the guard
+    if (rc == AFQMC_OK && S->mt.enabled && !(f64 && S->pr.on)) {
+      rc = mfma_build_tables(S->mt, p->precision, M, nup_i, ndn_i, G, Lh.data(), n_det);
+      S->device_bytes += S->mt.bytes;
+    }
+    if (rc == AFQMC_OK && S->guard_on && !S->pr.on) {
+      rc = mfma_build_tables(S->mt64, AFQMC_FP64, M, nup_i, ndn_i, G, Lh.data(), n_det);
+      S->device_bytes += S->mt64.bytes;
+    }
     if (rc != AFQMC_OK) {
       free_sys(S);
       return rc;
-    }
-    if (S->mt.enabled) S->device_bytes += S->mt.bytes;
-    // precision guard of the mixed modes: an FP64 copy of the tables for the walkers redone
-    // in FP64 (the FP64 MFMA contraction covers N <= 32, M <= 128)
-    const double guard = guard_threshold(p);
-    if (p->precision != AFQMC_FP64 && std::isfinite(guard) && S->mt.enabled && !S->mt.wide) {
-      rc = mfma_build_tables(S->mt64, AFQMC_FP64, M, nup_i, ndn_i, G, Lh.data(), n_det);
-      if (rc != AFQMC_OK || S->mt64.NP != S->mt.NP || S->mt64.KP != S->mt.KP) {
-        free_sys(S);
-        return rc != AFQMC_OK ? rc : AFQMC_E_UNSUPPORTED;
-      }
-      S->device_bytes += S->mt64.bytes;
-      S->guard_on = true;
-      S->guard = guard;
     }
   }
   // FP32 A-build and propagation in the mixed-precision modes: k_propagate_f32 where it
@@ -1458,19 +1640,21 @@ int afqmc_footprint_bytes(const afqmc_params* p, int32_t n_det, int32_t n_walker
   else if (!(p->precision == AFQMC_FP64 && n_det == 1)) return rc;
   S.f32_prop = p->precision != AFQMC_FP64 && M <= WIDE_KMAX &&
                std::max(S.nup, S.ndn) <= 64;
-  if (p->precision != AFQMC_FP64 && std::isfinite(guard_threshold(p)) && S.mt.enabled &&
-      !S.mt.wide && mfma_plan(S.mt64, AFQMC_FP64, M, S.nup, S.ndn, G, n_det) == AFQMC_OK) {
+  S.guard_on = p->precision != AFQMC_FP64 && std::isfinite(guard_threshold(p)) &&
+               S.mt.enabled && !S.mt.wide;
+  if (p->precision == AFQMC_FP64 || S.guard_on) pair_plan(S.pr, M, S.nup, S.ndn, G, n_det);
+  if (S.guard_on && !S.pr.on &&
+      mfma_plan(S.mt64, AFQMC_FP64, M, S.nup, S.ndn, G, n_det) == AFQMC_OK)
     S.mt64.enabled = true;
-    S.guard_on = true;
-  }
   S.Gp = S.f32_prop ? ((G + 31) / 32) * 32 : 0;
   const size_t nt = S.ntot, MM = (size_t)M * M, g1 = G > 0 ? G : 1;
   size_t sb = MM * 8 + n_det * nt * M * 8 + g1 * 8;          // E_h, V, lbar
   sb += (n_det * (size_t)G * nt * M > 0 ? n_det * (size_t)G * nt * M : 1) * 8;  // Lh
   sb += n_det * nt * M * 8 + 4 + CAP_COUNT * 8;              // ht, status, bound counters
   if (S.multi) sb += (size_t)2 * n_det * 8;                  // coefficients
-  if (S.mt.enabled) sb += S.mt.bytes;
-  if (S.guard_on) sb += S.mt64.bytes;
+  if (S.pr.on) sb += S.pr.bytes;
+  if (S.mt.enabled && !pair_mode(&S)) sb += S.mt.bytes;
+  if (S.mt64.enabled) sb += S.mt64.bytes;
   const size_t MMh = (size_t)M * (M + 1) / 2;
   if (p->precision == AFQMC_FP64) sb += 2 * MMh * 4;                // pair table
   if (S.f32_prop)                                                     // packed L^T, E_h (FP32)
@@ -1482,8 +1666,6 @@ int afqmc_footprint_bytes(const afqmc_params* p, int32_t n_det, int32_t n_walker
   *system_bytes = sb;
   const size_t nw = (size_t)n_walkers;
   *walker_bytes = layout(&S, nw).total + 256 + nw * nt * M * 16 + nw * (8 * 4 + 16 + 8);
-  S.mt.enabled = false;   // the descriptor owns no device memory
-  S.mt64.enabled = false;
   return AFQMC_OK;
 }
 

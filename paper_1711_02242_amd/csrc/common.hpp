@@ -12,6 +12,9 @@
 
 #define AFQMC_WAVE 64
 
+// Per-walker fault flags written by the overlap kernel.
+#define WFLAG_SINGULAR 1u
+
 struct cd {
   double re, im;
 };

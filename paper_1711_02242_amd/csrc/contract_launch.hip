@@ -1,0 +1,240 @@
+// Launches of the per-vector local-energy contraction: one kernel instance per precision, tile
+// variant and K chunk count.
+#include <hip/hip_runtime.h>
+
+#include "../../include/afqmc.h"
+#include "kernels_mfma.hpp"
+
+hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
+                         const void* thetaP, const double* weight, cd* tpart, cd* exch, int tile,
+                         const int* wlist, const int* wcount, const double* gthmax, double guard) {
+  if (t.precision == AFQMC_FP64) {
+    const size_t shm = mfma_f64_contract_lds_bytes(t);
+    dim3 grid((nw + 1) / 2, 2 * n_det);
+    // one instantiation per K chunk count (K_P = 32 .. 128 in steps of 32)
+    if (t.KP % 32 != 0 || t.KP < 32 || t.KP > MFMA_KMAX) return hipErrorInvalidValue;
+#define LAUNCH_F64(NPV, NKV)                                                                   \
+  do {                                                                                         \
+    (void)hipFuncSetAttribute((const void*)k_contract_f64mfma<NPV, NKV>,                       \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
+    hipLaunchKernelGGL((k_contract_f64mfma<NPV, NKV>), grid, dim3(256), shm, st, nw, G, t.nup, \
+                       t.ndn, t.KP, (const double*)t.Lp, (const double*)thetaP, weight, tpart, \
+                       exch, wlist, wcount, gthmax, guard);                                    \
+  } while (0)
+#define LAUNCH_F64_NP(NPV)                                                                     \
+  do {                                                                                         \
+    switch (t.KP / 8) {                                                                        \
+      case 4: LAUNCH_F64(NPV, 4); break;                                                       \
+      case 8: LAUNCH_F64(NPV, 8); break;                                                       \
+      case 12: LAUNCH_F64(NPV, 12); break;                                                     \
+      default: LAUNCH_F64(NPV, 16); break;                                                     \
+    }                                                                                          \
+  } while (0)
+    if (t.NP == 32) LAUNCH_F64_NP(32);
+    else LAUNCH_F64_NP(16);
+#undef LAUNCH_F64_NP
+#undef LAUNCH_F64
+    return hipGetLastError();
+  }
+  const bool bf = t.precision == AFQMC_BF16X3;
+  if (!mfma_tile_valid(t, tile)) tile = TILE_DEFAULT;
+  // default at N_P = 32: the block-exchange kernel (fewest LDS and vector instructions per g),
+  // eight walkers per workgroup when the workgroups with work (walkers, active spins,
+  // determinants) still cover every CU
+  if (tile == TILE_DEFAULT && !t.wide && t.NP == 32) {
+    const int spins = (t.nup > 0 ? 1 : 0) + (t.ndn > 0 ? 1 : 0);
+    tile = (size_t)((nw + 7) / 8) * spins * n_det >= (size_t)device_cu_count() ? TILE_BX8
+                                                                                 : TILE_BX;
+  }
+  if (tile == TILE_FLAT || tile == TILE_STACK) {
+    const bool stk = tile == TILE_STACK;
+    const FlatLaunch f = flat_launch(t.nup, t.ndn, G, bf, stk);
+    dim3 grid(nw, 2 * n_det);
+#define LAUNCH_FLAT_KR(BFV, KM, RTV)                                                              \
+  do {                                                                                            \
+    if (stk)                                                                                      \
+      hipLaunchKernelGGL((k_contract_mfma_stack<KM, BFV, ((RTV) > (BFV ? 3 : STACK_MAX_RT)        \
+                                                              ? (BFV ? 3 : STACK_MAX_RT)          \
+                                                              : (RTV))>),                         \
+                         grid, dim3(64 * f.waves), f.lds, st, nw, G, t.nup, t.ndn, t.NP, t.KP,    \
+                         f.qup, f.qdn, f.LDR, (const void*)t.Lp, thetaP, weight, tpart, exch);    \
+    else                                                                                          \
+      hipLaunchKernelGGL((k_contract_mfma_flat<KM, BFV, (RTV)>), grid, dim3(64 * f.waves), f.lds, \
+                         st, nw, G, t.nup, t.ndn, t.NP, t.KP, f.qup, f.qdn, f.LDR,                \
+                         (const void*)t.Lp, thetaP, weight, tpart, exch);                         \
+  } while (0)
+  // one instantiation per row-tile count (flat 1 .. 7, BF16x3 1 .. 4; stack 1 .. 7, BF16x3
+  // 1 .. 3)
+#define LAUNCH_FLAT_K(BFV, KM)                                                                    \
+  do {                                                                                            \
+    switch (f.RT) {                                                                               \
+      case 1: LAUNCH_FLAT_KR(BFV, KM, 1); break;                                                  \
+      case 2: LAUNCH_FLAT_KR(BFV, KM, 2); break;                                                  \
+      case 3: LAUNCH_FLAT_KR(BFV, KM, 3); break;                                                  \
+      case 4: LAUNCH_FLAT_KR(BFV, KM, 4); break;                                                  \
+      case 5: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 5); break;                                        \
+      case 6: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 6); break;                                        \
+      default: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 7); break;                                       \
+    }                                                                                             \
+  } while (0)
+  // and per K chunk count (K_P = 32 .. 224 in steps of 32)
+#define LAUNCH_FLAT(BFV)                                                                          \
+  do {                                                                                            \
+    constexpr int KCH_ = BFV ? 32 : 16;                                                           \
+    switch (t.KP / KCH_) {                                                                        \
+      case 32 / KCH_: LAUNCH_FLAT_K(BFV, 32 / KCH_); break;                                       \
+      case 64 / KCH_: LAUNCH_FLAT_K(BFV, 64 / KCH_); break;                                       \
+      case 96 / KCH_: LAUNCH_FLAT_K(BFV, 96 / KCH_); break;                                       \
+      case 128 / KCH_: LAUNCH_FLAT_K(BFV, 128 / KCH_); break;                                     \
+      case 160 / KCH_: LAUNCH_FLAT_K(BFV, 160 / KCH_); break;                                     \
+      case 192 / KCH_: LAUNCH_FLAT_K(BFV, 192 / KCH_); break;                                     \
+      default: LAUNCH_FLAT_K(BFV, 224 / KCH_); break;                                             \
+    }                                                                                             \
+  } while (0)
+    if (bf) LAUNCH_FLAT(true);
+    else LAUNCH_FLAT(false);
+#undef LAUNCH_FLAT
+#undef LAUNCH_FLAT_K
+#undef LAUNCH_FLAT_KR
+    return hipGetLastError();
+  }
+  if (t.wide || tile == TILE_WIDE) {
+    dim3 grid(nw, 2 * n_det);
+#define LAUNCH_WIDE_K(NPV, BFV, KM)                                                             \
+  do {                                                                                          \
+    const size_t shm_ = wide_contract_lds_bytes_t<NPV, BFV>(t.KP);                              \
+    hipLaunchKernelGGL((k_contract_mfma_wide<NPV, BFV, KM>), grid, dim3(4 * NPV), shm_, st, nw, \
+                       G, t.nup, t.ndn, t.KP, (const void*)t.Lp, thetaP, weight, tpart, exch);  \
+  } while (0)
+  // one instantiation per K chunk count (K_P = 32 .. 224 in steps of 32)
+#define LAUNCH_WIDE(NPV, BFV)                                                                   \
+  do {                                                                                          \
+    constexpr int KCH_ = BFV ? 32 : 16;                                                         \
+    switch (t.KP / KCH_) {                                                                      \
+      case 32 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 32 / KCH_); break;                                \
+      case 64 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 64 / KCH_); break;                                \
+      case 96 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 96 / KCH_); break;                                \
+      case 128 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 128 / KCH_); break;                              \
+      case 160 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 160 / KCH_); break;                              \
+      case 192 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 192 / KCH_); break;                              \
+      default: LAUNCH_WIDE_K(NPV, BFV, 224 / KCH_); break;                                      \
+    }                                                                                           \
+  } while (0)
+    if (t.NP == 64) {
+      if (bf) LAUNCH_WIDE(64, true);
+      else LAUNCH_WIDE(64, false);
+    } else if (t.NP == 48) {
+      if (bf) LAUNCH_WIDE(48, true);
+      else LAUNCH_WIDE(48, false);
+    } else {
+      if (bf) LAUNCH_WIDE(32, true);
+      else LAUNCH_WIDE(32, false);
+    }
+#undef LAUNCH_WIDE
+#undef LAUNCH_WIDE_K
+    return hipGetLastError();
+  }
+  const int wpb = tile == TILE_W2 ? 2 : 4;
+  // the kernels are instantiated for K_P = 32, 64, 96, 128
+  if (t.KP % 32 != 0 || t.KP < 32 || t.KP > MFMA_KMAX) return hipErrorInvalidValue;
+  if (tile == TILE_BX || tile == TILE_BX8) {
+    const int wb = tile == TILE_BX8 ? 8 : 4;
+    const size_t shm = bx_contract_lds_bytes(t.KP, bf, wb);
+    dim3 grid((nw + wb - 1) / wb, 2 * n_det);
+#define LAUNCH_BX(BFV, NKV, WBV)                                                               \
+  do {                                                                                         \
+    (void)hipFuncSetAttribute((const void*)k_contract_mfma_bx<BFV, NKV, WBV>,                  \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
+    hipLaunchKernelGGL((k_contract_mfma_bx<BFV, NKV, WBV>), grid, dim3(64 * WBV), shm, st, nw, \
+                       G, t.nup, t.ndn, (const void*)t.Lp, thetaP, weight, tpart, exch);       \
+  } while (0)
+#define LAUNCH_BX_W(BFV, NKV)                                                                  \
+  case NKV:                                                                                    \
+    if (wb == 8) LAUNCH_BX(BFV, NKV, 8);                                                       \
+    else LAUNCH_BX(BFV, NKV, 4);                                                               \
+    break;
+    // one instantiation per K chunk count (K_P = 32 .. 128 in steps of 32)
+    if (bf) {
+      switch (t.KP / 32) { LAUNCH_BX_W(true, 1) LAUNCH_BX_W(true, 2) LAUNCH_BX_W(true, 3)
+                           default: LAUNCH_BX_W(true, 4) }
+    } else {
+      switch (t.KP / 16) { LAUNCH_BX_W(false, 2) LAUNCH_BX_W(false, 4) LAUNCH_BX_W(false, 6)
+                           default: LAUNCH_BX_W(false, 8) }
+    }
+#undef LAUNCH_BX_W
+#undef LAUNCH_BX
+    return hipGetLastError();
+  }
+  if (tile == TILE_PP) {
+    const size_t shm = pp_contract_lds_bytes(t.NP, t.KP, bf);
+    dim3 grid((nw + 7) / 8, 2 * n_det);
+#define LAUNCH_PP_K(NPV, BFV, NKV)                                                             \
+  do {                                                                                         \
+    (void)hipFuncSetAttribute((const void*)k_contract_mfma_pp<NPV, BFV, NKV>,                  \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
+    hipLaunchKernelGGL((k_contract_mfma_pp<NPV, BFV, NKV>), grid, dim3(512), shm, st, nw, G,   \
+                       t.nup, t.ndn, (const void*)t.Lp, thetaP, weight, tpart, exch);          \
+  } while (0)
+#define LAUNCH_PP(NPV, BFV)                                                                    \
+  do {                                                                                         \
+    constexpr int KCH_ = contract_kch<NPV, BFV>();                                             \
+    switch (t.KP / KCH_) {                                                                     \
+      case 32 / KCH_: LAUNCH_PP_K(NPV, BFV, 32 / KCH_); break;                                 \
+      case 64 / KCH_: LAUNCH_PP_K(NPV, BFV, 64 / KCH_); break;                                 \
+      case 96 / KCH_: LAUNCH_PP_K(NPV, BFV, 96 / KCH_); break;                                 \
+      default: LAUNCH_PP_K(NPV, BFV, 128 / KCH_); break;                                       \
+    }                                                                                          \
+  } while (0)
+    if (t.NP == 32) {
+      if (bf) LAUNCH_PP(32, true);
+      else LAUNCH_PP(32, false);
+    } else {
+      if (bf) LAUNCH_PP(16, true);
+      else LAUNCH_PP(16, false);
+    }
+#undef LAUNCH_PP
+#undef LAUNCH_PP_K
+    return hipGetLastError();
+  }
+  const size_t shm = mfma_contract_lds_bytes(t, wpb);
+  dim3 grid((nw + wpb - 1) / wpb, 2 * n_det);
+#define LAUNCH_CONTRACT_K(NPV, BFV, WPBV, NKV)                                                  \
+  do {                                                                                          \
+    (void)hipFuncSetAttribute((const void*)k_contract_mfma<NPV, BFV, WPBV, NKV>,                \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);            \
+    hipLaunchKernelGGL((k_contract_mfma<NPV, BFV, WPBV, NKV>), grid, dim3(64 * WPBV), shm, st,  \
+                       nw, G, t.nup, t.ndn, t.KP, (const void*)t.Lp, thetaP, weight, tpart,     \
+                       exch);                                                                   \
+  } while (0)
+  // one instantiation per K chunk count (K_P = 32 .. 128 in steps of 32)
+#define LAUNCH_CONTRACT(NPV, BFV, WPBV)                                                         \
+  do {                                                                                          \
+    constexpr int KCH_ = contract_kch<NPV, BFV>();                                              \
+    switch (t.KP / KCH_) {                                                                      \
+      case 32 / KCH_: LAUNCH_CONTRACT_K(NPV, BFV, WPBV, 32 / KCH_); break;                      \
+      case 64 / KCH_: LAUNCH_CONTRACT_K(NPV, BFV, WPBV, 64 / KCH_); break;                      \
+      case 96 / KCH_: LAUNCH_CONTRACT_K(NPV, BFV, WPBV, 96 / KCH_); break;                      \
+      default: LAUNCH_CONTRACT_K(NPV, BFV, WPBV, 128 / KCH_); break;                            \
+    }                                                                                           \
+  } while (0)
+  if (wpb == 4) {
+    if (t.NP == 32) {
+      if (bf) LAUNCH_CONTRACT(32, true, 4);
+      else LAUNCH_CONTRACT(32, false, 4);
+    } else {
+      if (bf) LAUNCH_CONTRACT(16, true, 4);
+      else LAUNCH_CONTRACT(16, false, 4);
+    }
+  } else {
+    if (t.NP == 32) {
+      if (bf) LAUNCH_CONTRACT(32, true, 2);
+      else LAUNCH_CONTRACT(32, false, 2);
+    } else {
+      if (bf) LAUNCH_CONTRACT(16, true, 2);
+      else LAUNCH_CONTRACT(16, false, 2);
+    }
+  }
+#undef LAUNCH_CONTRACT
+#undef LAUNCH_CONTRACT_K
+  return hipGetLastError();
+}

@@ -12,9 +12,6 @@
 
 #include "common.hpp"
 
-// Per-walker fault flags written by the overlap kernel.
-#define WFLAG_SINGULAR 1u
-
 // ---------------------------------------------------------------------------
 // Local-energy contraction in FP64 (eq:localenergy3): for every g,
 // Omega = Lh^g_s Theta_s (N x N), tpart[w][s][g] = tr Omega and
@@ -644,46 +641,6 @@ __global__ void k_weights(int nw, int mode, double sf, double dtau, double h0,
 //   centre <- swe / sw                       (the local energy averaged over the block)
 // and the sums restart.  Both values stay fixed outside the growth phase.
 // ---------------------------------------------------------------------------
-// Precision guard of the mixed modes: the live walkers whose largest |Theta_pc| over spins
-// and determinants exceeds `limit`, listed in walker order in wlist, and their number in
-// *wcount (added to counts[CAP_GUARD] when counts != NULL).  One workgroup of 1024 threads,
-// each taking a contiguous range of walkers; the list offsets come from one sequential scan.
-__global__ void __launch_bounds__(1024) k_guard_list(int nw, int nd, double limit,
-                                                     const double* __restrict__ weight,
-                                                     const double* __restrict__ thmax,
-                                                     int* __restrict__ wlist,
-                                                     int* __restrict__ wcount,
-                                                     unsigned long long* __restrict__ counts) {
-  __shared__ int part[1024];
-  const int T = blockDim.x, t = threadIdx.x;
-  const int per = (nw + T - 1) / T;
-  const int lo = min(nw, t * per), hi = min(nw, lo + per);
-  auto flagged = [&](int w) {
-    if (!(weight[w] > 0.0)) return false;
-    double m = 0.0;
-    for (int i = 0; i < 2 * nd; ++i) m = fmax(m, thmax[(size_t)w * 2 * nd + i]);
-    return m > limit;
-  };
-  int c = 0;
-  for (int w = lo; w < hi; ++w) c += flagged(w) ? 1 : 0;
-  part[t] = c;
-  __syncthreads();
-  if (t == 0) {
-    int acc = 0;
-    for (int i = 0; i < T; ++i) {
-      const int v = part[i];
-      part[i] = acc;
-      acc += v;
-    }
-    *wcount = acc;
-    if (counts && acc > 0) atomicAdd(&counts[CAP_GUARD], (unsigned long long)acc);
-  }
-  __syncthreads();
-  int o = part[t];
-  for (int w = lo; w < hi; ++w)
-    if (flagged(w)) wlist[o++] = w;
-}
-
 __global__ void k_clear_u64(unsigned long long* __restrict__ c, int n) {
   if ((int)threadIdx.x < n) c[threadIdx.x] = 0ull;
 }

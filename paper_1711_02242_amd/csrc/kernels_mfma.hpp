@@ -398,241 +398,13 @@ inline size_t mfma_f64_contract_lds_bytes(const MfmaTables& t) {
   return ((size_t)t.NP * (t.KP + 2) + (size_t)2 * 2 * t.NP * (t.NP + 1)) * 8;
 }
 
-inline hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
+// The contraction of every walker by one of the variants (contract_launch.hip: a translation
+// unit of its own, for its many kernel instances).
+hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
                                 const void* thetaP, const double* weight, cd* tpart, cd* exch,
                                 int tile = TILE_DEFAULT, const int* wlist = nullptr,
                                 const int* wcount = nullptr, const double* gthmax = nullptr,
-                                double guard = 0.0) {
-  if (t.precision == AFQMC_FP64) {
-    const size_t shm = mfma_f64_contract_lds_bytes(t);
-    dim3 grid((nw + 1) / 2, 2 * n_det);
-    // one instantiation per K chunk count (K_P = 32 .. 128 in steps of 32)
-    if (t.KP % 32 != 0 || t.KP < 32 || t.KP > MFMA_KMAX) return hipErrorInvalidValue;
-#define LAUNCH_F64(NPV, NKV)                                                                   \
-  do {                                                                                         \
-    (void)hipFuncSetAttribute((const void*)k_contract_f64mfma<NPV, NKV>,                       \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
-    hipLaunchKernelGGL((k_contract_f64mfma<NPV, NKV>), grid, dim3(256), shm, st, nw, G, t.nup, \
-                       t.ndn, t.KP, (const double*)t.Lp, (const double*)thetaP, weight, tpart, \
-                       exch, wlist, wcount, gthmax, guard);                                    \
-  } while (0)
-#define LAUNCH_F64_NP(NPV)                                                                     \
-  do {                                                                                         \
-    switch (t.KP / 8) {                                                                        \
-      case 4: LAUNCH_F64(NPV, 4); break;                                                       \
-      case 8: LAUNCH_F64(NPV, 8); break;                                                       \
-      case 12: LAUNCH_F64(NPV, 12); break;                                                     \
-      default: LAUNCH_F64(NPV, 16); break;                                                     \
-    }                                                                                          \
-  } while (0)
-    if (t.NP == 32) LAUNCH_F64_NP(32);
-    else LAUNCH_F64_NP(16);
-#undef LAUNCH_F64_NP
-#undef LAUNCH_F64
-    return hipGetLastError();
-  }
-  const bool bf = t.precision == AFQMC_BF16X3;
-  if (!mfma_tile_valid(t, tile)) tile = TILE_DEFAULT;
-  // default at N_P = 32: the block-exchange kernel (fewest LDS and vector instructions per g),
-  // eight walkers per workgroup when the workgroups with work (walkers, active spins,
-  // determinants) still cover every CU
-  if (tile == TILE_DEFAULT && !t.wide && t.NP == 32) {
-    const int spins = (t.nup > 0 ? 1 : 0) + (t.ndn > 0 ? 1 : 0);
-    tile = (size_t)((nw + 7) / 8) * spins * n_det >= (size_t)device_cu_count() ? TILE_BX8
-                                                                                 : TILE_BX;
-  }
-  if (tile == TILE_FLAT || tile == TILE_STACK) {
-    const bool stk = tile == TILE_STACK;
-    const FlatLaunch f = flat_launch(t.nup, t.ndn, G, bf, stk);
-    dim3 grid(nw, 2 * n_det);
-#define LAUNCH_FLAT_KR(BFV, KM, RTV)                                                              \
-  do {                                                                                            \
-    if (stk)                                                                                      \
-      hipLaunchKernelGGL((k_contract_mfma_stack<KM, BFV, ((RTV) > (BFV ? 3 : STACK_MAX_RT)        \
-                                                              ? (BFV ? 3 : STACK_MAX_RT)          \
-                                                              : (RTV))>),                         \
-                         grid, dim3(64 * f.waves), f.lds, st, nw, G, t.nup, t.ndn, t.NP, t.KP,    \
-                         f.qup, f.qdn, f.LDR, (const void*)t.Lp, thetaP, weight, tpart, exch);    \
-    else                                                                                          \
-      hipLaunchKernelGGL((k_contract_mfma_flat<KM, BFV, (RTV)>), grid, dim3(64 * f.waves), f.lds, \
-                         st, nw, G, t.nup, t.ndn, t.NP, t.KP, f.qup, f.qdn, f.LDR,                \
-                         (const void*)t.Lp, thetaP, weight, tpart, exch);                         \
-  } while (0)
-  // one instantiation per row-tile count (flat 1 .. 7, BF16x3 1 .. 4; stack 1 .. 7, BF16x3
-  // 1 .. 3)
-#define LAUNCH_FLAT_K(BFV, KM)                                                                    \
-  do {                                                                                            \
-    switch (f.RT) {                                                                               \
-      case 1: LAUNCH_FLAT_KR(BFV, KM, 1); break;                                                  \
-      case 2: LAUNCH_FLAT_KR(BFV, KM, 2); break;                                                  \
-      case 3: LAUNCH_FLAT_KR(BFV, KM, 3); break;                                                  \
-      case 4: LAUNCH_FLAT_KR(BFV, KM, 4); break;                                                  \
-      case 5: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 5); break;                                        \
-      case 6: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 6); break;                                        \
-      default: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 7); break;                                       \
-    }                                                                                             \
-  } while (0)
-  // and per K chunk count (K_P = 32 .. 224 in steps of 32)
-#define LAUNCH_FLAT(BFV)                                                                          \
-  do {                                                                                            \
-    constexpr int KCH_ = BFV ? 32 : 16;                                                           \
-    switch (t.KP / KCH_) {                                                                        \
-      case 32 / KCH_: LAUNCH_FLAT_K(BFV, 32 / KCH_); break;                                       \
-      case 64 / KCH_: LAUNCH_FLAT_K(BFV, 64 / KCH_); break;                                       \
-      case 96 / KCH_: LAUNCH_FLAT_K(BFV, 96 / KCH_); break;                                       \
-      case 128 / KCH_: LAUNCH_FLAT_K(BFV, 128 / KCH_); break;                                     \
-      case 160 / KCH_: LAUNCH_FLAT_K(BFV, 160 / KCH_); break;                                     \
-      case 192 / KCH_: LAUNCH_FLAT_K(BFV, 192 / KCH_); break;                                     \
-      default: LAUNCH_FLAT_K(BFV, 224 / KCH_); break;                                             \
-    }                                                                                             \
-  } while (0)
-    if (bf) LAUNCH_FLAT(true);
-    else LAUNCH_FLAT(false);
-#undef LAUNCH_FLAT
-#undef LAUNCH_FLAT_K
-#undef LAUNCH_FLAT_KR
-    return hipGetLastError();
-  }
-  if (t.wide || tile == TILE_WIDE) {
-    dim3 grid(nw, 2 * n_det);
-#define LAUNCH_WIDE_K(NPV, BFV, KM)                                                             \
-  do {                                                                                          \
-    const size_t shm_ = wide_contract_lds_bytes_t<NPV, BFV>(t.KP);                              \
-    hipLaunchKernelGGL((k_contract_mfma_wide<NPV, BFV, KM>), grid, dim3(4 * NPV), shm_, st, nw, \
-                       G, t.nup, t.ndn, t.KP, (const void*)t.Lp, thetaP, weight, tpart, exch);  \
-  } while (0)
-  // one instantiation per K chunk count (K_P = 32 .. 224 in steps of 32)
-#define LAUNCH_WIDE(NPV, BFV)                                                                   \
-  do {                                                                                          \
-    constexpr int KCH_ = BFV ? 32 : 16;                                                         \
-    switch (t.KP / KCH_) {                                                                      \
-      case 32 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 32 / KCH_); break;                                \
-      case 64 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 64 / KCH_); break;                                \
-      case 96 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 96 / KCH_); break;                                \
-      case 128 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 128 / KCH_); break;                              \
-      case 160 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 160 / KCH_); break;                              \
-      case 192 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 192 / KCH_); break;                              \
-      default: LAUNCH_WIDE_K(NPV, BFV, 224 / KCH_); break;                                      \
-    }                                                                                           \
-  } while (0)
-    if (t.NP == 64) {
-      if (bf) LAUNCH_WIDE(64, true);
-      else LAUNCH_WIDE(64, false);
-    } else if (t.NP == 48) {
-      if (bf) LAUNCH_WIDE(48, true);
-      else LAUNCH_WIDE(48, false);
-    } else {
-      if (bf) LAUNCH_WIDE(32, true);
-      else LAUNCH_WIDE(32, false);
-    }
-#undef LAUNCH_WIDE
-#undef LAUNCH_WIDE_K
-    return hipGetLastError();
-  }
-  const int wpb = tile == TILE_W2 ? 2 : 4;
-  // the kernels are instantiated for K_P = 32, 64, 96, 128
-  if (t.KP % 32 != 0 || t.KP < 32 || t.KP > MFMA_KMAX) return hipErrorInvalidValue;
-  if (tile == TILE_BX || tile == TILE_BX8) {
-    const int wb = tile == TILE_BX8 ? 8 : 4;
-    const size_t shm = bx_contract_lds_bytes(t.KP, bf, wb);
-    dim3 grid((nw + wb - 1) / wb, 2 * n_det);
-#define LAUNCH_BX(BFV, NKV, WBV)                                                               \
-  do {                                                                                         \
-    (void)hipFuncSetAttribute((const void*)k_contract_mfma_bx<BFV, NKV, WBV>,                  \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
-    hipLaunchKernelGGL((k_contract_mfma_bx<BFV, NKV, WBV>), grid, dim3(64 * WBV), shm, st, nw, \
-                       G, t.nup, t.ndn, (const void*)t.Lp, thetaP, weight, tpart, exch);       \
-  } while (0)
-#define LAUNCH_BX_W(BFV, NKV)                                                                  \
-  case NKV:                                                                                    \
-    if (wb == 8) LAUNCH_BX(BFV, NKV, 8);                                                       \
-    else LAUNCH_BX(BFV, NKV, 4);                                                               \
-    break;
-    // one instantiation per K chunk count (K_P = 32 .. 128 in steps of 32)
-    if (bf) {
-      switch (t.KP / 32) { LAUNCH_BX_W(true, 1) LAUNCH_BX_W(true, 2) LAUNCH_BX_W(true, 3)
-                           default: LAUNCH_BX_W(true, 4) }
-    } else {
-      switch (t.KP / 16) { LAUNCH_BX_W(false, 2) LAUNCH_BX_W(false, 4) LAUNCH_BX_W(false, 6)
-                           default: LAUNCH_BX_W(false, 8) }
-    }
-#undef LAUNCH_BX_W
-#undef LAUNCH_BX
-    return hipGetLastError();
-  }
-  if (tile == TILE_PP) {
-    const size_t shm = pp_contract_lds_bytes(t.NP, t.KP, bf);
-    dim3 grid((nw + 7) / 8, 2 * n_det);
-#define LAUNCH_PP_K(NPV, BFV, NKV)                                                             \
-  do {                                                                                         \
-    (void)hipFuncSetAttribute((const void*)k_contract_mfma_pp<NPV, BFV, NKV>,                  \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
-    hipLaunchKernelGGL((k_contract_mfma_pp<NPV, BFV, NKV>), grid, dim3(512), shm, st, nw, G,   \
-                       t.nup, t.ndn, (const void*)t.Lp, thetaP, weight, tpart, exch);          \
-  } while (0)
-#define LAUNCH_PP(NPV, BFV)                                                                    \
-  do {                                                                                         \
-    constexpr int KCH_ = contract_kch<NPV, BFV>();                                             \
-    switch (t.KP / KCH_) {                                                                     \
-      case 32 / KCH_: LAUNCH_PP_K(NPV, BFV, 32 / KCH_); break;                                 \
-      case 64 / KCH_: LAUNCH_PP_K(NPV, BFV, 64 / KCH_); break;                                 \
-      case 96 / KCH_: LAUNCH_PP_K(NPV, BFV, 96 / KCH_); break;                                 \
-      default: LAUNCH_PP_K(NPV, BFV, 128 / KCH_); break;                                       \
-    }                                                                                          \
-  } while (0)
-    if (t.NP == 32) {
-      if (bf) LAUNCH_PP(32, true);
-      else LAUNCH_PP(32, false);
-    } else {
-      if (bf) LAUNCH_PP(16, true);
-      else LAUNCH_PP(16, false);
-    }
-#undef LAUNCH_PP
-#undef LAUNCH_PP_K
-    return hipGetLastError();
-  }
-  const size_t shm = mfma_contract_lds_bytes(t, wpb);
-  dim3 grid((nw + wpb - 1) / wpb, 2 * n_det);
-#define LAUNCH_CONTRACT_K(NPV, BFV, WPBV, NKV)                                                  \
-  do {                                                                                          \
-    (void)hipFuncSetAttribute((const void*)k_contract_mfma<NPV, BFV, WPBV, NKV>,                \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);            \
-    hipLaunchKernelGGL((k_contract_mfma<NPV, BFV, WPBV, NKV>), grid, dim3(64 * WPBV), shm, st,  \
-                       nw, G, t.nup, t.ndn, t.KP, (const void*)t.Lp, thetaP, weight, tpart,     \
-                       exch);                                                                   \
-  } while (0)
-  // one instantiation per K chunk count (K_P = 32 .. 128 in steps of 32)
-#define LAUNCH_CONTRACT(NPV, BFV, WPBV)                                                         \
-  do {                                                                                          \
-    constexpr int KCH_ = contract_kch<NPV, BFV>();                                              \
-    switch (t.KP / KCH_) {                                                                      \
-      case 32 / KCH_: LAUNCH_CONTRACT_K(NPV, BFV, WPBV, 32 / KCH_); break;                      \
-      case 64 / KCH_: LAUNCH_CONTRACT_K(NPV, BFV, WPBV, 64 / KCH_); break;                      \
-      case 96 / KCH_: LAUNCH_CONTRACT_K(NPV, BFV, WPBV, 96 / KCH_); break;                      \
-      default: LAUNCH_CONTRACT_K(NPV, BFV, WPBV, 128 / KCH_); break;                            \
-    }                                                                                           \
-  } while (0)
-  if (wpb == 4) {
-    if (t.NP == 32) {
-      if (bf) LAUNCH_CONTRACT(32, true, 4);
-      else LAUNCH_CONTRACT(32, false, 4);
-    } else {
-      if (bf) LAUNCH_CONTRACT(16, true, 4);
-      else LAUNCH_CONTRACT(16, false, 4);
-    }
-  } else {
-    if (t.NP == 32) {
-      if (bf) LAUNCH_CONTRACT(32, true, 2);
-      else LAUNCH_CONTRACT(32, false, 2);
-    } else {
-      if (bf) LAUNCH_CONTRACT(16, true, 2);
-      else LAUNCH_CONTRACT(16, false, 2);
-    }
-  }
-#undef LAUNCH_CONTRACT
-#undef LAUNCH_CONTRACT_K
-  return hipGetLastError();
-}
+                                double guard = 0.0);
 
 // ---------------------------------------------------------------------------
 // Overlap, determinant and Theta with the two small products on FP64 MFMA
@@ -643,7 +415,8 @@ inline hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int
 //   [T | I] -> [I | T^-1] (Gauss-Jordan, partial pivoting, log det from the pivots)
 //   Theta^T = (T^-1)^T U^T  (16x16 blocks, K = N, complex product as four real ones)
 // Outputs: e1 = tr(ht Theta), log det T (complex), singular flags, and the packed MFMA
-// operand of the contraction or (thetaT != NULL, for the FP64 VALU contraction) Theta^T in FP64.
+// operand of the contraction or (thetaT != NULL, for the FP64 VALU and virtual-space
+// contractions) Theta^T in FP64.
 // For the precision guard of the mixed modes (thmax != NULL): max |Theta_pc| of the block's
 // walker-spin in thmax and the FP64 packed operand (the layout of packed_kind 3) in packed64.
 // ---------------------------------------------------------------------------
@@ -844,7 +617,7 @@ __global__ void __launch_bounds__(256) k_overlap_mfma(
       const int c = 16 * a + q + 4 * v, p = 16 * b + l16;
       if (c >= N || p >= M) continue;
       const cd th = mkc(cr[v], ci[v]);
-      if (thetaT) Tw[(size_t)c * M + p] = th;   // FP64 copy only for the VALU contraction
+      if (thetaT) Tw[(size_t)c * M + p] = th;   // FP64 copy for the contractions that take it
       if (thmax) {
         th2max = fmax(th2max, th.re * th.re + th.im * th.im);
         double* o = packed64 + ((size_t)wd_ * 2 + s) * 2 * per + (size_t)c * KP + p;
@@ -937,8 +710,9 @@ __device__ inline void zero_packed_pad(E* base, int planes, size_t per, int N, i
 // lane reads those of its own half of the columns; row i loses f_i times that row, with
 // f_i = T_ik / T_pk and f_p = 1 - 1 / T_pk (which leaves the pivot row divided by the pivot);
 // column k then holds -f_i, and 1 / T_pk in row p_k.
-// With the precision guard (thmax != NULL) the FP64 operand is written only for a walker-spin
-// whose max |Theta| exceeds the guard's threshold: the guard redoes exactly those spins.
+// With the precision guard (thmax != NULL) the FP64 operand (Theta^T in guardT for the
+// virtual-space contraction, or packed64) is written only for a walker-spin whose max |Theta|
+// exceeds the guard's threshold: the guard redoes exactly those spins.
 // ---------------------------------------------------------------------------
 template <int NPAD>
 __global__ void __launch_bounds__(64, 2) k_overlap_wave(
@@ -946,7 +720,8 @@ __global__ void __launch_bounds__(64, 2) k_overlap_wave(
     const cd* __restrict__ U, const double* __restrict__ weight, int check_weight,
     cd* __restrict__ thetaT, cd* __restrict__ logdet, cd* __restrict__ e1,
     unsigned* __restrict__ wflag, void* __restrict__ packed, int packed_kind, int NP, int KP,
-    double* __restrict__ thmax, double* __restrict__ packed64, double guard) {
+    double* __restrict__ thmax, double* __restrict__ packed64, cd* __restrict__ guardT,
+    double guard) {
   static_assert(NPAD == 16 || NPAD == 32, "one wavefront inverts at most 32 x 32");
   constexpr int NB = NPAD / 16, NKC = NPAD / 16, XL = 33;
   __shared__ __attribute__((aligned(16))) cd Xs[32 * XL];   // T, then X
@@ -1213,6 +988,10 @@ __global__ void __launch_bounds__(64, 2) k_overlap_wave(
           const int c = 16 * a + q + 4 * v, p = pp;
           if (c >= N || p >= M) continue;
           const cd th = mkc(cr[a][v], ci[a][v]);
+          if (pass == 1 && guardT) {
+            guardT[((size_t)wd_ * ntot + off + c) * M + p] = th;
+            continue;
+          }
           if (pass == 1) {
             double* o = packed64 + ((size_t)wd_ * 2 + s) * 2 * per + (size_t)c * KP + p;
             o[0] = th.re;
@@ -1254,7 +1033,7 @@ __global__ void __launch_bounds__(64, 2) k_overlap_wave(
     zero_packed_pad(reinterpret_cast<float*>(packed) + ws_ * 2 * per, 2, per, N, M, NP, KP, lane);
   else if (packed_kind == 2)
     zero_packed_pad(reinterpret_cast<uint16_t*>(packed) + ws_ * 4 * per, 4, per, N, M, NP, KP, lane);
-  if (guarded) zero_packed_pad(packed64 + ws_ * 2 * per, 2, per, N, M, NP, KP, lane);
+  if (guarded && !guardT) zero_packed_pad(packed64 + ws_ * 2 * per, 2, per, N, M, NP, KP, lane);
   e1re = wave_sum(e1re);
   e1im = wave_sum(e1im);
   if (lane == 0) e1[2 * wd_ + s] = mkc(e1re, e1im);
