@@ -1769,25 +1769,23 @@ int mcd_scratch(void** out) {
 }
 
 // The decomposition on a workspace laid out as afqmc_mcd_workspace_bytes says: the residual
-// diagonal D, the dead flags and the McdState.  k_mcd_init writes every element of the three
-// that a decomposition of this M reads, so a reused workspace needs no clearing.
+// diagonal D; dead flags and block maxima; the McdState.  k_mcd_init writes every element of
+// the three that a decomposition of this M reads, so a reused workspace needs no clearing.
 int mcd_run(const double* eri, int32_t M, double delta, int32_t max_vectors, double* L_out,
             int32_t* n_vectors, int32_t* converged, void* workspace, hipStream_t st) {
   const size_t MM = (size_t)M * M;
+  const int nb = mcd_blocks((int)MM);
   double* D = at<double>(workspace, 0);
-  unsigned char* dead = at<unsigned char>(workspace, al256(MM * 8));
+  McdBest* best = at<McdBest>(workspace, al256(MM * 8));
+  unsigned long long* dead = reinterpret_cast<unsigned long long*>(best + 2 * (size_t)nb);
   McdState* state = at<McdState>(workspace, al256(MM * 8) + al256(MM));
-  hipLaunchKernelGGL(k_mcd_init, dim3((unsigned)((MM + 255) / 256)), dim3(256), 0, st, M, eri, D,
-                     dead, state);
+  hipLaunchKernelGGL(k_mcd_init, dim3(nb), dim3(64), 0, st, M, eri, D, dead, best, state);
   HIPCHK(hipGetLastError());
   McdState h{};
   int n = 0;
   for (; n <= max_vectors; ++n) {
-    hipLaunchKernelGGL(k_mcd_pivot, dim3(1), dim3(1024), 0, st, (int)MM, delta, n, max_vectors, D,
-                       dead, state);
-    if (n < max_vectors)
-      hipLaunchKernelGGL(k_mcd_column, dim3((unsigned)((MM + 255) / 256)), dim3(256), 0, st, M, n,
-                         eri, L_out, D, dead, state);
+    hipLaunchKernelGGL(k_mcd_vector, dim3(nb), dim3(1024), 0, st, M, n, delta, max_vectors, eri,
+                       L_out, D, dead, best, state);
     HIPCHK(hipGetLastError());
     if ((n & 31) == 31 || n == max_vectors) {
       HIPCHK(hipMemcpyAsync(&h, state, sizeof(h), hipMemcpyDeviceToHost, st));

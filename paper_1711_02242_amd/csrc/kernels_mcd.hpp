@@ -4,10 +4,17 @@
 // V_{mu nu} = v_pqrs with mu = p M + r, nu = q M + s, v stored as eri[p][q][r][s].
 // Only the diagonal of the residual, D_mu = (V - sum_g L^g L^g^T)_{mu mu}, is kept:
 // the pivot column of the residual is rebuilt from the tensor and the previous
-// vectors, c_mu = V_{mu nu0} - sum_g L^g_mu L^g_nu0.  Per vector:
-//   k_mcd_pivot : nu0 = argmax D (first index on ties), Dmax; stop when Dmax < delta;
-//                 damped prescreening sqrt(|D_mu| Dmax) <= min(1e-9, delta) -> mu dead;
-//   k_mcd_column: L_mu = c_mu / sqrt(Dmax) (0 for dead mu), D_mu -= L_mu^2.
+// vectors, c_mu = V_{mu nu0} - sum_g L^g_mu L^g_nu0.  Per vector, one launch of k_mcd_vector:
+//   nu0 = argmax D (first index on ties), Dmax; stop when Dmax < delta;
+//   damped prescreening sqrt(|D_mu| Dmax) <= min(1e-9, delta) -> mu dead (D_mu = 0);
+//   L_mu = c_mu / sqrt(Dmax) (0 for dead mu), D_mu -= L_mu^2.
+// What bounds it: the previous vectors are read once per vector (n M^2 doubles, mostly from the
+// L2 of the XCD that wrote them) behind a chain of a launch, the pivot and one latency per batch
+// of loads.  So a workgroup takes 64 mu with 16 wavefronts, wavefront v the vectors g = v, v + 16,
+// ...; L^g_nu0 is gathered into LDS by all threads at once; and each workgroup leaves the
+// argmax of its 64 new D for the next launch, where every workgroup reduces all of them.  (One
+// thread per mu running over all g, and a pivot launch of its own: 66 us per vector at M = 64
+// and up to 512 vectors, 33.7 ms in all; now 8.2 us per vector.)
 #pragma once
 
 #include "common.hpp"
@@ -15,107 +22,136 @@
 struct McdState {
   int done;       // 1 once converged or out of vectors
   int count;      // number of vectors when done
-  int piv;        // current pivot
+  int piv;        // unused
   int pad;
-  double dmax;    // current Dmax
+  double dmax;    // largest residual diagonal when done
 };
 
-__global__ void k_mcd_init(int M, const double* __restrict__ eri, double* __restrict__ D,
-                           unsigned char* __restrict__ dead, McdState* __restrict__ st) {
-  const int MM = M * M;
-  const int mu = blockIdx.x * blockDim.x + threadIdx.x;
+constexpr int MCD_B = 64;          // mu per workgroup
+constexpr int MCD_G = 1024;        // L^g_nu0 staged in LDS at a time
+
+// Largest D of a workgroup's mu (ties to the smallest mu).
+struct McdBest {
+  double d;
+  int mu, pad;
+};
+
+// Per workgroup b: dead bits of its 64 mu, and two McdBest (by parity of the vector), in the
+// M^2 bytes (rounded up to 256) that the workspace holds behind D: 40 bytes per 64 of them.
+__host__ __device__ inline int mcd_blocks(int MM) { return (MM + MCD_B - 1) / MCD_B; }
+
+__device__ __forceinline__ void mcd_best_of_wave(double d, int mu, McdBest* out, int lane) {
+  wave_argmax(d, mu);
+  if (lane == 0) *out = McdBest{d, mu, 0};
+}
+
+// One wavefront per 64 mu.
+__global__ void __launch_bounds__(64) k_mcd_init(int M, const double* __restrict__ eri,
+                                                 double* __restrict__ D,
+                                                 unsigned long long* __restrict__ dead,
+                                                 McdBest* __restrict__ best,
+                                                 McdState* __restrict__ st) {
+  const int MM = M * M, lane = threadIdx.x, mu = blockIdx.x * MCD_B + lane;
+  double d = -INFINITY;
   if (mu < MM) {
     const int p = mu / M, r = mu % M;
-    D[mu] = eri[(((size_t)p * M + p) * M + r) * M + r];
-    dead[mu] = 0;
+    d = eri[(((size_t)p * M + p) * M + r) * M + r];
+    D[mu] = d;
   }
+  // strict comparison with -infinity: a NaN diagonal is never chosen
+  mcd_best_of_wave(d > -INFINITY ? d : -INFINITY, d > -INFINITY ? mu : MM, &best[blockIdx.x], lane);
+  if (lane == 0) dead[blockIdx.x] = 0ull;
   if (mu == 0) {
     st->done = 0;
     st->count = 0;
     st->piv = -1;
+    st->pad = 0;
     st->dmax = 0.0;
   }
 }
 
-__global__ void __launch_bounds__(1024) k_mcd_pivot(int MM, double delta, int n, int max_vectors,
-                                                    double* __restrict__ D,
-                                                    unsigned char* __restrict__ dead,
-                                                    McdState* __restrict__ st) {
-  __shared__ double bv[16];
-  __shared__ int bi[16];
-  __shared__ double s_dmax;
-  __shared__ int s_stop;
-  if (threadIdx.x == 0) s_stop = st->done;
-  __syncthreads();
-  if (s_stop) return;
-  double best = -INFINITY;
-  int idx = MM;
-  for (int mu = threadIdx.x; mu < MM; mu += blockDim.x) {
-    const double v = D[mu];
-    if (v > best) {  // strict: the first (smallest) index wins within a thread's stride
-      best = v;
-      idx = mu;
-    }
-  }
-  // wave then block argmax, ties -> smallest index
-  wave_argmax(best, idx);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) {
-    bv[wid] = best;
-    bi[wid] = idx;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double b = -INFINITY;
-    int i = MM;
-    const int nwv = (blockDim.x + 63) / 64;
-    for (int k = 0; k < nwv; ++k)
-      if (bv[k] > b || (bv[k] == b && bi[k] < i)) {
-        b = bv[k];
-        i = bi[k];
+// Vector n.  best: [2][blocks], parity n & 1 read, the other written.
+__global__ void __launch_bounds__(1024) k_mcd_vector(int M, int n, double delta, int max_vectors,
+                                                     const double* __restrict__ eri,
+                                                     double* __restrict__ L /*[..][MM]*/,
+                                                     double* __restrict__ D,
+                                                     unsigned long long* __restrict__ dead,
+                                                     McdBest* __restrict__ best,
+                                                     McdState* __restrict__ st) {
+  __shared__ double s_l[MCD_G];
+  __shared__ double s_c[16][MCD_B];
+  __shared__ McdBest s_b[16];
+  const int MM = M * M, nb = mcd_blocks(MM);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (st->done) return;   // set by an earlier launch (or by this one: then every block stops below)
+  // ---- the pivot
+  {
+    const McdBest* in = best + (size_t)(n & 1) * nb;
+    double d = -INFINITY;
+    int mu = MM;
+    for (int b = tid; b < nb; b += 1024) {
+      const McdBest x = in[b];
+      if (x.d > d || (x.d == d && x.mu < mu)) {
+        d = x.d;
+        mu = x.mu;
       }
-    s_dmax = b;
-    if (!(b >= delta) || n >= max_vectors) {
-      st->done = 1;
-      st->count = n;
-      st->dmax = b;
-      s_stop = 1;
-    } else {
-      st->piv = i;
-      st->dmax = b;
     }
+    mcd_best_of_wave(d, mu, &s_b[wave], lane);
   }
   __syncthreads();
-  if (s_stop) return;
-  const double dmax = s_dmax;
-  const double screen = fmin(1e-9, delta);
-  for (int mu = threadIdx.x; mu < MM; mu += blockDim.x)
-    if (!dead[mu] && sqrt(fabs(D[mu]) * dmax) <= screen) {
-      dead[mu] = 1;
-      D[mu] = 0.0;
+  double dmax = -INFINITY;
+  int nu0 = MM;
+  for (int v = 0; v < 16; ++v) {
+    const McdBest x = s_b[v];
+    if (x.d > dmax || (x.d == dmax && x.mu < nu0)) {
+      dmax = x.d;
+      nu0 = x.mu;
     }
-}
-
-__global__ void __launch_bounds__(256) k_mcd_column(int M, int n, const double* __restrict__ eri,
-                                                    double* __restrict__ L /*[..][MM]*/,
-                                                    double* __restrict__ D,
-                                                    const unsigned char* __restrict__ dead,
-                                                    const McdState* __restrict__ st) {
-  if (st->done) return;
-  const int MM = M * M;
-  const int mu = blockIdx.x * blockDim.x + threadIdx.x;
-  if (mu >= MM) return;
-  const int nu0 = st->piv;
-  const double dmax = st->dmax;
-  double* Ln = L + (size_t)n * MM;
-  if (dead[mu]) {
-    Ln[mu] = 0.0;
+  }
+  if (!(dmax >= delta) || n >= max_vectors) {   // the same for every block
+    if (blockIdx.x == 0 && tid == 0) {
+      st->count = n;
+      st->dmax = dmax;
+      st->done = 1;
+    }
     return;
   }
-  const int p = mu / M, r = mu % M, q = nu0 / M, s = nu0 % M;
-  double c = eri[(((size_t)p * M + q) * M + r) * M + s];
-  for (int g = 0; g < n; ++g) c -= L[(size_t)g * MM + mu] * L[(size_t)g * MM + nu0];
-  const double l = c / sqrt(dmax);
-  Ln[mu] = l;
-  D[mu] = (mu == nu0) ? 0.0 : D[mu] - l * l;
+  // ---- c_mu: sums over the previous vectors, 16 wavefronts of 64 mu
+  const int mu = blockIdx.x * MCD_B + lane, muc = mu < MM ? mu : MM - 1;
+  double acc = 0.0;
+  for (int g0 = 0; g0 < n; g0 += MCD_G) {
+    __syncthreads();
+    if (g0 + tid < n) s_l[tid] = L[(size_t)(g0 + tid) * MM + nu0];
+    __syncthreads();
+    const int ng = n - g0 < MCD_G ? n - g0 : MCD_G;
+    const double* Lg = L + (size_t)g0 * MM + muc;
+#pragma unroll 8
+    for (int g = wave; g < ng; g += 16) acc = fma(Lg[(size_t)g * MM], s_l[g], acc);
+  }
+  s_c[wave][lane] = acc;
+  __syncthreads();
+  if (wave) return;
+  for (int v = 1; v < 16; ++v) acc += s_c[v][lane];
+  double d = -INFINITY;
+  bool gone = false;
+  if (mu < MM) {
+    const int p = mu / M, r = mu % M, q = nu0 / M, s = nu0 % M;
+    d = D[mu];
+    gone = (dead[blockIdx.x] >> lane) & 1ull;
+    if (!gone && sqrt(fabs(d) * dmax) <= fmin(1e-9, delta)) {
+      gone = true;
+      d = 0.0;
+    }
+    double l = 0.0;
+    if (!gone) {
+      l = (eri[(((size_t)p * M + q) * M + r) * M + s] - acc) / sqrt(dmax);
+      d = mu == nu0 ? 0.0 : d - l * l;
+    }
+    L[(size_t)n * MM + mu] = l;
+    D[mu] = d;
+  }
+  const unsigned long long bits = __ballot(gone);
+  if (lane == 0) dead[blockIdx.x] = bits;
+  mcd_best_of_wave(d > -INFINITY ? d : -INFINITY, d > -INFINITY ? mu : MM,
+                   &best[(size_t)((n + 1) & 1) * nb + blockIdx.x], lane);
 }
