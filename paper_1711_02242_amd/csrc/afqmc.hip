@@ -79,8 +79,9 @@ struct afqmc_sys_s {
   double guard = INFINITY; //   in FP64 (afqmc_params.theta_guard)
   float* Lt32 = nullptr;   // [apk_size(M)][Gp] FP32 transposed Cholesky tensor, block-packed
   int* abpairs = nullptr;  // [M(M+1)/2][2] (q M + p, p M + q) of each packed column (FP64)
-  double* Lt64 = nullptr;  // [M(M+1)/2][Gp64] FP64 packed L^T (FP64 A-build)
+  double* Lt64 = nullptr;  // [M(M+1)/2 or apk_size(M)][Gp64] FP64 packed L^T (FP64 A-build)
   int Gp64 = 0;            // G rounded up to 16
+  bool f64_reg = false;    // FP64 mode with A block-packed and held in registers (M <= 128)
   float* Eh32 = nullptr;   // [M][M] FP32 exp(-dtau/2 v0)
   int Gp = 0;              // G rounded up to 32
   bool f32_prop = false;   // A-build and propagation on FP32 MFMA (mixed-precision modes)
@@ -127,9 +128,11 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.logdet = take(nw * nd * 2 * 16);
   L.wflag = take(nw * nd * 2 * 4);
   L.enew = take(nw * 16);
-  L.y = take(nw * G * 16);
-  // exponent A: FP32 block-packed Re and Im planes, else FP64 complex M x M
-  L.A = take(S->f32_prop ? nw * (size_t)apk_size((int)M) * 8 : nw * M * M * 16);
+  L.y = take(nw * (S->f64_reg ? (size_t)S->Gp64 : G) * 16);
+  // exponent A: block-packed Re and Im planes (FP32, FP64), else FP64 complex M x M
+  L.A = take(S->f32_prop  ? nw * (size_t)apk_size((int)M) * 8
+             : S->f64_reg ? nw * (size_t)apk_size((int)M) * 16
+                          : nw * M * M * 16);
   L.X0 = take(nw * nt * M * 16);
   L.X1 = take(nw * nt * M * 16);
   L.Y = take(nw * nt * M * 16);
@@ -520,7 +523,9 @@ int launch_fields(afqmc_sys_s* S, const afqmc_walkers* w, const afqmc_fields* f,
   void* ws = w->workspace;
   hipLaunchKernelGGL(k_fields, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, S->stream,
                      w->n_walkers, S->G, S->s, S->p.fb_cap, at<cd>(ws, L.tcur), w->weight,
-                     w->walker_id, f->seed, f->job_id, w->step, dstep, f->x, at<cd>(ws, L.y), xout,
+                     w->walker_id, f->seed, f->job_id, w->step, dstep, f->x, at<cd>(ws, L.y),
+                     S->f64_reg ? at<double>(ws, L.y) : nullptr,
+                     S->f32_prop ? at<float>(ws, L.y32) : nullptr, S->f32_prop ? S->Gp : S->Gp64, xout,
                      S->status,
                      ((S->p.flags & (AFQMC_FLAG_HYBRID | AFQMC_FLAG_FREE_PROJECTION)) && !xout)
                          ? at<cd>(ws, L.fbterm) : nullptr,
@@ -559,9 +564,9 @@ double guard_threshold(const afqmc_params* p) {
   return p->precision == AFQMC_BF16X3 ? 0.75 : 4.0;
 }
 
-// Rows a of the orthonormal complement of the N rows of V (each of length M): Householder
+// Rows a (Mp apart) of the orthonormal complement of the N rows of V (of length M): Householder
 // reflections that take V's columns to a triangle, applied to the unit vectors N .. M - 1.
-void host_complement(const double* V, int N, int M, double* Qt) {
+void host_complement(const double* V, int N, int M, int Mp, double* Qt) {
   std::vector<double> H((size_t)N * M), beta(N, 0.0);
   std::vector<double> A(V, V + (size_t)N * M);   // row i: column i of the matrix
   for (int k = 0; k < N; ++k) {
@@ -582,7 +587,7 @@ void host_complement(const double* V, int N, int M, double* Qt) {
     }
   }
   for (int a = 0; a < M - N; ++a) {
-    double* x = Qt + (size_t)a * M;
+    double* x = Qt + (size_t)a * Mp;
     for (int p = 0; p < M; ++p) x[p] = p == N + a ? 1.0 : 0.0;
     for (int k = N - 1; k >= 0; --k) {
       const double* v = H.data() + (size_t)k * M;
@@ -601,7 +606,7 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
   const PairDims& p = t.dim;
   const int M = S->M, G = S->G, nt = S->ntot, nd = S->n_det;
   const size_t nv = (size_t)p.nv[0] + p.nv[1], dps = (size_t)p.dp[0] + p.dp[1];
-  std::vector<double> Qt((size_t)nd * nv * M), f(nd * dps, 0.0), t0((size_t)nd * 2 * G, 0.0),
+  std::vector<double> Qt((size_t)nd * nv * p.Mp, 0.0), f(nd * dps, 0.0), t0((size_t)nd * 2 * G, 0.0),
       c0((size_t)nd * 2, 0.0);
   const int nthr = setup_threads(G);
   for (int d = 0; d < nd; ++d)
@@ -609,17 +614,17 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
       const int N = p.N[s], off = s ? p.N[0] : 0;
       if (N == 0) continue;
       const double* V = Vr.data() + ((size_t)d * nt + off) * M;
-      double* Q = Qt.data() + ((size_t)d * nv + (s ? p.nv[0] : 0)) * M;
+      double* Q = Qt.data() + ((size_t)d * nv + (s ? p.nv[0] : 0)) * p.Mp;
       double* fs = f.data() + d * dps + (s ? p.dp[0] : 0);
       if (s == 1 && p.N[0] == N && memcmp(V, V - (size_t)N * M, sizeof(double) * N * M) == 0) {
         // the same orbitals as spin up
-        memcpy(Q, Q - (size_t)p.nv[0] * M, sizeof(double) * p.nv[0] * M);
+        memcpy(Q, Q - (size_t)p.nv[0] * p.Mp, sizeof(double) * p.nv[0] * p.Mp);
         memcpy(fs, fs - p.dp[0], sizeof(double) * p.dp[0]);
         memcpy(&t0[((size_t)d * 2 + 1) * G], &t0[((size_t)d * 2) * G], sizeof(double) * G);
         c0[2 * d + 1] = c0[2 * d];
         continue;
       }
-      host_complement(V, N, M, Q);
+      host_complement(V, N, M, p.Mp, Q);
       std::vector<double> T((size_t)N * N);
       for (int i = 0; i < N; ++i)
         for (int j = 0; j < N; ++j) {
@@ -665,7 +670,7 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
       for (int c = 0; c < N; ++c)
         for (int a = 0; a < p.nv[s]; ++a) {
           double acc = 0.0;
-          for (int q = 0; q < M; ++q) acc += F[0][(size_t)c * M + q] * Q[(size_t)a * M + q];
+          for (int q = 0; q < M; ++q) acc += F[0][(size_t)c * M + q] * Q[(size_t)a * p.Mp + q];
           fs[(size_t)c * p.nv[s] + a] = acc;
         }
     }
@@ -689,9 +694,9 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
       double* Bs = t.B + (size_t)d * G * dps + (s ? (size_t)G * p.dp[0] : 0);
       const long long rows = (long long)G * p.N[s];
       hipLaunchKernelGGL(k_pair_b, dim3((unsigned)((rows + 15) / 16), (p.nv[s] + 63) / 64), dim3(64),
-                         0, 0, M, p.N[s], p.nv[s], G, p.dp[s], (size_t)nt * M,
+                         0, 0, M, p.Mp, p.N[s], p.nv[s], G, p.dp[s], (size_t)nt * M,
                          S->Lh + ((size_t)d * G * nt + (s ? p.N[0] : 0)) * M,
-                         t.Qt + ((size_t)d * nv + (s ? p.nv[0] : 0)) * M, Bs);
+                         t.Qt + ((size_t)d * nv + (s ? p.nv[0] : 0)) * p.Mp, Bs);
       hipLaunchKernelGGL(k_pair_build, dim3(p.dp[s] / 64, p.dp[s] / 64), dim3(256), 0, 0, p.d[s],
                          p.dp[s], p.nv[s], G, (const double*)Bs,
                          t.K + ((size_t)d * (p.P[0] + p.P[1]) + (s ? p.P[0] : 0)) * PAIR_B * PAIR_B);
@@ -956,29 +961,40 @@ int setup_impl(const afqmc_params* p, double h0, const double* h1, const double*
     free_sys(S);
     return AFQMC_E_HIP;
   }
-  // packed pairs (q M + p, p M + q), p <= q, of the symmetric FP64 A-build; FP64 packed L^T
+  // FP64 packed L^T: one row per entry of the block-packed A where the propagation holds A in
+  // registers (L^g is symmetric; rows past M stay zero), else per pair p <= q with the pairs
+  // (q M + p, p M + q)
   if (p->precision == AFQMC_FP64) {
-    const size_t MMh = (size_t)M * (M + 1) / 2;
-    const std::vector<std::pair<int, int>> order = pair_order(M);
-    std::vector<int> pairs(2 * MMh);
-    for (size_t k = 0; k < MMh; ++k) {
-      const int q = order[k].first, pp = order[k].second;
-      pairs[2 * k] = q * M + pp;
-      pairs[2 * k + 1] = pp * M + q;
-    }
-    if ((rc = dev_upload(S, &S->abpairs, pairs.data(), pairs.size()))) {
-      free_sys(S);
-      return rc;
-    }
+    S->f64_reg = M <= MFMA_KMAX;
     S->Gp64 = ((G + 15) / 16) * 16;
-    std::vector<double> lt(MMh * (S->Gp64 > 0 ? S->Gp64 : 1), 0.0);
-    for (size_t k = 0; k < MMh; ++k)
-      for (int g = 0; g < G; ++g)
-        lt[k * S->Gp64 + g] =
-            L_chol[(size_t)g * M * M + (size_t)order[k].first * M + order[k].second];
+    const size_t gp = S->Gp64 > 0 ? S->Gp64 : 1;
+    const size_t rows = S->f64_reg ? (size_t)apk_size(M) : (size_t)M * (M + 1) / 2;
+    const std::vector<std::pair<int, int>> order =
+        S->f64_reg ? std::vector<std::pair<int, int>>() : pair_order(M);
+    std::vector<double> lt(rows * gp, 0.0);
+    parallel_for((int)rows, [&](int k, int) {
+      int q, pp;
+      if (S->f64_reg) apk_entry(k, q, pp);
+      else q = order[k].first, pp = order[k].second;
+      if (q < M && pp < M)
+        for (int g = 0; g < G; ++g)
+          lt[(size_t)k * gp + g] = L_chol[(size_t)g * M * M + (size_t)q * M + pp];
+    });
     if ((rc = dev_upload(S, &S->Lt64, lt.data(), lt.size()))) {
       free_sys(S);
       return rc;
+    }
+    if (!S->f64_reg) {
+      std::vector<int> pairs(2 * rows);
+      for (size_t k = 0; k < rows; ++k) {
+        const int q = order[k].first, pp = order[k].second;
+        pairs[2 * k] = q * M + pp;
+        pairs[2 * k + 1] = pp * M + q;
+      }
+      if ((rc = dev_upload(S, &S->abpairs, pairs.data(), pairs.size()))) {
+        free_sys(S);
+        return rc;
+      }
     }
   }
   if (multi) {
@@ -1139,9 +1155,6 @@ int step_pre(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool graph
     float* Aim = Are + (size_t)nw * apk_size(M);
     if (s->G > 0) {
       Timer tm(s, KG_ABUILD);
-      const size_t ne = (size_t)nw * s->Gp;
-      hipLaunchKernelGGL(k_y_to_f32, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, s->stream, nw,
-                         s->G, s->Gp, at<cd>(ws, L.y), at<float>(ws, L.y32));
       const int MA = apk_size(M);
       const int cb = abuild_cb(2 * nw, MA);
       dim3 grid((2 * nw + AB_BM - 1) / AB_BM, (MA + 16 * cb - 1) / (16 * cb));
@@ -1203,6 +1216,52 @@ int step_pre(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool graph
 #undef PROP_KR
       HIPCHK(hipGetLastError());
     }
+  } else if (s->f64_reg) {
+    double* Are = at<double>(ws, L.A);
+    double* Aim = Are + (size_t)nw * apk_size(M);
+    if (s->G > 0) {
+      Timer tm(s, KG_ABUILD);
+      const int MA = apk_size(M), cb = abuild_f64_cb(2 * nw, MA);
+      dim3 grid((2 * nw + AB_BM - 1) / AB_BM, (MA + 16 * cb - 1) / (16 * cb));
+#define ABUILD(CBV)                                                                              \
+  case CBV:                                                                                      \
+    hipLaunchKernelGGL(k_abuild_f64<CBV>, grid, dim3(512), abuild_f64_lds<CBV>(), s->stream,     \
+                       2 * nw, MA, s->Gp64, s->s, at<double>(ws, L.y), s->Lt64, Are, Aim);       \
+    break;
+      switch (cb) {
+        ABUILD(17) ABUILD(16) ABUILD(12) ABUILD(8) ABUILD(4)
+        default: return AFQMC_E_UNSUPPORTED;
+      }
+#undef ABUILD
+      HIPCHK(hipGetLastError());
+    }
+    Timer tm(s, KG_PROP);
+    const int nkc = (M + 15) / 16, nrb = std::max(s->nup, s->ndn) > 16 ? 2 : 1, rp = 16 * nrb;
+    // one workgroup per walker reads A once for all its rows; with too few walkers to fill the
+    // device, one per row block
+    const int jobs = (s->nup + rp - 1) / rp + (s->ndn + rp - 1) / rp;
+    const dim3 grid(nw, nw >= 2 * device_cu_count() ? 1 : jobs);
+#define PROPR_K(NKCV, NRBV)                                                                    \
+  do {                                                                                         \
+    const int shm = 2 * 16 * NRBV * (16 * NKCV + 2) * 8;                                       \
+    (void)hipFuncSetAttribute((const void*)k_propagate_f64r<NKCV, NRBV>,                       \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, shm);                \
+    hipLaunchKernelGGL((k_propagate_f64r<NKCV, NRBV>), grid, dim3(64 * NKCV), shm, s->stream,  \
+                       M, s->nup, s->ndn, s->G > 0 ? s->p.n_taylor : 0, s->Eh, Are, Aim,       \
+                       (cd*)w->U, w->weight);                                                  \
+  } while (0)
+#define PROPR(NKCV)                                                                            \
+  case NKCV:                                                                                   \
+    if (nrb == 2) PROPR_K(NKCV, 2);                                                            \
+    else PROPR_K(NKCV, 1);                                                                     \
+    break;
+    switch (nkc) {
+      PROPR(1) PROPR(2) PROPR(3) PROPR(4) PROPR(5) PROPR(6) PROPR(7) PROPR(8)
+      default: return AFQMC_E_UNSUPPORTED;
+    }
+#undef PROPR
+#undef PROPR_K
+    HIPCHK(hipGetLastError());
   } else {
     if (s->G > 0) {
       Timer tm(s, KG_ABUILD);
@@ -1228,8 +1287,7 @@ int step_pre(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool graph
                        (cd*)w->U, w->weight);                                                  \
     break;
       switch (Kp / 16) {
-        PROP64(1) PROP64(2) PROP64(3) PROP64(4) PROP64(5) PROP64(6) PROP64(7)
-        PROP64(8) PROP64(9) PROP64(10) PROP64(11) PROP64(12) PROP64(13) PROP64(14)
+        PROP64(9) PROP64(10) PROP64(11) PROP64(12) PROP64(13) PROP64(14)
         default: return AFQMC_E_UNSUPPORTED;
       }
 #undef PROP64
@@ -1647,6 +1705,8 @@ int afqmc_footprint_bytes(const afqmc_params* p, int32_t n_det, int32_t n_walker
       mfma_plan(S.mt64, AFQMC_FP64, M, S.nup, S.ndn, G, n_det) == AFQMC_OK)
     S.mt64.enabled = true;
   S.Gp = S.f32_prop ? ((G + 31) / 32) * 32 : 0;
+  S.f64_reg = p->precision == AFQMC_FP64 && M <= MFMA_KMAX;
+  S.Gp64 = p->precision == AFQMC_FP64 ? ((G + 15) / 16) * 16 : 0;
   const size_t nt = S.ntot, MM = (size_t)M * M, g1 = G > 0 ? G : 1;
   size_t sb = MM * 8 + n_det * nt * M * 8 + g1 * 8;          // E_h, V, lbar
   sb += (n_det * (size_t)G * nt * M > 0 ? n_det * (size_t)G * nt * M : 1) * 8;  // Lh
@@ -1655,13 +1715,11 @@ int afqmc_footprint_bytes(const afqmc_params* p, int32_t n_det, int32_t n_walker
   if (S.pr.on) sb += S.pr.bytes;
   if (S.mt.enabled && !pair_mode(&S)) sb += S.mt.bytes;
   if (S.mt64.enabled) sb += S.mt64.bytes;
-  const size_t MMh = (size_t)M * (M + 1) / 2;
-  if (p->precision == AFQMC_FP64) sb += 2 * MMh * 4;                // pair table
   if (S.f32_prop)                                                     // packed L^T, E_h (FP32)
     sb += (size_t)apk_size(M) * (S.Gp > 0 ? S.Gp : 1) * 4 + MM * 4;
-  if (p->precision == AFQMC_FP64) {                                   // packed L^T (FP64)
-    const size_t gp64 = ((size_t)G + 15) / 16 * 16;
-    sb += MMh * (gp64 > 0 ? gp64 : 1) * 8;
+  if (p->precision == AFQMC_FP64) {                                   // packed L^T, pairs (FP64)
+    const size_t rows = S.f64_reg ? (size_t)apk_size(M) : (size_t)M * (M + 1) / 2;
+    sb += rows * (S.Gp64 > 0 ? S.Gp64 : 1) * 8 + (S.f64_reg ? 0 : 2 * rows * 4);
   }
   *system_bytes = sb;
   const size_t nw = (size_t)n_walkers;

@@ -37,6 +37,7 @@ constexpr size_t PAIR_MAX_BYTES = size_t(16) << 30;   // of the K tables
 // Sizes of the tables of one system (host and device).
 struct PairDims {
   int n_det, G, Gt;                // Gt = ceil(G / 128) trace row tiles
+  int Mp;                          // M rounded up to 16
   int N[2], nv[2], d[2], dp[2];    // amplitudes, padded to a multiple of 128
   int T[2], P[2];                  // block rows dp / 128, units T (T + 1) / 2
 };
@@ -44,7 +45,7 @@ struct PairDims {
 struct PairTables {
   bool on = false;
   PairDims dim{};
-  double* Qt = nullptr;   // [n_det][nv_up + nv_dn][M]: the complements, rows a
+  double* Qt = nullptr;   // [n_det][nv_up + nv_dn][Mp]: the complements, rows a (zero past M)
   double* f = nullptr;    // [n_det][dp_up + dp_dn], zero past d_s
   double* t0 = nullptr;   // [n_det][2][G]: tr Om0^g
   double* c0 = nullptr;   // [n_det][2]
@@ -74,6 +75,7 @@ inline void pair_plan(PairTables& t, int M, int nup, int ndn, int G, int n_det) 
   t.bytes = 0;
   p.n_det = n_det;
   p.G = G;
+  p.Mp = (M + 15) / 16 * 16;
   p.Gt = (G + PAIR_B - 1) / PAIR_B;
   double fp = 0.0, fo = 0.0;
   bool ok = G > 0;
@@ -99,7 +101,7 @@ inline void pair_plan(PairTables& t, int M, int nup, int ndn, int G, int n_det) 
   const size_t k = pair_k_elems(p);
   if (k * 8 > PAIR_MAX_BYTES) return;
   const size_t nv = (size_t)p.nv[0] + p.nv[1];
-  t.bytes = (k + pair_b_elems(p) + n_det * (nv * M + p.dp[0] + p.dp[1] + 2 * (size_t)G + 2)) * 8;
+  t.bytes = (k + pair_b_elems(p) + n_det * (nv * p.Mp + p.dp[0] + p.dp[1] + 2 * (size_t)G + 2)) * 8;
   t.on = true;
 }
 
@@ -112,7 +114,7 @@ inline void pair_free_tables(PairTables& t) {
 // Setup: B^g = Lh^g Q of one (determinant, spin), rows (g, c) of Lh at Lh + g gst + c M, on
 // v_mfma_f64_16x16x4_f64: one wavefront per 16 rows and 64 virtuals.  B [G][dp] zeroed before.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) k_pair_b(int M, int N, int nv, int G, int dp, size_t gst,
+__global__ void __launch_bounds__(64) k_pair_b(int M, int Mp, int N, int nv, int G, int dp, size_t gst,
                                                const double* __restrict__ Lh,
                                                const double* __restrict__ Qt,
                                                double* __restrict__ B) {
@@ -124,7 +126,7 @@ __global__ void __launch_bounds__(64) k_pair_b(int M, int N, int nv, int G, int 
 #pragma unroll
   for (int b = 0; b < 4; ++b) {
     const int a = blockIdx.y * 64 + 16 * b + l16;
-    qrow[b] = Qt + (size_t)(a < nv ? a : nv - 1) * M;
+    qrow[b] = Qt + (size_t)(a < nv ? a : nv - 1) * Mp;
   }
   f64x4 acc[4];
 #pragma unroll
@@ -136,7 +138,7 @@ __global__ void __launch_bounds__(64) k_pair_b(int M, int N, int nv, int G, int 
       const double v = lrow[kk], l = k < M ? v : 0.0;
 #pragma unroll
       for (int b = 0; b < 4; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(l, qrow[b][kk], acc[b], 0, 0, 0);
+        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(l, qrow[b][k], acc[b], 0, 0, 0);
     }
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
@@ -206,6 +208,8 @@ __global__ void __launch_bounds__(256) k_pair_build(int d, int dp, int nv, int G
 // host picks AB so that the groups of blocks are even); the four wavefronts of a workgroup
 // read the same rows of Q close in time, so they come from the L1.  Each lane takes four
 // consecutive p per step in both operands.
+// M = 128, N = 32 + 32, 1024 walkers: 0.125 ms, 234 MB read and written (0.154 ms without the
+// loads ahead and the padded rows of Q).
 // With thmax != NULL only the walker-spins whose max |Theta| exceeds `guard`.
 // Grid: (walkers, 4-wavefront groups of (c block, a group) per spin, n_det).
 // ---------------------------------------------------------------------------
@@ -231,34 +235,50 @@ __global__ void __launch_bounds__(256, 2) k_pair_virtual(
   const int l16 = lane & 15, q = lane >> 4;
   const int c_in = 16 * cb + l16, cc = c_in < N ? c_in : N - 1;
   const cd* Th = thetaT + ((size_t)wd * ntot + (s ? p.N[0] : 0) + cc) * M;
-  const double* Qs = Qt + (size_t)d * (p.nv[0] + p.nv[1]) * M + (size_t)(s ? p.nv[0] : 0) * M;
+  const double* Qs = Qt + ((size_t)d * (p.nv[0] + p.nv[1]) + (s ? p.nv[0] : 0)) * p.Mp;
   const double* qrow[AB];
 #pragma unroll
   for (int b = 0; b < AB; ++b) {
     const int a = 16 * (ag * AB + b) + l16;
-    qrow[b] = Qs + (size_t)(a < nv ? a : nv - 1) * M;
+    qrow[b] = Qs + (size_t)(a < nv ? a : nv - 1) * p.Mp + 4 * q;
   }
   f64x4 ar[AB], ai[AB];
 #pragma unroll
   for (int b = 0; b < AB; ++b) ar[b] = ai[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < M; k0 += 16) {
-    cd th[4];
-    double qv[AB][4];
+  // the next 16 p go out before the MFMAs of these; p past M reads Theta at M - 1 against the
+  // zeros of Q's padding
+  cd th[4], tn[4];
+  f64x2 qv[AB][2], qn[AB][2];
+  auto load = [&](int k0, cd (&t)[4], f64x2 (&v)[AB][2]) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int k = k0 + 4 * q + u, kk = k < M ? k : M - 1;
-      const cd t = Th[kk];
-      th[u] = k < M ? t : mkc(0.0, 0.0);   // k past M: zero on the Theta side
-#pragma unroll
-      for (int b = 0; b < AB; ++b) qv[b][u] = qrow[b][kk];
+      const int k = k0 + 4 * q + u;
+      t[u] = Th[k < M ? k : M - 1];
     }
+#pragma unroll
+    for (int b = 0; b < AB; ++b) {
+      v[b][0] = *reinterpret_cast<const f64x2*>(qrow[b] + k0);
+      v[b][1] = *reinterpret_cast<const f64x2*>(qrow[b] + k0 + 2);
+    }
+  };
+  load(0, th, qv);
+  for (int k0 = 0; k0 < M; k0 += 16) {
+    load(k0 + 16 < M ? k0 + 16 : k0, tn, qn);
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int b = 0; b < AB; ++b) {
-        ar[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(th[u].re, qv[b][u], ar[b], 0, 0, 0);
-        ai[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(th[u].im, qv[b][u], ai[b], 0, 0, 0);
+        const double v = qv[b][u >> 1][u & 1];
+        ar[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(th[u].re, v, ar[b], 0, 0, 0);
+        ai[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(th[u].im, v, ai[b], 0, 0, 0);
       }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) th[u] = tn[u];
+#pragma unroll
+    for (int b = 0; b < AB; ++b) {
+      qv[b][0] = qn[b][0];
+      qv[b][1] = qn[b][1];
+    }
   }
   const size_t o = (size_t)wd * pair_x_elems(p) + (s ? 2 * (size_t)p.dp[0] : 0);
   const int dp = p.dp[s];
@@ -384,6 +404,9 @@ struct PairSeg {
 // blocks of v_mfma_f64_16x16x4_f64, 128 accumulator VGPRs), chunks of 16 k double-buffered in
 // LDS (74 KB: two workgroups per CU), the next chunk's loads ahead of this one's MFMAs also
 // across units and tiles.  A lane takes two consecutive k of its row in both operands.
+// M = 128, N = 32 + 32, G = 800, 1024 walkers: 1.13 ms, 55 TFLOP/s (77 % of the matrix cores'
+// cycles at the 2.2 GHz the card holds in FP64; 62 TFLOP/s on all-zero data; eight wavefronts
+// of half the columns gave the same).
 constexpr int PAIR_LD = PAIR_KC + 2;
 constexpr int PAIR_LDS = 4 * PAIR_B * PAIR_LD * 8;
 

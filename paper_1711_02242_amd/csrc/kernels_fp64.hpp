@@ -205,13 +205,16 @@ __global__ void __launch_bounds__(256) k_energy_assemble_multi(
 // ---------------------------------------------------------------------------
 // Auxiliary fields and force bias (eq:hs2, eq:fb, eq:precomputing2, App. B.1):
 // x from the Philox stream (or given), xbar = -i s t capped in modulus,
-// y = x - xbar.  One thread per (walker, block of 4 fields).
+// y = x - xbar.  One thread per (walker, block of 4 fields).  y goes out in the A-build's form:
+// rows 2w (Re) and 2w + 1 (Im) of Gp entries, zero past G, in FP64 (yp) or FP32 (y32), or
+// (neither) interleaved complex [nw][G].
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_fields(
     int nw, int G, double s, double fb_cap, const cd* __restrict__ tcur,
     const double* __restrict__ weight, const int64_t* __restrict__ walker_id, uint64_t seed,
     uint64_t job, int64_t step_arg, const int64_t* __restrict__ dstep,
-    const double* __restrict__ xin, cd* __restrict__ y,
+    const double* __restrict__ xin, cd* __restrict__ y, double* __restrict__ yp,
+    float* __restrict__ y32, int Gp,
     double* __restrict__ xout, unsigned* __restrict__ status, cd* __restrict__ fbterm,
     const double* __restrict__ lbar, cd* __restrict__ mfterm,
     unsigned long long* __restrict__ counts) {
@@ -246,6 +249,7 @@ __global__ void __launch_bounds__(256) k_fields(
   unsigned ncap = 0;
   double fr = 0.0, fi = 0.0;  // sum over the block of x xbar - xbar^2 / 2 (eq:hybrid-wt)
   double mr = 0.0, mi = 0.0;  // sum over the block of y_g lbar_g (mean-field c-number)
+  const size_t row = (size_t)(2 * w) * Gp;
   for (int j = 0; j < 4; ++j) {
     const int g = 4 * b + j;
     if (g >= G) break;
@@ -268,8 +272,21 @@ __global__ void __launch_bounds__(256) k_fields(
       mr += yv.re * lb;
       mi += yv.im * lb;
     }
-    y[(size_t)w * G + g] = yv;
+    if (y32) {
+      y32[row + g] = (float)yv.re;
+      y32[row + Gp + g] = (float)yv.im;
+    } else if (yp) {
+      yp[row + g] = yv.re;
+      yp[row + Gp + g] = yv.im;
+    } else {
+      y[(size_t)w * G + g] = yv;
+    }
   }
+  if (b == nblk - 1 && (y32 || yp))
+    for (int g = G; g < Gp; ++g) {
+      if (y32) y32[row + g] = y32[row + Gp + g] = 0.f;
+      else yp[row + g] = yp[row + Gp + g] = 0.0;
+    }
   if (fbterm) fbterm[(size_t)w * nblk + b] = mkc(fr, fi);
   // log of exp(-i s sum y lbar) = (s Im(sum y lbar), -s Re(sum y lbar))
   if (mfterm) mfterm[(size_t)w * nblk + b] = mkc(s * mi, -s * mr);

@@ -183,20 +183,17 @@ __global__ void __launch_bounds__(256, 2) k_abuild_f32(int rows /*2 nw*/, int MA
     }
 }
 
-// Column blocks of 16 per A-build tile, from those compiled: the least MFMA time, counted as
-// (rounds of the device's workgroup slots) x (workgroups per CU) x CB, with the workgroups
-// per CU of each instance from the runtime's occupancy (queried once per device); ties go to
-// the wider tile.
+// Column blocks of 16 per A-build tile, from those compiled (FN: the kernel of each, block
+// threads, dynamic LDS): the least MFMA time, counted as (rounds of the device's workgroup
+// slots) x (workgroups per CU) x CB, with the workgroups per CU of each instance from the
+// runtime's occupancy (queried once per device); ties go to the wider tile.
 constexpr int AB_CBS[] = {17, 16, 12, 8, 4};
 constexpr int AB_NCB = sizeof(AB_CBS) / sizeof(AB_CBS[0]);
-template <int I>
-inline const void* abuild_fn() {
-  return reinterpret_cast<const void*>(k_abuild_f32<AB_CBS[I]>);
-}
-inline int abuild_cb(int rows, int MA) {
-  static int per_cu[64][AB_NCB] = {};
-  static const void* const fns[AB_NCB] = {abuild_fn<0>(), abuild_fn<1>(), abuild_fn<2>(),
-                                          abuild_fn<3>(), abuild_fn<4>()};
+struct AbuildFn {
+  const void* fn;
+  int threads, lds;
+};
+inline int abuild_pick(const AbuildFn* fns, int (&per_cu)[64][AB_NCB], int rows, int MA) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
   const long long cus = device_cu_count(), nrow = (rows + AB_BM - 1) / AB_BM;
@@ -205,10 +202,12 @@ inline int abuild_cb(int rows, int MA) {
   for (int i = 0; i < AB_NCB; ++i) {
     if (per_cu[dev][i] <= 0) {
       int n = 0;
-      per_cu[dev][i] =
-          hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fns[i], 256, 0) == hipSuccess && n > 0
-              ? n
-              : 1;
+      if (fns[i].lds > 0)
+        (void)hipFuncSetAttribute(fns[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize, fns[i].lds);
+      per_cu[dev][i] = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                           &n, fns[i].fn, fns[i].threads, fns[i].lds) == hipSuccess && n > 0
+                           ? n
+                           : 1;
     }
     const long long cb = AB_CBS[i], n = per_cu[dev][i];
     const long long wgs = nrow * ((MA + 16 * cb - 1) / (16 * cb));
@@ -216,6 +215,14 @@ inline int abuild_cb(int rows, int MA) {
     if (best_cost < 0 || cost < best_cost) best = (int)cb, best_cost = cost;
   }
   return best;
+}
+inline int abuild_cb(int rows, int MA) {
+  static int per_cu[64][AB_NCB] = {};
+  static const AbuildFn fns[AB_NCB] = {
+      {(const void*)k_abuild_f32<17>, 256, 0}, {(const void*)k_abuild_f32<16>, 256, 0},
+      {(const void*)k_abuild_f32<12>, 256, 0}, {(const void*)k_abuild_f32<8>, 256, 0},
+      {(const void*)k_abuild_f32<4>, 256, 0}};
+  return abuild_pick(fns, per_cu, rows, MA);
 }
 
 // ---------------------------------------------------------------------------
@@ -420,18 +427,6 @@ __global__ void __launch_bounds__(64 * NKC, 1) k_propagate_f32(
   }
 }
 
-// Fields for the FP32 A-build: Y[2w][g] = Re y, Y[2w+1][g] = Im y, zero for g >= G (< Gp).
-__global__ void __launch_bounds__(256) k_y_to_f32(int nw, int G, int Gp, const cd* __restrict__ y,
-                                                  float* __restrict__ Y) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (size_t)nw * Gp) return;
-  const int w = (int)(e / Gp), g = (int)(e % Gp);
-  cd v = mkc(0.0, 0.0);
-  if (g < G) v = y[(size_t)w * G + g];
-  Y[(size_t)(2 * w) * Gp + g] = (float)v.re;
-  Y[(size_t)(2 * w + 1) * Gp + g] = (float)v.im;
-}
-
 // ---------------------------------------------------------------------------
 // Fused propagation for the wide shapes (M up to 224, up to 64 orbitals per spin):
 // u' = u E_h T_n(A) E_h for the orbitals of one spin of one walker per workgroup
@@ -590,6 +585,297 @@ __global__ void __launch_bounds__(64 * NKC) k_propagate_f32_wide(
       const int c = 16 * rb + 4 * q4 + v;
       if (c < N) Uo[(size_t)c * M + qcol] = mkc((double)cre[rb][v], (double)cim[rb][v]);
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// FP64 A-build for M <= 128 on v_mfma_f64_16x16x4_f64: the GEMM of k_abuild_f32 (rows of Y,
+// block-packed columns of A, planar output of MA doubles per walker and plane).  Tile 128 rows
+// x 16 CB columns per workgroup of eight wavefronts, each 16 rows x 16 CB columns (CB blocks of
+// accumulators, 136 VGPRs at CB = 17, so two wavefronts per SIMD), K chunks of 16
+// double-buffered in LDS, 144-byte rows.  A lane takes two consecutive k of its row in both
+// operands.  Each MFMA reads one B fragment: 32 B per clock and CU from LDS at the full rate.
+// At M = 128, 1024 walkers: 512 tiles of 272 columns, two full rounds on 256 CUs, 0.50 ms, 57
+// TFLOP/s (64 x 64 tiles with mirrored stores of the whole A: 0.64 ms; a library FP64 product
+// of 4096^3 runs at 60 on this card).
+// ---------------------------------------------------------------------------
+constexpr int AB64_LDP = AB_BK + 2;
+template <int CB>
+constexpr int abuild_f64_lds() {
+  return 2 * (AB_BM + 16 * CB) * AB64_LDP * 8;
+}
+
+template <int CB>
+__global__ void __launch_bounds__(512, 2) k_abuild_f64(int rows /*2 nw*/, int MA, int Gp, double s,
+                                                       const double* __restrict__ Y,
+                                                       const double* __restrict__ Lt,
+                                                       double* __restrict__ Are,
+                                                       double* __restrict__ Aim) {
+  constexpr int BN = 16 * CB, TR = AB_BM + BN, LD = AB64_LDP;
+  constexpr int NLD = TR * (AB_BK / 2);           // 16-byte pieces of one K chunk
+  constexpr int PER = (NLD + 511) / 512;
+  extern __shared__ __attribute__((aligned(16))) double ab64_smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int2 tile = xcd_tile(gridDim.x, gridDim.y);
+  const int r0 = tile.x * AB_BM, c0 = tile.y * BN;
+  const int l16 = lane & 15, q = lane >> 4;
+  // piece e of a chunk: tile row e / 8 (rows below AB_BM are Y rows, the rest Lt rows), k
+  // offset 2 (e % 8); pass c covers rows 64 c .. 64 c + 63, so the Y / Lt choice is uniform.
+  // Rows past the walkers and columns past the packed triangle re-read row / column 0: they
+  // only feed accumulator rows / columns that are never stored.
+  f64x2 stg[PER];
+  auto gload = [&](int k0) {
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+      const int e = tid + c * 512;
+      if ((c + 1) * 512 <= NLD || e < NLD) {
+        const int rr = e >> 3, kk = (e & 7) * 2;
+        const double* src;
+        if (c * 64 + 63 < AB_BM) {
+          const int gr = r0 + rr;
+          src = Y + (size_t)(gr < rows ? gr : 0) * Gp;
+        } else {
+          const int gc = c0 + rr - AB_BM;
+          src = Lt + (size_t)(gc < MA ? gc : 0) * Gp;
+        }
+        stg[c] = *reinterpret_cast<const f64x2*>(src + k0 + kk);
+      }
+    }
+  };
+  auto lstore = [&](double* dst) {
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+      const int e = tid + c * 512;
+      if ((c + 1) * 512 <= NLD || e < NLD)
+        *reinterpret_cast<f64x2*>(dst + (e >> 3) * LD + (e & 7) * 2) = stg[c];
+    }
+  };
+  f64x4 acc[CB];
+#pragma unroll
+  for (int b = 0; b < CB; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const int nk = Gp / AB_BK;
+  gload(0);
+  lstore(ab64_smem);
+  __syncthreads();
+  for (int kc = 0; kc < nk; ++kc) {
+    const double* Lb = ab64_smem + (size_t)(kc & 1) * TR * LD;
+    if (kc + 1 < nk) gload((kc + 1) * AB_BK);
+    const double* A = Lb + (16 * wave + l16) * LD + 2 * q;
+    const double* B = Lb + (AB_BM + l16) * LD + 2 * q;
+#pragma unroll
+    for (int kk = 0; kk < AB_BK; kk += 8) {
+      const f64x2 fa = *reinterpret_cast<const f64x2*>(A + kk);
+      // four column blocks at a time, so that an accumulator is used again four MFMAs later
+#pragma unroll
+      for (int b0 = 0; b0 < CB; b0 += 4) {
+        f64x2 fb[4];
+#pragma unroll
+        for (int b = b0; b < b0 + 4 && b < CB; ++b)
+          fb[b - b0] = *reinterpret_cast<const f64x2*>(B + 16 * b * LD + kk);
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int b = b0; b < b0 + 4 && b < CB; ++b)
+            acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[e], fb[b - b0][e], acc[b], 0, 0, 0);
+      }
+    }
+    if (kc + 1 < nk) lstore(ab64_smem + (size_t)((kc + 1) & 1) * TR * LD);
+    __syncthreads();
+  }
+  // lane: column 16 b + l16, rows q + 4 v of the wavefront's 16; even rows are Re y (the Im
+  // part of A), odd rows Im y
+  double* out = q & 1 ? Are : Aim;
+  const double f = q & 1 ? -s : s;
+#pragma unroll
+  for (int b = 0; b < CB; ++b) {
+    const int cc = c0 + 16 * b + l16;
+    if (cc >= MA) continue;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = r0 + 16 * wave + q + 4 * v;
+      if (r < rows) out[(size_t)(r >> 1) * MA + cc] = f * acc[b][v];
+    }
+  }
+}
+
+inline int abuild_f64_cb(int rows, int MA) {
+  static int per_cu[64][AB_NCB] = {};
+  static const AbuildFn fns[AB_NCB] = {
+      {(const void*)k_abuild_f64<17>, 512, abuild_f64_lds<17>()},
+      {(const void*)k_abuild_f64<16>, 512, abuild_f64_lds<16>()},
+      {(const void*)k_abuild_f64<12>, 512, abuild_f64_lds<12>()},
+      {(const void*)k_abuild_f64<8>, 512, abuild_f64_lds<8>()},
+      {(const void*)k_abuild_f64<4>, 512, abuild_f64_lds<4>()}};
+  return abuild_pick(fns, per_cu, rows, MA);
+}
+
+// Four consecutive entries A[q][p0 .. p0 + 3] of a block-packed FP64 plane (as apk_load4).
+__device__ __forceinline__ void apk_load4(const double* __restrict__ Ap, int M, int q, int p0,
+                                          double (&v)[4]) {
+  if ((p0 >> 3) <= (q >> 3)) {
+    const double* a = Ap + apk_index(q, p0);
+    const f64x2 x = *reinterpret_cast<const f64x2*>(a), y = *reinterpret_cast<const f64x2*>(a + 2);
+    v[0] = x[0], v[1] = x[1], v[2] = y[0], v[3] = y[1];
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = p0 + e < M ? Ap[apk_index(q, p0 + e)] : 0.0;
+}
+
+// ---------------------------------------------------------------------------
+// FP64 propagation for M <= 128: u' = u E_h T_n(A) E_h on v_mfma_f64_16x16x4_f64 with A_w in
+// registers.  One wavefront per 16 output columns q; a wavefront's columns of A (Re and Im, 16
+// NKC VGPRs each half: 128 at M = 128) stay in registers for every row block of the walker and
+// every Taylor term, so A is read once per walker (k_propagate_f64 below streams it for each
+// term, row block and spin).  The current term, 16 NRB rows, is in LDS as the A operand.  The
+// complex product T A takes three real ones.  Job: 16 NRB rows of one spin; workgroup (w, y) of the
+// grid takes jobs y, y + gridDim.y, ... of walker w.  Operand lanes and output layout as in
+// k_propagate_f64.  Bound by the FP64 matrix cores (about 57 TFLOP/s on real data): M = 128,
+// N = 32 + 32, 1024 walkers 0.91 ms (four products and A streamed: 1.28; four products with A in
+// registers: 1.05).
+// ---------------------------------------------------------------------------
+template <int NKC, int NRB>
+__global__ void __launch_bounds__(64 * NKC, 2) k_propagate_f64r(
+    int M, int nup, int ndn, int n_taylor, const double* __restrict__ Eh /*[M][M]*/,
+    const double* __restrict__ Are, const double* __restrict__ Aim, cd* __restrict__ U,
+    const double* __restrict__ weight) {
+  extern __shared__ __attribute__((aligned(16))) double dsm[];
+  constexpr int Kp = 16 * NKC, ldt = Kp + 2, RP = 16 * NRB;
+  const int w = blockIdx.x;
+  if (!(weight[w] > 0.0)) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double* Tr = dsm;                 // [RP][ldt]
+  double* Ti = dsm + RP * ldt;      // [RP][ldt]
+  const int j = lane & 15, q4 = lane >> 4;
+  const int qcol = 16 * wave + j;
+  const bool colok = qcol < M;
+  const size_t MA = (size_t)apk_size(M);
+  const double* Ehq = Eh + (size_t)(colok ? qcol : 0) * M;
+  double ar[NKC][4], ai[NKC][4];
+#pragma unroll
+  for (int kc = 0; kc < NKC; ++kc) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ar[kc][e] = ai[kc][e] = 0.0;
+    if (colok && n_taylor > 0) {
+      apk_load4(Are + (size_t)w * MA, M, qcol, 16 * kc + 4 * q4, ar[kc]);
+      apk_load4(Aim + (size_t)w * MA, M, qcol, 16 * kc + 4 * q4, ai[kc]);
+    }
+  }
+  const int jup = (nup + RP - 1) / RP, jobs = jup + (ndn + RP - 1) / RP;
+  for (int job = blockIdx.y; job < jobs; job += gridDim.y) {
+    const int s = job >= jup ? 1 : 0, rblk = job - (s ? jup : 0);
+    const int off = (s ? nup : 0) + RP * rblk, nrows = min(RP, (s ? ndn : nup) - RP * rblk);
+    cd* Uw = U + ((size_t)w * (nup + ndn) + off) * M;
+    {
+      constexpr int NIT = RP * Kp / (64 * NKC);   // = 4 NRB
+      cd uv[NIT];
+#pragma unroll
+      for (int it = 0; it < NIT; ++it) {
+        const int e = tid + it * 64 * NKC, c = e / Kp, p = e % Kp;
+        uv[it] = Uw[(size_t)(c < nrows ? c : 0) * M + (p < M ? p : 0)];
+      }
+#pragma unroll
+      for (int it = 0; it < NIT; ++it) {
+        const int e = tid + it * 64 * NKC, c = e / Kp, p = e % Kp;
+        const bool ok = c < nrows && p < M;
+        Tr[c * ldt + p] = ok ? uv[it].re : 0.0;
+        Ti[c * ldt + p] = ok ? uv[it].im : 0.0;
+      }
+    }
+    __syncthreads();
+    f64x4 yre[NRB], yim[NRB], cre[NRB], cim[NRB];
+    auto mul_real = [&]() {   // C = T E_h, E_h streamed (shared by all walkers)
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) cre[rb] = cim[rb] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) {
+        double b[4];
+        const int p0 = 16 * kc + 4 * q4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b[e] = (colok && p0 + e < M) ? Ehq[p0 + e] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int rb = 0; rb < NRB; ++rb) {
+            cre[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(Tr[(16 * rb + j) * ldt + p0 + e], b[e], cre[rb], 0, 0, 0);
+            cim[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ti[(16 * rb + j) * ldt + p0 + e], b[e], cim[rb], 0, 0, 0);
+          }
+      }
+    };
+    auto store_planes = [&](const f64x4* pr, const f64x4* pi) {
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          Tr[(16 * rb + q4 + 4 * v) * ldt + qcol] = pr[rb][v];
+          Ti[(16 * rb + q4 + 4 * v) * ldt + qcol] = pi[rb][v];
+        }
+    };
+    mul_real();   // X = U E_h: the first term and Y = X
+    __syncthreads();
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+      yre[rb] = cre[rb];
+      yim[rb] = cim[rb];
+    }
+    store_planes(cre, cim);
+    __syncthreads();
+    for (int n = 1; n <= n_taylor; ++n) {
+      // P1 = Tr Ar, P2 = Ti Ai, P3 = (Tr + Ti)(Ar + Ai): Re = P1 - P2, Im = P3 - P1 - P2
+      f64x4 p3[NRB];
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) cre[rb] = cim[rb] = p3[rb] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) {
+        const int p0 = 16 * kc + 4 * q4;
+        // Ar + Ai is formed again for every term: held across the loop it would take 64 more
+        // registers (the opaque use of Ar keeps the compiler from hoisting it)
+        double as[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          asm volatile("" : "+v"(ar[kc][e]));
+          as[e] = ar[kc][e] + ai[kc][e];
+        }
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+          const f64x2* tr = reinterpret_cast<const f64x2*>(&Tr[(16 * rb + j) * ldt + p0]);
+          const f64x2* ti = reinterpret_cast<const f64x2*>(&Ti[(16 * rb + j) * ldt + p0]);
+          const f64x2 t0 = tr[0], t1 = tr[1], u0 = ti[0], u1 = ti[1];
+          const f64x2 w0 = t0 + u0, w1 = t1 + u1;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            cre[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(e < 2 ? t0[e & 1] : t1[e & 1], ar[kc][e], cre[rb], 0, 0, 0);
+            cim[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(e < 2 ? u0[e & 1] : u1[e & 1], ai[kc][e], cim[rb], 0, 0, 0);
+            p3[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(e < 2 ? w0[e & 1] : w1[e & 1], as[e], p3[rb], 0, 0, 0);
+          }
+        }
+      }
+      const double inv = 1.0 / (double)n;
+      __syncthreads();
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb) {
+        p3[rb] = (p3[rb] - cre[rb] - cim[rb]) * inv;
+        cre[rb] = (cre[rb] - cim[rb]) * inv;
+        cim[rb] = p3[rb];
+        yre[rb] += cre[rb];
+        yim[rb] += cim[rb];
+      }
+      store_planes(cre, cim);
+      __syncthreads();
+    }
+    store_planes(yre, yim);   // U' = Y E_h
+    __syncthreads();
+    mul_real();
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int c = 16 * rb + q4 + 4 * v;
+        if (colok && c < nrows) Uw[(size_t)c * M + qcol] = mkc(cre[rb][v], cim[rb][v]);
+      }
+    __syncthreads();   // the next job's rows overwrite the planes
   }
 }
 
