@@ -55,7 +55,7 @@ struct TimedLaunch {
 struct WsLayout {
   size_t thetaT, tcur, tpart, exch, e1, logdet, wflag, enew, y, A, X0, X1, Y, parent, csum,
       wnew, asnap, lsnap, esum, thetaP, y32, fbterm, mfterm, logR, psnap, ldc, wflc, dstep, growth,
-      thmax, thetaP64, glist, slist, gcount, part, psplit, pstart, total;
+      thmax, thetaP64, glist, slist, ulist, gcount, part, psplit, pstart, total;
 };
 
 }  // namespace
@@ -123,7 +123,7 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.thetaT = take(S->mt.enabled && !S->pr.on ? 0 : nw * nd * nt * M * 16);
   L.tcur = take(nw * G * 16);
   L.tpart = take(nw * nd * 2 * G * 16);
-  L.exch = take(nw * nd * 2 * 16);
+  L.exch = take(nw * nd * 2 * 16 * (mfma_tile_splits(S->mt, TILE_DEFAULT) ? CONTRACT_MAX_SPLITS : 1));
   L.e1 = take(nw * nd * 2 * 16);
   L.logdet = take(nw * nd * 2 * 16);
   L.wflag = take(nw * nd * 2 * 4);
@@ -159,7 +159,8 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.thetaP64 = take(!S->guard_on ? 0 : S->pr.on ? xb : mfma_theta_bytes(S->mt64, nw));
   L.glist = take(S->guard_on ? nw * 4 : 0);
   L.slist = take(S->guard_on ? nw * 8 : 0);
-  L.gcount = take(S->guard_on ? 16 : 0);
+  L.ulist = take(S->guard_on ? nw * 8 : 0);
+  L.gcount = take(S->guard_on ? 32 : 0);
   const int cus = device_cu_count();
   L.part = take(S->pr.on ? pair_part_elems(S->pr.dim, (int)nw, cus) * 16 : 0);
   L.psplit = take(S->pr.on ? pair_split_elems(S->pr.dim) * 16 : 0);
@@ -403,8 +404,27 @@ int launch_overlap(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L, in
   return AFQMC_OK;
 }
 
-// The local-energy contraction and the energy assembly.  `in_step` counts the walkers the
-// precision guard redoes in FP64 (the counters of afqmc_get_bound_counts cover steps only).
+// Exchange partial sums of the contraction in use (splits of the Cholesky vectors).  Without
+// the virtual-space form the guard's FP64 kernel overwrites a whole sum: no splits then.
+int exch_splits(const afqmc_sys_s* S, int nw) {
+  if (S->guard_on && !S->pr.on) return 1;
+  return mfma_splits(S->mt, nw, S->n_det, S->G, S->tile);
+}
+
+// Before the contraction: the precision guard's lists of walkers.  `in_step` counts the walkers
+// it redoes in FP64 (the counters of afqmc_get_bound_counts cover steps only).
+int launch_guard_list(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L, bool in_step) {
+  if (!S->guard_on) return AFQMC_OK;
+  void* ws = w->workspace;
+  Timer tm(S, KG_GUARD);
+  hipLaunchKernelGGL(k_guard_list, dim3(1), dim3(1024), 0, S->stream, w->n_walkers, S->n_det,
+                     S->guard, w->weight, (const double*)at<double>(ws, L.thmax),
+                     at<int>(ws, L.glist), at<int>(ws, L.slist), at<int>(ws, L.ulist),
+                     at<int>(ws, L.gcount), in_step ? S->capcount : nullptr);
+  HIPCHK(hipGetLastError());
+  return AFQMC_OK;
+}
+
 // The contraction proper (tpart, exch of every walker in the system's precision).
 int launch_contraction(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L) {
   void* ws = w->workspace;
@@ -437,25 +457,28 @@ int launch_contraction(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L
     HIPCHK(hipGetLastError());
   } else {
     Timer tm(S, KG_CONTRACT);
+    // walker-spins above the guard's threshold are left to its FP64 pass
+    ContractSel sel{};
+    if (S->guard_on)
+      sel = ContractSel{at<int>(ws, L.ulist), at<int>(ws, L.gcount) + 3, at<double>(ws, L.thmax),
+                        S->guard, w->n_walkers, 0};
+    sel.stride = (size_t)w->n_walkers * S->n_det * 2;
     HIPCHK(mfma_contract(S->mt, S->stream, w->n_walkers, S->n_det, S->G, at<void>(ws, L.thetaP),
-                         w->weight, at<cd>(ws, L.tpart), at<cd>(ws, L.exch), S->tile));
+                         w->weight, at<cd>(ws, L.tpart), at<cd>(ws, L.exch), S->tile, sel,
+                         exch_splits(S, w->n_walkers)));
   }
   return AFQMC_OK;
 }
 
 // After the contraction: the precision guard's FP64 pass and the energy assembly.
-int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L,
-                          bool in_step) {
+int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L) {
   void* ws = w->workspace;
+  const int nz = exch_splits(S, w->n_walkers);
+  const size_t xst = (size_t)w->n_walkers * S->n_det * 2;
   if (S->mt.enabled && S->guard_on) {
-    // walkers far from the trial (large Theta) again in FP64, over the partial sums of the
-    // low-precision pass: of a listed walker, the spins whose max |Theta| exceeds the threshold
+    // walkers far from the trial (large Theta) in FP64: of a listed walker, the spins whose
+    // max |Theta| exceeds the threshold
     Timer tm(S, KG_GUARD);
-    hipLaunchKernelGGL(k_guard_list, dim3(1), dim3(1024), 0, S->stream, w->n_walkers, S->n_det,
-                       S->guard, w->weight, (const double*)at<double>(ws, L.thmax),
-                       at<int>(ws, L.glist), at<int>(ws, L.slist), at<int>(ws, L.gcount),
-                       in_step ? S->capcount : nullptr);
-    HIPCHK(hipGetLastError());
     if (S->pr.on) {
       const double* thmax = at<double>(ws, L.thmax);
       pair_virtual(S->pr, S->stream, w->n_walkers, S->M, at<cd>(ws, L.thetaT), w->weight,
@@ -464,20 +487,22 @@ int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout
       HIPCHK(pair_contract(S->pr, S->stream, w->n_walkers, device_cu_count(),
                            at<double>(ws, L.thetaP64), at<cd>(ws, L.tpart), at<cd>(ws, L.exch),
                            at<cd>(ws, L.part), at<cd>(ws, L.psplit), at<long long>(ws, L.pstart),
-                           at<int>(ws, L.slist), at<int>(ws, L.gcount) + 1, thmax, S->guard));
+                           at<int>(ws, L.slist), at<int>(ws, L.gcount) + 1, thmax, S->guard, nz,
+                           xst));
     } else {
       HIPCHK(mfma_contract(S->mt64, S->stream, w->n_walkers, S->n_det, S->G,
                            at<void>(ws, L.thetaP64), w->weight, at<cd>(ws, L.tpart),
-                           at<cd>(ws, L.exch), TILE_DEFAULT, at<int>(ws, L.glist),
-                           at<int>(ws, L.gcount), (const double*)at<double>(ws, L.thmax),
-                           S->guard));
+                           at<cd>(ws, L.exch), TILE_DEFAULT,
+                           ContractSel{at<int>(ws, L.glist), at<int>(ws, L.gcount),
+                                       at<double>(ws, L.thmax), S->guard, w->n_walkers, 0},
+                           1));
     }
   }
   if (S->multi) {
     Timer tm(S, KG_ASSEMBLE);
     hipLaunchKernelGGL(k_energy_assemble_multi, dim3(w->n_walkers), dim3(256), 0, S->stream, S->G,
                        S->n_det, S->h0, (double)S->sf, S->coef, at<cd>(ws, L.tpart),
-                       at<cd>(ws, L.exch), at<cd>(ws, L.e1), at<cd>(ws, L.logdet),
+                       at<cd>(ws, L.exch), nz, xst, at<cd>(ws, L.e1), at<cd>(ws, L.logdet),
                        at<unsigned>(ws, L.wflag), w->weight, 1, at<cd>(ws, L.tcur),
                        at<cd>(ws, L.enew), at<cd>(ws, L.ldc), at<unsigned>(ws, L.wflc));
     HIPCHK(hipGetLastError());
@@ -485,7 +510,7 @@ int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout
     Timer tm(S, KG_ASSEMBLE);
     hipLaunchKernelGGL(k_energy_assemble, dim3(w->n_walkers), dim3(256), 0, S->stream, S->G, S->h0,
                        (double)S->sf,
-                       at<cd>(ws, L.tpart), at<cd>(ws, L.exch), at<cd>(ws, L.e1), w->weight, 1,
+                       at<cd>(ws, L.tpart), at<cd>(ws, L.exch), nz, xst, at<cd>(ws, L.e1), w->weight, 1,
                        at<cd>(ws, L.tcur), at<cd>(ws, L.enew));
     HIPCHK(hipGetLastError());
   }
@@ -493,8 +518,9 @@ int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout
 }
 
 int launch_contract(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L, bool in_step) {
-  const int rc = launch_contraction(S, w, L);
-  return rc ? rc : launch_guard_assemble(S, w, L, in_step);
+  int rc = launch_guard_list(S, w, L, in_step);
+  if (!rc) rc = launch_contraction(S, w, L);
+  return rc ? rc : launch_guard_assemble(S, w, L);
 }
 
 int do_measure(afqmc_sys_s* S, afqmc_walkers* w) {
@@ -1135,8 +1161,8 @@ bool in_growth_phase(const afqmc_sys_s* s, int64_t k) {
   return !(s->p.flags & AFQMC_FLAG_FREE_PROJECTION) && s->p.n_growth > 0 && k < s->p.n_growth;
 }
 
-// One step of the random walk (Sec. III.E) enqueued on s->stream, in three parts: everything
-// up to the new overlaps (step_pre), the local-energy contraction, and the rest (step_post).
+// One step of the random walk (Sec. III.E) enqueued on s->stream, in two parts: everything
+// up to the new overlaps (step_pre), and the rest (step_post).
 // With `graph` the step number is read on the device from the workspace counter (so that a
 // captured graph can be replayed) and the counter is advanced at the end; otherwise the host
 // value is used and the counter is set to it.
@@ -1350,8 +1376,8 @@ int step_post(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool grap
   const int64_t k = w->step;
   int64_t* dstep = at<int64_t>(ws, L.dstep);
   int rc;
-  // 6. the local energy of the new determinants (after the contraction)
-  if ((rc = launch_guard_assemble(s, w, L, true))) return rc;
+  // 6. the local energy of the new determinants
+  if ((rc = launch_contract(s, w, L, true))) return rc;
   const bool qr_due = s->p.qr_period > 0 && (k + 1) % s->p.qr_period == 0;
   // 7. phaseless weights, with the growth-phase sums around them (App. B.1, B.2)
   const bool pop_due = s->p.pop_period > 0 && (k + 1) % s->p.pop_period == 0;
@@ -1410,11 +1436,8 @@ int step_post(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool grap
 }
 
 int step_impl(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool graph) {
-  int rc = step_pre(s, w, f, graph);
-  if (rc) return rc;
-  const WsLayout L = layout(s, (size_t)w->n_walkers);
-  if ((rc = launch_contraction(s, w, L))) return rc;
-  return step_post(s, w, f, graph);
+  const int rc = step_pre(s, w, f, graph);
+  return rc ? rc : step_post(s, w, f, graph);
 }
 
 }  // namespace
@@ -1996,6 +2019,8 @@ int afqmc_autotune(afqmc_sys s, afqmc_walkers* w, int32_t reuse, int32_t* tile, 
   double best_ms = 0.0;
   bool any = false;
   constexpr int REPS = 3;
+  // every walker in whole launches (no splits, nothing left to the guard): what is compared, and
+  // with it the arithmetic of a run, does not depend on how far the walkers are
   for (int t = TILE_W4; t < TILE_COUNT && rc == AFQMC_OK; ++t) {
     if (!mfma_tile_valid(s->mt, t)) continue;
     // one untimed launch, then REPS timed ones; only the workspace partial sums are written
@@ -2003,7 +2028,8 @@ int afqmc_autotune(afqmc_sys s, afqmc_walkers* w, int32_t reuse, int32_t* tile, 
       if (r == 1 && hipEventRecord(a, s->stream) != hipSuccess) rc = AFQMC_E_HIP;
       if (rc == AFQMC_OK &&
           mfma_contract(s->mt, s->stream, w->n_walkers, s->n_det, s->G, at<void>(ws, L.thetaP),
-                        w->weight, at<cd>(ws, L.tpart), at<cd>(ws, L.exch), t) != hipSuccess)
+                        w->weight, at<cd>(ws, L.tpart), at<cd>(ws, L.exch), t, ContractSel{},
+                        1, true) != hipSuccess)
         rc = AFQMC_E_HIP;
     }
     float el = 0.f;

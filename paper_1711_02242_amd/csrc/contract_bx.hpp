@@ -22,12 +22,13 @@
 template <bool BF16, int NK, int WPB>
 __global__ void __launch_bounds__(64 * WPB, 8 / WPB) k_contract_mfma_bx(
     int nw, int G, int nup, int ndn, const void* __restrict__ Lp_, const void* __restrict__ thp_,
-    const double* __restrict__ weight, cd* __restrict__ tpart, cd* __restrict__ exch) {
+    const double* __restrict__ weight, cd* __restrict__ tpart, cd* __restrict__ exch,
+    ContractSel sel) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int NP = 32, NT = 64 * WPB;
   constexpr int ESZ = BF16 ? 2 : 4, PLANES = BF16 ? 2 : 1;
   constexpr int KCH = BF16 ? 32 : 16;     // K per chunk: FP32 4 MFMA steps of 4, BF16 one of 32
-  constexpr int KP = NK * KCH;
+  constexpr int KP = (NK * KCH + 31) / 32 * 32;   // K_P; chunks past NK hold only zeros
   constexpr int lda = KP + (BF16 ? 8 : 4);   // LDS row stride of the tile (elements)
   constexpr size_t tile_elems = (size_t)NP * KP * PLANES;
   constexpr int tile_lds_bytes = NP * lda * ESZ * PLANES;
@@ -36,22 +37,19 @@ __global__ void __launch_bounds__(64 * WPB, 8 / WPB) k_contract_mfma_bx(
   const int N = s ? ndn : nup;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int w = blockIdx.x * WPB + wave;
-  const int wd = w * n_det + dd;
-  const bool active = (w < nw) && (N > 0) && (weight[w] > 0.0);
-  if (N == 0) {
-    if (w < nw) {
-      for (int g = lane; g < G; g += 64) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
-      if (lane == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
-    }
+  if (contract_empty_spin(N, blockIdx.x * WPB + wave, nw, n_det, dd, s, G, lane, tpart, exch, sel))
     return;
-  }
+  if (sel.none_left(blockIdx.x * WPB, s)) return;
+  const int w = sel.walker(blockIdx.x * WPB + wave, s, nw);
+  const int wd = w * n_det + dd;
+  const bool active = w >= 0 && weight[w] > 0.0 && sel.takes(wd, s);
+  const GRange gr = sel.range(G);
   unsigned char* Abuf0 = smem;
   unsigned char* Abuf1 = smem + tile_lds_bytes;
   // [16 rows][LDX][Re A, Im A, Re D, Im D] per wave
   float* ep = reinterpret_cast<float*>(smem + 2 * tile_lds_bytes) + (size_t)wave * 16 * LDX * 4;
   const unsigned char* Lbase =
-      reinterpret_cast<const unsigned char*>(Lp_) + ((size_t)dd * 2 + s) * G * tile_elems * ESZ;
+      reinterpret_cast<const unsigned char*>(Lp_) + (((size_t)dd * 2 + s) * G + gr.b) * tile_elems * ESZ;
 
   // ---- copy of one g-tile global -> LDS, 16 bytes per thread per chunk
   constexpr int chunks_per_row = KP * ESZ / 16;
@@ -108,16 +106,18 @@ __global__ void __launch_bounds__(64 * WPB, 8 / WPB) k_contract_mfma_bx(
   }
 
   double xr = 0.0, xi = 0.0;
-  if (G > 0) {
+  const int ng = gr.e - gr.b;
+  double* const trow = reinterpret_cast<double*>(tpart + ((size_t)wd * 2 + s) * G + gr.b);
+  if (ng > 0) {
     gload(0);
     lstore(Abuf0);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): Theta and the first tile
   __syncthreads();
-  for (int g = 0; g < G; ++g) {
+  for (int g = 0; g < ng; ++g) {
     unsigned char* Acur = (g & 1) ? Abuf1 : Abuf0;
     unsigned char* Anext = (g & 1) ? Abuf0 : Abuf1;
-    gload(g + 1 < G ? g + 1 : g);   // unconditional: the waits before the MFMAs skip it
+    gload(g + 1 < ng ? g + 1 : g);   // unconditional: the waits before the MFMAs skip it
     if (active) {
       // A fragments: rows j (upper block) and 16 + j (lower block) of Lh^g
       const unsigned char* up = Acur + ((size_t)j * lda + kofs) * ESZ;
@@ -214,19 +214,19 @@ __global__ void __launch_bounds__(64 * WPB, 8 / WPB) k_contract_mfma_bx(
       xi += (double)__builtin_fmaf(2.f, qi, pi);
       // trace: Re in lane 31 (A + D), Im in lane 63
       d = dpp_half_sum(d);
-      double* tp = reinterpret_cast<double*>(tpart + ((size_t)wd * 2 + s) * G + g);
+      double* tp = trow + 2 * g;
       if (lane == 31) tp[0] = (double)d;
       if (lane == 63) tp[1] = (double)d;
       // the next g's stores to the planes come after every lane's loads of this g
       wave_lds_fence();
     }
-    if (g + 1 < G) lstore(Anext);
+    if (g + 1 < ng) lstore(Anext);
     __syncthreads();
   }
   if (active) {
     xr = wave_sum(xr);
     xi = wave_sum(xi);
-    if (lane == 0) exch[2 * wd + s] = mkc(xr, xi);
+    if (lane == 0) exch[sel.part() + 2 * wd + s] = mkc(xr, xi);
   }
 }
 

@@ -34,7 +34,8 @@ template <int NK, bool BF16, int RT>
 __global__ void __launch_bounds__(512) k_contract_mfma_flat(
     int nw, int G, int nup, int ndn, int NP, int KP, int qup, int qdn, int LDR,
     const void* __restrict__ Lp_, const void* __restrict__ thp_,
-    const double* __restrict__ weight, cd* __restrict__ tpart, cd* __restrict__ exch) {
+    const double* __restrict__ weight, cd* __restrict__ tpart, cd* __restrict__ exch,
+    ContractSel sel) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int s = blockIdx.y & 1, dd = blockIdx.y >> 1, n_det = gridDim.y >> 1;
   const int N = s ? ndn : nup;
@@ -50,7 +51,7 @@ __global__ void __launch_bounds__(512) k_contract_mfma_flat(
     if (tid == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
     return;
   }
-  if (!(weight[w] > 0.0)) return;  // the whole workgroup is one walker
+  if (!(weight[w] > 0.0) || !sel.takes(wd, s)) return;  // the whole workgroup is one walker
 
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int PLANES = BF16 ? 2 : 1;
@@ -271,7 +272,8 @@ template <int NK, bool BF16, int RT>
 __global__ void __launch_bounds__(256) k_contract_mfma_stack(
     int nw, int G, int nup, int ndn, int NP, int KP, int qup, int qdn, int LDR,
     const void* __restrict__ Lp_, const void* __restrict__ thp_,
-    const double* __restrict__ weight, cd* __restrict__ tpart, cd* __restrict__ exch) {
+    const double* __restrict__ weight, cd* __restrict__ tpart, cd* __restrict__ exch,
+    ContractSel sel) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int s = blockIdx.y & 1, dd = blockIdx.y >> 1, n_det = gridDim.y >> 1;
   const int N = s ? ndn : nup;
@@ -287,7 +289,7 @@ __global__ void __launch_bounds__(256) k_contract_mfma_stack(
     if (tid == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
     return;
   }
-  if (!(weight[w] > 0.0)) return;  // the whole workgroup is one walker
+  if (!(weight[w] > 0.0) || !sel.takes(wd, s)) return;  // the whole workgroup is one walker
 
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int PLANES = BF16 ? 2 : 1;

@@ -7,7 +7,7 @@
 
 hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
                          const void* thetaP, const double* weight, cd* tpart, cd* exch, int tile,
-                         const int* wlist, const int* wcount, const double* gthmax, double guard) {
+                         ContractSel sel, int nz, bool plain) {
   if (t.precision == AFQMC_FP64) {
     const size_t shm = mfma_f64_contract_lds_bytes(t);
     dim3 grid((nw + 1) / 2, 2 * n_det);
@@ -19,7 +19,7 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
     hipLaunchKernelGGL((k_contract_f64mfma<NPV, NKV>), grid, dim3(256), shm, st, nw, G, t.nup, \
                        t.ndn, t.KP, (const double*)t.Lp, (const double*)thetaP, weight, tpart, \
-                       exch, wlist, wcount, gthmax, guard);                                    \
+                       exch, sel.list, sel.cnt, sel.thmax, sel.guard);                         \
   } while (0)
 #define LAUNCH_F64_NP(NPV)                                                                     \
   do {                                                                                         \
@@ -38,13 +38,15 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
   }
   const bool bf = t.precision == AFQMC_BF16X3;
   if (!mfma_tile_valid(t, tile)) tile = TILE_DEFAULT;
+  // FP32 chunks of 16 k past M hold only zeros and are left out (the same bits)
+  const int nk16 = plain ? t.KP / 16 : (t.M + 15) / 16;
   // default at N_P = 32: the block-exchange kernel (fewest LDS and vector instructions per g),
   // eight walkers per workgroup when the workgroups with work (walkers, active spins,
   // determinants) still cover every CU
   if (tile == TILE_DEFAULT && !t.wide && t.NP == 32) {
     const int spins = (t.nup > 0 ? 1 : 0) + (t.ndn > 0 ? 1 : 0);
-    tile = (size_t)((nw + 7) / 8) * spins * n_det >= (size_t)device_cu_count() ? TILE_BX8
-                                                                                 : TILE_BX;
+    tile = (size_t)((nw + 7) / 8) * spins * n_det * nz >= (size_t)device_cu_count() ? TILE_BX8
+                                                                                      : TILE_BX;
   }
   if (tile == TILE_FLAT || tile == TILE_STACK) {
     const bool stk = tile == TILE_STACK;
@@ -57,11 +59,11 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
                                                               ? (BFV ? 3 : STACK_MAX_RT)          \
                                                               : (RTV))>),                         \
                          grid, dim3(64 * f.waves), f.lds, st, nw, G, t.nup, t.ndn, t.NP, t.KP,    \
-                         f.qup, f.qdn, f.LDR, (const void*)t.Lp, thetaP, weight, tpart, exch);    \
+                         f.qup, f.qdn, f.LDR, (const void*)t.Lp, thetaP, weight, tpart, exch, sel); \
     else                                                                                          \
       hipLaunchKernelGGL((k_contract_mfma_flat<KM, BFV, (RTV)>), grid, dim3(64 * f.waves), f.lds, \
                          st, nw, G, t.nup, t.ndn, t.NP, t.KP, f.qup, f.qdn, f.LDR,                \
-                         (const void*)t.Lp, thetaP, weight, tpart, exch);                         \
+                         (const void*)t.Lp, thetaP, weight, tpart, exch, sel);                    \
   } while (0)
   // one instantiation per row-tile count (flat 1 .. 7, BF16x3 1 .. 4; stack 1 .. 7, BF16x3
   // 1 .. 3)
@@ -104,7 +106,7 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
   do {                                                                                          \
     const size_t shm_ = wide_contract_lds_bytes_t<NPV, BFV>(t.KP);                              \
     hipLaunchKernelGGL((k_contract_mfma_wide<NPV, BFV, KM>), grid, dim3(4 * NPV), shm_, st, nw, \
-                       G, t.nup, t.ndn, t.KP, (const void*)t.Lp, thetaP, weight, tpart, exch);  \
+                       G, t.nup, t.ndn, t.KP, (const void*)t.Lp, thetaP, weight, tpart, exch, sel); \
   } while (0)
   // one instantiation per K chunk count (K_P = 32 .. 224 in steps of 32)
 #define LAUNCH_WIDE(NPV, BFV)                                                                   \
@@ -140,26 +142,28 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
   if (tile == TILE_BX || tile == TILE_BX8) {
     const int wb = tile == TILE_BX8 ? 8 : 4;
     const size_t shm = bx_contract_lds_bytes(t.KP, bf, wb);
-    dim3 grid((nw + wb - 1) / wb, 2 * n_det);
+    dim3 grid((nw + wb - 1) / wb, 2 * n_det, nz);
 #define LAUNCH_BX(BFV, NKV, WBV)                                                               \
   do {                                                                                         \
     (void)hipFuncSetAttribute((const void*)k_contract_mfma_bx<BFV, NKV, WBV>,                  \
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
     hipLaunchKernelGGL((k_contract_mfma_bx<BFV, NKV, WBV>), grid, dim3(64 * WBV), shm, st, nw, \
-                       G, t.nup, t.ndn, (const void*)t.Lp, thetaP, weight, tpart, exch);       \
+                       G, t.nup, t.ndn, (const void*)t.Lp, thetaP, weight, tpart, exch, sel);  \
   } while (0)
 #define LAUNCH_BX_W(BFV, NKV)                                                                  \
   case NKV:                                                                                    \
     if (wb == 8) LAUNCH_BX(BFV, NKV, 8);                                                       \
     else LAUNCH_BX(BFV, NKV, 4);                                                               \
     break;
-    // one instantiation per K chunk count (K_P = 32 .. 128 in steps of 32)
+    // one instantiation per K chunk count (16 < N <= M, so FP32 has at least two chunks of 16)
     if (bf) {
       switch (t.KP / 32) { LAUNCH_BX_W(true, 1) LAUNCH_BX_W(true, 2) LAUNCH_BX_W(true, 3)
                            default: LAUNCH_BX_W(true, 4) }
     } else {
-      switch (t.KP / 16) { LAUNCH_BX_W(false, 2) LAUNCH_BX_W(false, 4) LAUNCH_BX_W(false, 6)
-                           default: LAUNCH_BX_W(false, 8) }
+      switch (nk16) { LAUNCH_BX_W(false, 2) LAUNCH_BX_W(false, 3) LAUNCH_BX_W(false, 4)
+                      LAUNCH_BX_W(false, 5) LAUNCH_BX_W(false, 6) LAUNCH_BX_W(false, 7)
+                      LAUNCH_BX_W(false, 8)
+                      default: return hipErrorInvalidValue; }
     }
 #undef LAUNCH_BX_W
 #undef LAUNCH_BX
@@ -167,13 +171,13 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
   }
   if (tile == TILE_PP) {
     const size_t shm = pp_contract_lds_bytes(t.NP, t.KP, bf);
-    dim3 grid((nw + 7) / 8, 2 * n_det);
+    dim3 grid((nw + 7) / 8, 2 * n_det, nz);
 #define LAUNCH_PP_K(NPV, BFV, NKV)                                                             \
   do {                                                                                         \
     (void)hipFuncSetAttribute((const void*)k_contract_mfma_pp<NPV, BFV, NKV>,                  \
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
     hipLaunchKernelGGL((k_contract_mfma_pp<NPV, BFV, NKV>), grid, dim3(512), shm, st, nw, G,   \
-                       t.nup, t.ndn, (const void*)t.Lp, thetaP, weight, tpart, exch);          \
+                       t.nup, t.ndn, (const void*)t.Lp, thetaP, weight, tpart, exch, sel);     \
   } while (0)
 #define LAUNCH_PP(NPV, BFV)                                                                    \
   do {                                                                                         \
@@ -197,14 +201,14 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
     return hipGetLastError();
   }
   const size_t shm = mfma_contract_lds_bytes(t, wpb);
-  dim3 grid((nw + wpb - 1) / wpb, 2 * n_det);
+  dim3 grid((nw + wpb - 1) / wpb, 2 * n_det, nz);
 #define LAUNCH_CONTRACT_K(NPV, BFV, WPBV, NKV)                                                  \
   do {                                                                                          \
     (void)hipFuncSetAttribute((const void*)k_contract_mfma<NPV, BFV, WPBV, NKV>,                \
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);            \
     hipLaunchKernelGGL((k_contract_mfma<NPV, BFV, WPBV, NKV>), grid, dim3(64 * WPBV), shm, st,  \
                        nw, G, t.nup, t.ndn, t.KP, (const void*)t.Lp, thetaP, weight, tpart,     \
-                       exch);                                                                   \
+                       exch, sel);                                                                \
   } while (0)
   // one instantiation per K chunk count (K_P = 32 .. 128 in steps of 32)
 #define LAUNCH_CONTRACT(NPV, BFV, WPBV)                                                         \
@@ -223,7 +227,14 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
       else LAUNCH_CONTRACT(32, false, 4);
     } else {
       if (bf) LAUNCH_CONTRACT(16, true, 4);
-      else LAUNCH_CONTRACT(16, false, 4);
+      else
+        switch (nk16) {
+          case 1: LAUNCH_CONTRACT_K(16, false, 4, 1); break;
+          case 3: LAUNCH_CONTRACT_K(16, false, 4, 3); break;
+          case 5: LAUNCH_CONTRACT_K(16, false, 4, 5); break;
+          case 7: LAUNCH_CONTRACT_K(16, false, 4, 7); break;
+          default: LAUNCH_CONTRACT(16, false, 4);
+        }
     }
   } else {
     if (t.NP == 32) {

@@ -38,6 +38,49 @@ __device__ __forceinline__ void exch_term(float R, float I, float Rt, float It, 
   pi = __builtin_fmaf(I, Rt, pi);
 }
 
+// Which walkers and Cholesky vectors a launch of a per-vector kernel takes.
+struct GRange {
+  int b, e;
+};
+struct ContractSel {
+  // walkers list[s][0 .. cnt[s]) of spin s (NULL: all), and of a listed walker only the
+  // determinants with thmax <= guard: those the precision guard does not redo in FP64
+  const int* list;
+  const int* cnt;
+  const double* thmax;
+  double guard;
+  int nw;          // row length of list
+  size_t stride;   // exch elements per split of g
+  // split z of gridDim.z takes the vectors [G z / nz, G (z + 1) / nz) and leaves its own exchange
+  // sum: few walkers then still give every SIMD its wavefronts
+  __device__ __forceinline__ GRange range(int G) const {
+    const long long z = blockIdx.z, nz = gridDim.z;
+    return GRange{(int)(G * z / nz), (int)(G * (z + 1) / nz)};
+  }
+  __device__ __forceinline__ size_t part() const { return blockIdx.z * stride; }
+  __device__ __forceinline__ bool none_left(int slot, int s) const { return list && slot >= cnt[s]; }
+  __device__ __forceinline__ int walker(int slot, int s, int n) const {
+    if (!list) return slot < n ? slot : -1;
+    return slot < cnt[s] ? list[(size_t)s * nw + slot] : -1;
+  }
+  __device__ __forceinline__ bool takes(int wd, int s) const {
+    return !list || !(thmax[2 * (size_t)wd + s] > guard);
+  }
+};
+// A spin without electrons: zero traces and exchange of walker w, one wavefront per walker.
+__device__ __forceinline__ bool contract_empty_spin(int N, int w, int nw, int n_det, int dd, int s,
+                                                    int G, int lane, cd* tpart, cd* exch,
+                                                    const ContractSel& sel) {
+  if (N != 0) return false;
+  if (w < nw) {
+    const size_t wds = 2 * ((size_t)w * n_det + dd) + s;
+    if (blockIdx.z == 0)
+      for (int g = lane; g < G; g += 64) tpart[wds * G + g] = mkc(0.0, 0.0);
+    if (lane == 0) exch[sel.part() + wds] = mkc(0.0, 0.0);
+  }
+  return true;
+}
+
 // One K chunk of Omega = Lh Theta for the Re and Im halves.  FP32: a holds four K values of
 // one row of Lh (one per MFMA step), br / bi four K values of one column of Re / Im Theta.
 // BF16x3: a / al the hi / lo bf16 of eight K values, br / brl and bi / bil likewise; the
@@ -104,7 +147,7 @@ template <int NP, bool BF16, int WPB, int NK>
 __global__ void __launch_bounds__(64 * WPB, 2) k_contract_mfma(
     int nw, int G, int nup, int ndn, int KP_arg, const void* __restrict__ Lp_,
     const void* __restrict__ thp_, const double* __restrict__ weight, cd* __restrict__ tpart,
-    cd* __restrict__ exch) {
+    cd* __restrict__ exch, ContractSel sel) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // blockIdx.y = 2 d + s: determinant d of the trial, spin s
   const int s = blockIdx.y & 1, dd = blockIdx.y >> 1, n_det = gridDim.y >> 1;
@@ -112,21 +155,18 @@ __global__ void __launch_bounds__(64 * WPB, 2) k_contract_mfma(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int NT = 64 * WPB;
-  const int w = blockIdx.x * WPB + wave;
-  const int wd = w * n_det + dd;   // (walker, determinant) slot of the outputs
-  const bool active = (w < nw) && (N > 0) && (weight[w] > 0.0);
-  if (N == 0) {
-    if (w < nw) {
-      for (int g = lane; g < G; g += 64) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
-      if (lane == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
-    }
+  if (contract_empty_spin(N, blockIdx.x * WPB + wave, nw, n_det, dd, s, G, lane, tpart, exch, sel))
     return;
-  }
+  if (sel.none_left(blockIdx.x * WPB, s)) return;
+  const int w = sel.walker(blockIdx.x * WPB + wave, s, nw);
+  const int wd = w * n_det + dd;   // (walker, determinant) slot of the outputs
+  const bool active = w >= 0 && weight[w] > 0.0 && sel.takes(wd, s);
+  const GRange gr = sel.range(G);
   // element sizes: fp32 tiles are floats; bf16 tiles are 2-byte values, hi and lo planes.
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int PLANES = BF16 ? 2 : 1;
   constexpr int KCH = contract_kch<NP, BF16>();
-  constexpr int KP = NK * KCH;                          // K_P (the launcher passes it as KP_arg)
+  constexpr int KP = (NK * KCH + 31) / 32 * 32;         // K_P; chunks past NK hold only zeros
   (void)KP_arg;
   constexpr int lda = KP + (BF16 ? 8 : 4);              // LDS row stride in elements (16 B pad)
   constexpr size_t tile_elems = (size_t)NP * KP * PLANES;  // one g in global memory
@@ -139,7 +179,7 @@ __global__ void __launch_bounds__(64 * WPB, 2) k_contract_mfma(
   float* ep_im = ep + NP * LDE;
 
   const unsigned char* Lbase =
-      reinterpret_cast<const unsigned char*>(Lp_) + ((size_t)dd * 2 + s) * G * tile_elems * ESZ;
+      reinterpret_cast<const unsigned char*>(Lp_) + (((size_t)dd * 2 + s) * G + gr.b) * tile_elems * ESZ;
 
   // ---- copy of one g-tile global -> LDS, 16 bytes per thread per chunk
   constexpr int chunks_per_row = KP * ESZ / 16;
@@ -195,7 +235,9 @@ __global__ void __launch_bounds__(64 * WPB, 2) k_contract_mfma(
   using Acc = typename std::conditional<NP == 32, f32x16, f32x4>::type;
   constexpr int NV = NP == 32 ? 16 : 4;   // accumulator elements per lane
   double xr = 0.0, xi = 0.0;
-  if (G > 0) {
+  const int ng = gr.e - gr.b;
+  double* const trow = reinterpret_cast<double*>(tpart + ((size_t)wd * 2 + s) * G + gr.b);
+  if (ng > 0) {
     AFQMC_GLOAD(0);
     AFQMC_LSTORE(Abuf0);
   }
@@ -203,16 +245,16 @@ __global__ void __launch_bounds__(64 * WPB, 2) k_contract_mfma(
   // the Theta registers land inside the g loop, where they also wait for the next tile
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
   __syncthreads();
-  for (int g = 0; g < G; ++g) {
+  for (int g = 0; g < ng; ++g) {
     unsigned char* Acur = (g & 1) ? Abuf1 : Abuf0;
     unsigned char* Anext = (g & 1) ? Abuf0 : Abuf1;
     // FP32: the next tile's loads are unconditional (the last g re-reads its own tile), so
     // the waits placed before the MFMAs do not stall on them; BF16x3 keeps the conditional
     // form, which measures faster there
     if constexpr (BF16) {
-      if (g + 1 < G) AFQMC_GLOAD(g + 1);
+      if (g + 1 < ng) AFQMC_GLOAD(g + 1);
     } else {
-      AFQMC_GLOAD(g + 1 < G ? g + 1 : g);
+      AFQMC_GLOAD(g + 1 < ng ? g + 1 : g);
     }
     const unsigned char* arow = Acur + ((size_t)col * lda + kofs) * ESZ;
     const size_t lo_ofs = (size_t)NP * lda * ESZ;   // bf16: lo plane of the tile
@@ -299,17 +341,17 @@ __global__ void __launch_bounds__(64 * WPB, 2) k_contract_mfma(
       xi += (double)pi;
       // trace: Re in lane NP - 1, Im in lane 2 NP - 1
       d = NP == 32 ? dpp_half_sum(d) : dpp_row_sum(d);
-      double* tp = reinterpret_cast<double*>(tpart + ((size_t)wd * 2 + s) * G + g);
+      double* tp = trow + 2 * g;
       if (lane == NP - 1) tp[0] = (double)d;
       if (lane == 2 * NP - 1) tp[1] = (double)d;
     }
-    if (g + 1 < G) AFQMC_LSTORE(Anext);
+    if (g + 1 < ng) AFQMC_LSTORE(Anext);
     __syncthreads();
   }
   if (active) {
     xr = wave_sum(xr);
     xi = wave_sum(xi);
-    if (lane == 0) exch[2 * wd + s] = mkc(xr, xi);
+    if (lane == 0) exch[sel.part() + 2 * wd + s] = mkc(xr, xi);
   }
 #undef AFQMC_GLOAD
 #undef AFQMC_LSTORE

@@ -698,7 +698,7 @@ __global__ void __launch_bounds__(1024) k_pair_reduce(PairDims p, int nw, int nw
                                                       const int* __restrict__ list,
                                                       const int* __restrict__ cnt,
                                                       const double* __restrict__ thmax,
-                                                      double guard) {
+                                                      double guard, int nz, size_t xst) {
   __shared__ cd red[16][PAIR_W];
   const int c = blockIdx.x, s = blockIdx.y & 1, d = blockIdx.y >> 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -757,63 +757,73 @@ __global__ void __launch_bounds__(1024) k_pair_reduce(PairDims p, int nw, int nw
   if (wave) return;
   for (int v = 1; v < 16; ++v) x = cadd(x, red[v][lane]);
   const long long wds = slot(c * PAIR_W + lane);
-  if (wds >= 0) exch[wds] = mkc(fma(2.0, x.re, c0[2 * d + s]), 2.0 * x.im);
+  if (wds < 0) return;
+  exch[wds] = mkc(fma(2.0, x.re, c0[2 * d + s]), 2.0 * x.im);
+  // the partial sums of a split low-precision contraction of the same walker-spin
+  for (int z = 1; z < nz; ++z) exch[z * xst + wds] = mkc(0.0, 0.0);
 }
 
 // ---------------------------------------------------------------------------
 // Precision guard of the mixed modes.  glist: the live walkers whose largest |Theta_pc| over
 // spins and determinants exceeds `limit`, in walker order, their number in gcount[0] (added to
 // counts[CAP_GUARD] when counts != NULL); slist[s]: those whose spin s does (over
-// determinants), gcount[1 + s] of them.  One workgroup; every 1024 walkers one ballot per
+// determinants), gcount[1 + s] of them; ulist[s]: the live walkers with a determinant whose spin
+// s does not, gcount[3 + s] of them (the low-precision contraction takes only these).  One workgroup; every 1024 walkers one ballot per
 // wavefront and a prefix over the 16 wavefronts (a scan by one thread took 13.7 us).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(1024) k_guard_list(int nw, int nd, double limit,
                                                      const double* __restrict__ weight,
                                                      const double* __restrict__ thmax,
                                                      int* __restrict__ glist, int* __restrict__ slist,
+                                                     int* __restrict__ ulist,
                                                      int* __restrict__ gcount,
                                                      unsigned long long* __restrict__ counts) {
-  __shared__ int wsum[3][16];
+  constexpr int NL = 5;
+  __shared__ int wsum[NL][16];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  int base[3] = {0, 0, 0};
+  int* const out[NL] = {glist, slist, slist + nw, ulist, ulist + nw};
+  int base[NL] = {};
   for (int w0 = 0; w0 < nw; w0 += 1024) {
     const int w = w0 + tid;
-    bool f[3] = {false, false, false};
+    bool f[NL] = {};
     if (w < nw && weight[w] > 0.0) {
       double m0 = 0.0, m1 = 0.0;
+      bool u0 = false, u1 = false;
       for (int i = 0; i < nd; ++i) {
-        m0 = fmax(m0, thmax[(size_t)w * 2 * nd + 2 * i]);
-        m1 = fmax(m1, thmax[(size_t)w * 2 * nd + 2 * i + 1]);
+        const double a = thmax[(size_t)w * 2 * nd + 2 * i], b = thmax[(size_t)w * 2 * nd + 2 * i + 1];
+        m0 = fmax(m0, a);
+        m1 = fmax(m1, b);
+        u0 = u0 || !(a > limit);
+        u1 = u1 || !(b > limit);
       }
       f[1] = m0 > limit;
       f[2] = m1 > limit;
       f[0] = f[1] || f[2];
+      f[3] = u0;
+      f[4] = u1;
     }
-    unsigned long long m[3];
+    unsigned long long m[NL];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < NL; ++i) {
       m[i] = __ballot(f[i]);
       if (lane == 0) wsum[i][wv] = __popcll(m[i]);
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < NL; ++i) {
       int before = base[i], all = 0;
       for (int k = 0; k < 16; ++k) {
         const int v = wsum[i][k];
         before += k < wv ? v : 0;
         all += v;
       }
-      if (f[i]) {
-        const int at = before + __popcll(m[i] & ((1ull << lane) - 1ull));
-        (i == 0 ? glist : slist + (size_t)(i - 1) * nw)[at] = w;
-      }
+      if (f[i]) out[i][before + __popcll(m[i] & ((1ull << lane) - 1ull))] = w;
       base[i] += all;
     }
     __syncthreads();
   }
   if (tid == 0) {
-    for (int i = 0; i < 3; ++i) gcount[i] = base[i];
+    for (int i = 0; i < NL; ++i) gcount[i] = base[i];
     if (counts && base[0] > 0) atomicAdd(&counts[CAP_GUARD], (unsigned long long)base[0]);
   }
 }
@@ -824,7 +834,8 @@ inline size_t pair_split_elems(const PairDims& p) { return (size_t)PAIR_SPLIT * 
 inline hipError_t pair_contract(const PairTables& t, hipStream_t st, int nw, int cus,
                                 const double* X, cd* tpart, cd* exch, cd* part, cd* split,
                                 long long* start, const int* list = nullptr, const int* cnt = nullptr,
-                                const double* thmax = nullptr, double guard = 0.0) {
+                                const double* thmax = nullptr, double guard = 0.0, int nz = 1,
+                                size_t xst = 0) {
   const PairArgs a{t.dim, nw,    t.K,   t.B,  t.f, t.t0,  X,
                    tpart, part,  split, start, list, cnt, thmax, guard};
   const int nwg = pair_grid(t.dim, nw, cus);
@@ -834,7 +845,7 @@ inline hipError_t pair_contract(const PairTables& t, hipStream_t st, int nw, int
   hipLaunchKernelGGL(k_pair_reduce, dim3((nw + PAIR_W - 1) / PAIR_W, 2 * t.dim.n_det, 1 + t.dim.Gt),
                      dim3(1024), 0, st, t.dim, nw, nwg, (const cd*)part, (const cd*)split,
                      (const long long*)start,
-                     (const double*)t.c0, exch, tpart, list, cnt, thmax, guard);
+                     (const double*)t.c0, exch, tpart, list, cnt, thmax, guard, nz, xst);
   return hipGetLastError();
 }
 

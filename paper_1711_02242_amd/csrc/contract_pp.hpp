@@ -20,7 +20,7 @@ template <int NP, bool BF16, int NK>
 __global__ void __launch_bounds__(512, 1) k_contract_mfma_pp(
     int nw, int G, int nup, int ndn, const void* __restrict__ Lp_,
     const void* __restrict__ thp_, const double* __restrict__ weight, cd* __restrict__ tpart,
-    cd* __restrict__ exch) {
+    cd* __restrict__ exch, ContractSel sel) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int WPB = 8, NT = 512;
   const int bx = blockIdx.x;
@@ -29,16 +29,13 @@ __global__ void __launch_bounds__(512, 1) k_contract_mfma_pp(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 2;
-  const int w = bx * WPB + wave;
+  // uniform over the workgroup (N depends on the spin only)
+  if (contract_empty_spin(N, bx * WPB + wave, nw, n_det, dd, s, G, lane, tpart, exch, sel)) return;
+  if (sel.none_left(bx * WPB, s)) return;
+  const int w = sel.walker(bx * WPB + wave, s, nw);
   const int wd = w * n_det + dd;
-  const bool active = (w < nw) && (N > 0) && (weight[w] > 0.0);
-  if (N == 0) {   // uniform over the workgroup (N depends on the spin only)
-    if (w < nw) {
-      for (int g = lane; g < G; g += 64) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
-      if (lane == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
-    }
-    return;
-  }
+  const bool active = w >= 0 && weight[w] > 0.0 && sel.takes(wd, s);
+  const GRange gr = sel.range(G);
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int PLANES = BF16 ? 2 : 1;
   constexpr int KCH = contract_kch<NP, BF16>();
@@ -50,7 +47,7 @@ __global__ void __launch_bounds__(512, 1) k_contract_mfma_pp(
   float* ep_re = reinterpret_cast<float*>(smem + 2 * tile_lds_bytes) + (size_t)wave * 2 * NP * LDE;
   float* ep_im = ep_re + NP * LDE;
   const unsigned char* Lbase =
-      reinterpret_cast<const unsigned char*>(Lp_) + ((size_t)dd * 2 + s) * G * tile_elems * ESZ;
+      reinterpret_cast<const unsigned char*>(Lp_) + (((size_t)dd * 2 + s) * G + gr.b) * tile_elems * ESZ;
 
   // ---- copy of one g-tile global -> LDS by all 512 threads, 16 bytes per thread per chunk
   constexpr int chunks_per_row = KP * ESZ / 16;
@@ -106,20 +103,22 @@ __global__ void __launch_bounds__(512, 1) k_contract_mfma_pp(
   constexpr int NV = NP == 32 ? 16 : 4;
   Acc cre, cim;   // Omega of the wave's last chain, kept for its epilogue
   double xr = 0.0, xi = 0.0;
-  if (G > 0) {
+  const int ng = gr.e - gr.b;
+  double* const trow = reinterpret_cast<double*>(tpart + ((size_t)wd * 2 + s) * G + gr.b);
+  if (ng > 0) {
     gload(0);
     lstore(smem);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): Theta and the first tile
   __syncthreads();
-  const int nph = 2 * G + 1;
+  const int nph = 2 * ng + 1;
   for (int ph = 0; ph < nph; ++ph) {
     // tile g + 1 is fetched during phase 2g and stored at its end
     const int gt = ph >> 1;
-    const bool fetch = (ph & 1) == 0 && gt + 1 < G;
+    const bool fetch = (ph & 1) == 0 && gt + 1 < ng;
     if (fetch) gload(gt + 1);
     const int mine = ph - grp;   // this wave's step: 2g chain of g, 2g + 1 epilogue of g
-    if (active && mine >= 0 && mine < 2 * G) {
+    if (active && mine >= 0 && mine < 2 * ng) {
       const int g = mine >> 1;
       if ((mine & 1) == 0) {
         __builtin_amdgcn_s_setprio(1);
@@ -176,7 +175,7 @@ __global__ void __launch_bounds__(512, 1) k_contract_mfma_pp(
         xi += (double)pi;
         // trace: Re in lane NP - 1, Im in lane 2 NP - 1
         d = NP == 32 ? dpp_half_sum(d) : dpp_row_sum(d);
-        double* tp = reinterpret_cast<double*>(tpart + ((size_t)wd * 2 + s) * G + g);
+        double* tp = trow + 2 * g;
         if (lane == NP - 1) tp[0] = (double)d;
         if (lane == 2 * NP - 1) tp[1] = (double)d;
         // the planes are written again two phases later, after two barriers
@@ -188,7 +187,7 @@ __global__ void __launch_bounds__(512, 1) k_contract_mfma_pp(
   if (active) {
     xr = wave_sum(xr);
     xi = wave_sum(xi);
-    if (lane == 0) exch[2 * wd + s] = mkc(xr, xi);
+    if (lane == 0) exch[sel.part() + 2 * wd + s] = mkc(xr, xi);
   }
 }
 

@@ -21,7 +21,7 @@ template <int NPW, bool BF16, int NK>
 __global__ void __launch_bounds__(256, 2) k_contract_mfma_wide(
     int nw, int G, int nup, int ndn, int KP, const void* __restrict__ Lp_,
     const void* __restrict__ thp_, const double* __restrict__ weight, cd* __restrict__ tpart,
-    cd* __restrict__ exch) {
+    cd* __restrict__ exch, ContractSel sel) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int NW = NPW / 16;   // wavefronts = 16-column blocks of Theta
   constexpr int NR = NPW / 16;   // 16-row tiles of Omega
@@ -38,7 +38,7 @@ __global__ void __launch_bounds__(256, 2) k_contract_mfma_wide(
     if (tid == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
     return;
   }
-  if (!(weight[w] > 0.0)) return;  // the whole workgroup is one walker
+  if (!(weight[w] > 0.0) || !sel.takes(wd, s)) return;  // the whole workgroup is one walker
 
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int PLANES = BF16 ? 2 : 1;

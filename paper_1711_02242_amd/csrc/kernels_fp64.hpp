@@ -84,7 +84,8 @@ __global__ void __launch_bounds__(256) k_contract_fp64(
 // (eq:localenergy2-3 with the 1/2 of eq:bo_ham2).  One block per walker.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_energy_assemble(
-    int G, double h0, double sf, const cd* __restrict__ tpart, const cd* __restrict__ exch,
+    int G, double h0, double sf, const cd* __restrict__ tpart, const cd* __restrict__ exch, int nz,
+    size_t xst /*exch holds nz partial sums, xst apart*/,
     const cd* __restrict__ e1, const double* __restrict__ weight, int check_weight,
     cd* __restrict__ tcur /*[nw][G]*/, cd* __restrict__ enew /*[nw]*/) {
   __shared__ double red[8];
@@ -100,7 +101,12 @@ __global__ void __launch_bounds__(256) k_energy_assemble(
   jr = block_sum(jr, red);
   ji = block_sum(ji, red);
   if (tid == 0) {
-    const cd x = cadd(cscale(exch[2 * w], sf), exch[2 * w + 1]);
+    cd x0 = exch[2 * w], x1 = exch[2 * w + 1];
+    for (int z = 1; z < nz; ++z) {
+      x0 = cadd(x0, exch[z * xst + 2 * w]);
+      x1 = cadd(x1, exch[z * xst + 2 * w + 1]);
+    }
+    const cd x = cadd(cscale(x0, sf), x1);
     const cd e = cadd(cscale(e1[2 * w], sf), e1[2 * w + 1]);
     enew[w] = mkc(h0 + e.re + 0.5 * (jr - x.re), e.im + 0.5 * (ji - x.im));
   }
@@ -119,8 +125,8 @@ __global__ void __launch_bounds__(256) k_energy_assemble(
 constexpr int AFQMC_MAX_DETS = 1024;
 __global__ void __launch_bounds__(256) k_energy_assemble_multi(
     int G, int n_det, double h0, double sf, const double* __restrict__ coef /*[n_det][2]*/,
-    const cd* __restrict__ tpart, const cd* __restrict__ exch, const cd* __restrict__ e1,
-    const cd* __restrict__ logdet, const unsigned* __restrict__ wflag,
+    const cd* __restrict__ tpart, const cd* __restrict__ exch, int nz, size_t xst,
+    const cd* __restrict__ e1, const cd* __restrict__ logdet, const unsigned* __restrict__ wflag,
     const double* __restrict__ weight, int check_weight, cd* __restrict__ tcur /*[nw][G]*/,
     cd* __restrict__ enew /*[nw]*/, cd* __restrict__ ldc /*[nw][2]*/,
     unsigned* __restrict__ wflc /*[nw][2]*/) {
@@ -193,7 +199,12 @@ __global__ void __launch_bounds__(256) k_energy_assemble_multi(
     jr = block_sum(jr, red);
     ji = block_sum(ji, red);
     if (tid == 0) {
-      const cd x = cadd(cscale(exch[2 * wd], sf), exch[2 * wd + 1]);
+      cd x0 = exch[2 * wd], x1 = exch[2 * wd + 1];
+      for (int z = 1; z < nz; ++z) {
+        x0 = cadd(x0, exch[z * xst + 2 * wd]);
+        x1 = cadd(x1, exch[z * xst + 2 * wd + 1]);
+      }
+      const cd x = cadd(cscale(x0, sf), x1);
       const cd e = cadd(cscale(e1[2 * wd], sf), e1[2 * wd + 1]);
       const cd ed = mkc(h0 + e.re + 0.5 * (jr - x.re), e.im + 0.5 * (ji - x.im));
       s_esum = cadd(s_esum, cmul(rd, ed));

@@ -398,13 +398,41 @@ inline size_t mfma_f64_contract_lds_bytes(const MfmaTables& t) {
   return ((size_t)t.NP * (t.KP + 2) + (size_t)2 * 2 * t.NP * (t.NP + 1)) * 8;
 }
 
-// The contraction of every walker by one of the variants (contract_launch.hip: a translation
-// unit of its own, for its many kernel instances).
+// Splits of the Cholesky vectors of a launch of the kernels with one wavefront per walker-spin
+// (exch then holds that many partial sums).  A workgroup's time is that of its vectors plus
+// about three more for its prologue, and the launch takes whole rounds of the device's
+// workgroup slots: the split with the least of the product, of at least 8 vectors each.  Slots:
+// eight wavefronts per CU at N_P = 32 (the registers hold Theta), sixteen at N_P = 16.  One
+// function of the sizes for every such variant, so that those with the same arithmetic keep the
+// same sums.  M = 112, N = 28 closed shell, 1024 walkers: 128 workgroups of eight, 2 splits;
+// M = 64, N = 16, 512 walkers: 256 of four, 4 splits.
+constexpr int CONTRACT_MAX_SPLITS = 16;
+inline bool mfma_tile_splits(const MfmaTables& t, int tile) {
+  if (!t.enabled || t.precision == AFQMC_FP64 || t.wide) return false;
+  return tile == TILE_DEFAULT || tile == TILE_W4 || tile == TILE_W2 || tile == TILE_PP ||
+         tile == TILE_BX || tile == TILE_BX8;
+}
+inline int mfma_splits(const MfmaTables& t, int nw, int n_det, int G, int tile) {
+  if (!mfma_tile_splits(t, tile)) return 1;
+  const int spins = (t.nup > 0 ? 1 : 0) + (t.ndn > 0 ? 1 : 0);
+  const long long per = t.NP == 32 ? 8 : 4, slots = (long long)device_cu_count() * (t.NP == 32 ? 1 : 4);
+  const long long wgs = (nw + per - 1) / per * spins * n_det;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int z = 1; z <= CONTRACT_MAX_SPLITS && (z == 1 || G / z >= 8); ++z) {
+    const double cost = (double)((wgs * z + slots - 1) / slots) * ((G + z - 1) / z + 3.0);
+    if (z == 1 || cost < best_cost) best = z, best_cost = cost;
+  }
+  return best;
+}
+
+// The contraction of every walker by one of the variants, in nz splits where mfma_tile_splits
+// (contract_launch.hip: a translation unit of its own, for its many kernel instances).  `plain`:
+// whole steps of 32 k, as the autotuner compares the variants; else FP32 chunks of 16 k past M are
+// left out where the kernel has such an instance.
 hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
-                                const void* thetaP, const double* weight, cd* tpart, cd* exch,
-                                int tile = TILE_DEFAULT, const int* wlist = nullptr,
-                                const int* wcount = nullptr, const double* gthmax = nullptr,
-                                double guard = 0.0);
+                         const void* thetaP, const double* weight, cd* tpart, cd* exch, int tile,
+                         ContractSel sel, int nz, bool plain = false);
 
 // ---------------------------------------------------------------------------
 // Overlap, determinant and Theta with the two small products on FP64 MFMA
