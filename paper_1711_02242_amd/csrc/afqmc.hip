@@ -123,7 +123,7 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.thetaT = take(S->mt.enabled && !S->pr.on ? 0 : nw * nd * nt * M * 16);
   L.tcur = take(nw * G * 16);
   L.tpart = take(nw * nd * 2 * G * 16);
-  L.exch = take(nw * nd * 2 * 16 * (mfma_tile_splits(S->mt, TILE_DEFAULT) ? CONTRACT_MAX_SPLITS : 1));
+  L.exch = take(nw * nd * 2 * 16 * (mfma_splittable(S->mt) ? CONTRACT_MAX_SPLITS : 1));
   L.e1 = take(nw * nd * 2 * 16);
   L.logdet = take(nw * nd * 2 * 16);
   L.wflag = take(nw * nd * 2 * 4);

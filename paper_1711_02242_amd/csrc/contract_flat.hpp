@@ -47,8 +47,9 @@ __global__ void __launch_bounds__(512) k_contract_mfma_flat(
   const int NWV = blockDim.x >> 6;
   if (w >= nw) return;
   if (N == 0) {
-    for (int g = tid; g < G; g += blockDim.x) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
-    if (tid == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
+    if (blockIdx.z == 0)
+      for (int g = tid; g < G; g += blockDim.x) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
+    if (tid == 0) exch[sel.part() + 2 * wd + s] = mkc(0.0, 0.0);
     return;
   }
   if (!(weight[w] > 0.0) || !sel.takes(wd, s)) return;  // the whole workgroup is one walker
@@ -88,6 +89,7 @@ __global__ void __launch_bounds__(512) k_contract_mfma_flat(
   }
 
   const int ngroups = (G + q - 1) / q;
+  const GRange kr = sel.range(ngroups);   // whole groups
   // Byte offset, from a group's first block, of this lane's A row (row `col`) in each row
   // tile of a full group.  In a group of qk blocks the rows at offsets >= qk gstride lie past
   // its end and read the group's first row instead (clamp()).
@@ -104,22 +106,23 @@ __global__ void __launch_bounds__(512) k_contract_mfma_flat(
 
   u32x4 acur[RT], acur_l[BF16 ? RT : 1];
   {
-    const uint32_t lim = qlim(0);
+    const uint32_t lim = qlim(kr.b);
+    const unsigned char* g0 = Lbase + (size_t)kr.b * q * gstride;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-      const unsigned char* p = Lbase + clamp(ro[r], lim);
+      const unsigned char* p = g0 + clamp(ro[r], lim);
       acur[r] = ld(p);
       if (BF16) acur_l[BF16 ? r : 0] = ld(p + per * ESZ);
     }
   }
 
   double xr = 0.0, xi = 0.0;
-  for (int k = 0; k < ngroups; ++k) {
+  for (int k = kr.b; k < kr.e; ++k) {
     const unsigned char* gb = Lbase + (size_t)k * q * gstride;
     const uint32_t lim = qlim(k);
     // the next group (this one again after the last, so that the loads never depend on a
     // branch and the wait before each chunk's MFMAs covers only that chunk)
-    const int kn = k + 1 < ngroups ? k + 1 : k;
+    const int kn = k + 1 < kr.e ? k + 1 : k;
     const unsigned char* gbn = Lbase + (size_t)kn * q * gstride;
     const uint32_t limn = qlim(kn);
     f32x4 acc[RT];
@@ -242,7 +245,7 @@ __global__ void __launch_bounds__(512) k_contract_mfma_flat(
     __syncthreads();  // reads done before the next group's stores
   }
 
-  for (int g = tid; g < G; g += blockDim.x)
+  for (int g = kr.b * q + tid; g < min(G, kr.e * q); g += blockDim.x)
     tpart[((size_t)wd * 2 + s) * G + g] = mkc((double)tr[2 * g], (double)tr[2 * g + 1]);
   xr = wave_sum(xr);
   xi = wave_sum(xi);
@@ -257,7 +260,7 @@ __global__ void __launch_bounds__(512) k_contract_mfma_flat(
       sr += red[kk];
       si += red[NWV + kk];
     }
-    exch[2 * wd + s] = mkc(sr, si);
+    exch[sel.part() + 2 * wd + s] = mkc(sr, si);
   }
 }
 
@@ -285,8 +288,9 @@ __global__ void __launch_bounds__(256) k_contract_mfma_stack(
   const int NWV = blockDim.x >> 6;
   if (w >= nw) return;
   if (N == 0) {
-    for (int g = tid; g < G; g += blockDim.x) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
-    if (tid == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
+    if (blockIdx.z == 0)
+      for (int g = tid; g < G; g += blockDim.x) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
+    if (tid == 0) exch[sel.part() + 2 * wd + s] = mkc(0.0, 0.0);
     return;
   }
   if (!(weight[w] > 0.0) || !sel.takes(wd, s)) return;  // the whole workgroup is one walker
@@ -329,6 +333,7 @@ __global__ void __launch_bounds__(256) k_contract_mfma_stack(
   }
 
   const int ngroups = (G + q - 1) / q;
+  const GRange kr = sel.range(ngroups);   // whole groups
   uint32_t ro[RT];
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
@@ -342,20 +347,21 @@ __global__ void __launch_bounds__(256) k_contract_mfma_stack(
 
   u32x4 acur[RT], acur_l[BF16 ? RT : 1];
   {
-    const uint32_t lim = qlim(0);
+    const uint32_t lim = qlim(kr.b);
+    const unsigned char* g0 = Lbase + (size_t)kr.b * q * gstride;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
-      const unsigned char* p = Lbase + clamp(ro[r], lim);
+      const unsigned char* p = g0 + clamp(ro[r], lim);
       acur[r] = ld(p);
       if (BF16) acur_l[BF16 ? r : 0] = ld(p + per * ESZ);
     }
   }
 
   double xr = 0.0, xi = 0.0;
-  for (int k = 0; k < ngroups; ++k) {
+  for (int k = kr.b; k < kr.e; ++k) {
     const unsigned char* gb = Lbase + (size_t)k * q * gstride;
     const uint32_t lim = qlim(k);
-    const int kn = k + 1 < ngroups ? k + 1 : k;
+    const int kn = k + 1 < kr.e ? k + 1 : k;
     const unsigned char* gbn = Lbase + (size_t)kn * q * gstride;
     const uint32_t limn = qlim(kn);
     f32x4 cre[RT], cim[RT];
@@ -464,7 +470,7 @@ __global__ void __launch_bounds__(256) k_contract_mfma_stack(
     __syncthreads();  // reads done before the next group's stores
   }
 
-  for (int g = tid; g < G; g += blockDim.x)
+  for (int g = kr.b * q + tid; g < min(G, kr.e * q); g += blockDim.x)
     tpart[((size_t)wd * 2 + s) * G + g] = mkc((double)tr[2 * g], (double)tr[2 * g + 1]);
   xr = wave_sum(xr);
   xi = wave_sum(xi);
@@ -479,7 +485,7 @@ __global__ void __launch_bounds__(256) k_contract_mfma_stack(
       sr += red[kk];
       si += red[NWV + kk];
     }
-    exch[2 * wd + s] = mkc(sr, si);
+    exch[sel.part() + 2 * wd + s] = mkc(sr, si);
   }
 }
 

@@ -48,78 +48,36 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
     tile = (size_t)((nw + 7) / 8) * spins * n_det * nz >= (size_t)device_cu_count() ? TILE_BX8
                                                                                       : TILE_BX;
   }
-  if (tile == TILE_FLAT || tile == TILE_STACK) {
-    const bool stk = tile == TILE_STACK;
-    const FlatLaunch f = flat_launch(t.nup, t.ndn, G, bf, stk);
-    dim3 grid(nw, 2 * n_det);
-#define LAUNCH_FLAT_KR(BFV, KM, RTV)                                                              \
-  do {                                                                                            \
-    if (stk)                                                                                      \
-      hipLaunchKernelGGL((k_contract_mfma_stack<KM, BFV, ((RTV) > (BFV ? 3 : STACK_MAX_RT)        \
-                                                              ? (BFV ? 3 : STACK_MAX_RT)          \
-                                                              : (RTV))>),                         \
-                         grid, dim3(64 * f.waves), f.lds, st, nw, G, t.nup, t.ndn, t.NP, t.KP,    \
-                         f.qup, f.qdn, f.LDR, (const void*)t.Lp, thetaP, weight, tpart, exch, sel); \
-    else                                                                                          \
-      hipLaunchKernelGGL((k_contract_mfma_flat<KM, BFV, (RTV)>), grid, dim3(64 * f.waves), f.lds, \
-                         st, nw, G, t.nup, t.ndn, t.NP, t.KP, f.qup, f.qdn, f.LDR,                \
-                         (const void*)t.Lp, thetaP, weight, tpart, exch, sel);                    \
-  } while (0)
-  // one instantiation per row-tile count (flat 1 .. 7, BF16x3 1 .. 4; stack 1 .. 7, BF16x3
-  // 1 .. 3)
-#define LAUNCH_FLAT_K(BFV, KM)                                                                    \
-  do {                                                                                            \
-    switch (f.RT) {                                                                               \
-      case 1: LAUNCH_FLAT_KR(BFV, KM, 1); break;                                                  \
-      case 2: LAUNCH_FLAT_KR(BFV, KM, 2); break;                                                  \
-      case 3: LAUNCH_FLAT_KR(BFV, KM, 3); break;                                                  \
-      case 4: LAUNCH_FLAT_KR(BFV, KM, 4); break;                                                  \
-      case 5: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 5); break;                                        \
-      case 6: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 6); break;                                        \
-      default: LAUNCH_FLAT_KR(BFV, KM, BFV ? 4 : 7); break;                                       \
-    }                                                                                             \
-  } while (0)
-  // and per K chunk count (K_P = 32 .. 224 in steps of 32)
-#define LAUNCH_FLAT(BFV)                                                                          \
-  do {                                                                                            \
-    constexpr int KCH_ = BFV ? 32 : 16;                                                           \
-    switch (t.KP / KCH_) {                                                                        \
-      case 32 / KCH_: LAUNCH_FLAT_K(BFV, 32 / KCH_); break;                                       \
-      case 64 / KCH_: LAUNCH_FLAT_K(BFV, 64 / KCH_); break;                                       \
-      case 96 / KCH_: LAUNCH_FLAT_K(BFV, 96 / KCH_); break;                                       \
-      case 128 / KCH_: LAUNCH_FLAT_K(BFV, 128 / KCH_); break;                                     \
-      case 160 / KCH_: LAUNCH_FLAT_K(BFV, 160 / KCH_); break;                                     \
-      case 192 / KCH_: LAUNCH_FLAT_K(BFV, 192 / KCH_); break;                                     \
-      default: LAUNCH_FLAT_K(BFV, 224 / KCH_); break;                                             \
-    }                                                                                             \
-  } while (0)
-    if (bf) LAUNCH_FLAT(true);
-    else LAUNCH_FLAT(false);
-#undef LAUNCH_FLAT
-#undef LAUNCH_FLAT_K
-#undef LAUNCH_FLAT_KR
-    return hipGetLastError();
-  }
+  if (tile == TILE_FLAT || tile == TILE_STACK)
+    return mfma_contract_flat(t, st, nw, n_det, G, thetaP, weight, tpart, exch, tile == TILE_STACK,
+                              sel, nz, bf ? t.KP / 32 : nk16);
   if (t.wide || tile == TILE_WIDE) {
-    dim3 grid(nw, 2 * n_det);
+    dim3 grid(nw, 2 * n_det, nz);
 #define LAUNCH_WIDE_K(NPV, BFV, KM)                                                             \
   do {                                                                                          \
     const size_t shm_ = wide_contract_lds_bytes_t<NPV, BFV>(t.KP);                              \
     hipLaunchKernelGGL((k_contract_mfma_wide<NPV, BFV, KM>), grid, dim3(4 * NPV), shm_, st, nw, \
                        G, t.nup, t.ndn, t.KP, (const void*)t.Lp, thetaP, weight, tpart, exch, sel); \
   } while (0)
-  // one instantiation per K chunk count (K_P = 32 .. 224 in steps of 32)
+  // one instantiation per K chunk count (FP32 of 16, BF16x3 of 32, up to K_P = 224)
 #define LAUNCH_WIDE(NPV, BFV)                                                                   \
   do {                                                                                          \
-    constexpr int KCH_ = BFV ? 32 : 16;                                                         \
-    switch (t.KP / KCH_) {                                                                      \
-      case 32 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 32 / KCH_); break;                                \
-      case 64 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 64 / KCH_); break;                                \
-      case 96 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 96 / KCH_); break;                                \
-      case 128 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 128 / KCH_); break;                              \
-      case 160 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 160 / KCH_); break;                              \
-      case 192 / KCH_: LAUNCH_WIDE_K(NPV, BFV, 192 / KCH_); break;                              \
-      default: LAUNCH_WIDE_K(NPV, BFV, 224 / KCH_); break;                                      \
+    switch (BFV ? t.KP / 32 : nk16) {                                                           \
+      case 1: LAUNCH_WIDE_K(NPV, BFV, 1); break;                                                \
+      case 2: LAUNCH_WIDE_K(NPV, BFV, 2); break;                                                \
+      case 3: LAUNCH_WIDE_K(NPV, BFV, 3); break;                                                \
+      case 4: LAUNCH_WIDE_K(NPV, BFV, 4); break;                                                \
+      case 5: LAUNCH_WIDE_K(NPV, BFV, 5); break;                                                \
+      case 6: LAUNCH_WIDE_K(NPV, BFV, 6); break;                                                \
+      case 7: LAUNCH_WIDE_K(NPV, BFV, 7); break;                                                \
+      case 8: LAUNCH_WIDE_K(NPV, BFV, BFV ? 7 : 8); break;                                      \
+      case 9: LAUNCH_WIDE_K(NPV, BFV, BFV ? 7 : 9); break;                                      \
+      case 10: LAUNCH_WIDE_K(NPV, BFV, BFV ? 7 : 10); break;                                    \
+      case 11: LAUNCH_WIDE_K(NPV, BFV, BFV ? 7 : 11); break;                                    \
+      case 12: LAUNCH_WIDE_K(NPV, BFV, BFV ? 7 : 12); break;                                    \
+      case 13: LAUNCH_WIDE_K(NPV, BFV, BFV ? 7 : 13); break;                                    \
+      case 14: LAUNCH_WIDE_K(NPV, BFV, BFV ? 7 : 14); break;                                    \
+      default: return hipErrorInvalidValue;                                                     \
     }                                                                                           \
   } while (0)
     if (t.NP == 64) {

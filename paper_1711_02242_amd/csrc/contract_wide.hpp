@@ -34,12 +34,16 @@ __global__ void __launch_bounds__(256, 2) k_contract_mfma_wide(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (w >= nw) return;
   if (N == 0) {
-    for (int g = tid; g < G; g += NT) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
-    if (tid == 0) exch[2 * wd + s] = mkc(0.0, 0.0);
+    if (blockIdx.z == 0)
+      for (int g = tid; g < G; g += blockDim.x) tpart[((size_t)wd * 2 + s) * G + g] = mkc(0.0, 0.0);
+    if (tid == 0) exch[sel.part() + 2 * wd + s] = mkc(0.0, 0.0);
     return;
   }
   if (!(weight[w] > 0.0) || !sel.takes(wd, s)) return;  // the whole workgroup is one walker
 
+  const GRange gr = sel.range(G);
+  const int ng = gr.e - gr.b;
+  double* const trow = reinterpret_cast<double*>(tpart + ((size_t)wd * 2 + s) * G + gr.b);
   constexpr int ESZ = BF16 ? 2 : 4;
   constexpr int PLANES = BF16 ? 2 : 1;
   const size_t tile_elems = (size_t)NPW * KP * PLANES;  // one g in global memory
@@ -49,11 +53,11 @@ __global__ void __launch_bounds__(256, 2) k_contract_mfma_wide(
   double* red = reinterpret_cast<double*>(ep_im + NPW * LDE);  // [2][NW]
 
   const unsigned char* Lbase =
-      reinterpret_cast<const unsigned char*>(Lp_) + ((size_t)dd * 2 + s) * G * tile_elems * ESZ;
+      reinterpret_cast<const unsigned char*>(Lp_) + (((size_t)dd * 2 + s) * G + gr.b) * tile_elems * ESZ;
 
   // ---- Theta column block into registers (B operand: rows k, column 16 wave + col)
   constexpr int KCH = BF16 ? 32 : 16;      // K per register chunk (4 lane groups)
-  constexpr int MAXK = NK;                 // K chunks held: KP = NK * KCH exactly
+  constexpr int MAXK = NK;                 // K chunks held; chunks past NK hold only zeros
   constexpr int nk = NK;
   const int col = lane & 15, kg = lane >> 4;
   const int kofs = BF16 ? 8 * kg : 4 * kg;
@@ -92,14 +96,14 @@ __global__ void __launch_bounds__(256, 2) k_contract_mfma_wide(
 
   double xr = 0.0, xi = 0.0;
   u32x4 acur[NR], acur_lo[BF16 ? NR : 1];
-  if (G > 0) {
+  if (ng > 0) {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       acur[r] = a_ld(Lbase, r, 0);
       if (BF16) acur_lo[BF16 ? r : 0] = a_ld(Lbase + plane_bytes, r, 0);
     }
   }
-  for (int g = 0; g < G; ++g) {
+  for (int g = 0; g < ng; ++g) {
     const unsigned char* tg = Lbase + (size_t)g * tile_bytes;
     f32x4 cre[NR], cim[NR];
 #pragma unroll
@@ -111,7 +115,7 @@ __global__ void __launch_bounds__(256, 2) k_contract_mfma_wide(
     for (int c = 0; c < MAXK; ++c) {
       if (c < nk) {
         // next chunk (or the first chunk of the next g) one step ahead
-        const bool more = c + 1 < nk || g + 1 < G;
+        const bool more = c + 1 < nk || g + 1 < ng;
         const unsigned char* tn = c + 1 < nk ? tg : tg + tile_bytes;
         const int cn = c + 1 < nk ? c + 1 : 0;
         u32x4 anx[NR], anx_lo[BF16 ? NR : 1];
@@ -192,7 +196,7 @@ __global__ void __launch_bounds__(256, 2) k_contract_mfma_wide(
       const float* epp = wave == 0 ? ep_re : ep_im;
       float d = lane < NPW ? epp[lane * LDE + lane] : 0.f;
       d = dpp_wave_sum(d);
-      if (lane == 0) reinterpret_cast<double*>(tpart + ((size_t)wd * 2 + s) * G + g)[wave] = (double)d;
+      if (lane == 0) trow[2 * g + wave] = (double)d;
     }
     __syncthreads();  // Omega reads done before the next g writes it
   }
@@ -209,7 +213,7 @@ __global__ void __launch_bounds__(256, 2) k_contract_mfma_wide(
       sr += red[k];
       si += red[NW + k];
     }
-    exch[2 * wd + s] = mkc(sr, si);
+    exch[sel.part() + 2 * wd + s] = mkc(sr, si);
   }
 }
 

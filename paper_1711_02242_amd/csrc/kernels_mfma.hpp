@@ -398,24 +398,27 @@ inline size_t mfma_f64_contract_lds_bytes(const MfmaTables& t) {
   return ((size_t)t.NP * (t.KP + 2) + (size_t)2 * 2 * t.NP * (t.NP + 1)) * 8;
 }
 
-// Splits of the Cholesky vectors of a launch of the kernels with one wavefront per walker-spin
-// (exch then holds that many partial sums).  A workgroup's time is that of its vectors plus
-// about three more for its prologue, and the launch takes whole rounds of the device's
-// workgroup slots: the split with the least of the product, of at least 8 vectors each.  Slots:
-// eight wavefronts per CU at N_P = 32 (the registers hold Theta), sixteen at N_P = 16.  One
-// function of the sizes for every such variant, so that those with the same arithmetic keep the
-// same sums.  M = 112, N = 28 closed shell, 1024 walkers: 128 workgroups of eight, 2 splits;
-// M = 64, N = 16, 512 walkers: 256 of four, 4 splits.
+// Splits of the Cholesky vectors of a launch (exch then holds that many partial sums).  A
+// workgroup's time is that of its vectors plus about three more for its prologue, and the launch
+// takes whole rounds of the device's workgroup slots: the split with the least of the product, of
+// at least 8 vectors each.  Slots per CU: the kernels with a wavefront per walker-spin eight
+// wavefronts at N_P = 32 (the registers hold Theta), sixteen at N_P = 16; the wide kernel twelve
+// (eight at N_P = 64), the stacked-row kernels about two workgroups.  One function of the sizes
+// for all variants with a wavefront per walker-spin, so that those with the same arithmetic keep
+// the same sums.  M = 112, N = 28 closed shell, 1024 walkers: 128 workgroups of eight, 2 splits;
+// M = 64, N = 16, 512 walkers: 256 of four, 4 splits; M = 143, N = 35, 701 walkers: 1402 wide
+// workgroups for 1024 slots, 8 splits.
 constexpr int CONTRACT_MAX_SPLITS = 16;
-inline bool mfma_tile_splits(const MfmaTables& t, int tile) {
-  if (!t.enabled || t.precision == AFQMC_FP64 || t.wide) return false;
-  return tile == TILE_DEFAULT || tile == TILE_W4 || tile == TILE_W2 || tile == TILE_PP ||
-         tile == TILE_BX || tile == TILE_BX8;
+inline bool mfma_splittable(const MfmaTables& t) {
+  return t.enabled && t.precision != AFQMC_FP64;
 }
 inline int mfma_splits(const MfmaTables& t, int nw, int n_det, int G, int tile) {
-  if (!mfma_tile_splits(t, tile)) return 1;
+  if (!mfma_splittable(t)) return 1;
   const int spins = (t.nup > 0 ? 1 : 0) + (t.ndn > 0 ? 1 : 0);
-  const long long per = t.NP == 32 ? 8 : 4, slots = (long long)device_cu_count() * (t.NP == 32 ? 1 : 4);
+  long long per = t.NP == 32 ? 8 : 4, slots = t.NP == 32 ? 1 : 4;   // walkers per workgroup; per CU
+  if (tile == TILE_FLAT || tile == TILE_STACK) per = 1, slots = 2;
+  else if (t.wide || tile == TILE_WIDE) per = 1, slots = t.NP == 32 ? 6 : t.NP == 48 ? 4 : 2;
+  slots *= device_cu_count();
   const long long wgs = (nw + per - 1) / per * spins * n_det;
   int best = 1;
   double best_cost = 0.0;
@@ -426,13 +429,18 @@ inline int mfma_splits(const MfmaTables& t, int nw, int n_det, int G, int tile) 
   return best;
 }
 
-// The contraction of every walker by one of the variants, in nz splits where mfma_tile_splits
-// (contract_launch.hip: a translation unit of its own, for its many kernel instances).  `plain`:
+// The contraction of every walker by one of the variants, in nz splits (FP64: 1).
+// contract_launch.hip and contract_launch_flat.hip: translation units of their own, for their
+// many kernel instances.  `plain`:
 // whole steps of 32 k, as the autotuner compares the variants; else FP32 chunks of 16 k past M are
 // left out where the kernel has such an instance.
 hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
                          const void* thetaP, const double* weight, cd* tpart, cd* exch, int tile,
                          ContractSel sel, int nz, bool plain = false);
+// The stacked-row kernels' part of it: nk chunks of 16 k (BF16x3: of 32).
+hipError_t mfma_contract_flat(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
+                              const void* thetaP, const double* weight, cd* tpart, cd* exch,
+                              bool stk, ContractSel sel, int nz, int nk);
 
 // ---------------------------------------------------------------------------
 // Overlap, determinant and Theta with the two small products on FP64 MFMA

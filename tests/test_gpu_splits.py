@@ -21,15 +21,19 @@ SHAPES = {
     "m100_dn0": (100, 12, 0, 90, 5),
     "n20_m44": (44, 20, 18, 131, 5),
     "n32_m112": (112, 32, 29, 75, 9),
-    "n17_m17_g8": (24, 17, 16, 8, 4),
+    "n17_m24_g8": (24, 17, 16, 8, 4),
+    "n35_m130": (130, 35, 0, 77, 3),
+    "n50_m145": (145, 50, 49, 60, 2),
 }
 
 
-def _measure(s, U, nw, precision, **kw):
+def _measure(s, U, nw, precision, tile=None, **kw):
     import torch
 
     import paper_1711_02242_amd as afq
     gs = afq.System.from_synthetic(s, dtau=0.005, precision=precision, **kw)
+    if tile:
+        gs.set_tile(tile)
     wk = gs.walkers(nw)
     gs.init(wk)
     wk.U.copy_(torch.from_numpy(oracle_U_to_gpu(U[0][:nw], U[1][:nw])))
@@ -54,14 +58,15 @@ def test_split_multidet():
                  trial=noci_trial(s, 3, seed=73))
 
 
-@pytest.mark.parametrize("n", [12, 24])
-def test_results_do_not_depend_on_the_walker_count(n):
+@pytest.mark.parametrize("n,tile", [(12, None), (24, None), (12, "flat"), (21, "stack"),
+                                    (21, "wide"), (35, None), (35, "stack"), (35, "flat")])
+def test_results_do_not_depend_on_the_walker_count(n, tile):
     """Other walker counts take other splits: FP64 sums of the same FP32 terms."""
     s = gen_system(56, n, 211, seed=74)
     U = random_walkers(s, 700, seed=75, amplitude=0.4)
-    ref = _measure(s, U, 700, "fp32", theta_guard=np.inf)
+    ref = _measure(s, U, 700, "fp32", tile, theta_guard=np.inf)
     for nw in (1, 17, 130):
-        e = _measure(s, U, nw, "fp32", theta_guard=np.inf)
+        e = _measure(s, U, nw, "fp32", tile, theta_guard=np.inf)
         assert np.abs(e - ref[:nw]).max() <= 1e-12 * np.abs(ref).max()
 
 
