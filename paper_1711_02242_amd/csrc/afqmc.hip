@@ -53,7 +53,7 @@ struct TimedLaunch {
 };
 
 struct WsLayout {
-  size_t thetaT, tcur, tpart, exch, e1, logdet, wflag, enew, y, A, X0, X1, Y, parent, csum,
+  size_t thetaT, tcur, tpart, exch, e1, logdet, wflag, enew, wold, wstat, y, A, X0, X1, Y, parent, csum,
       wnew, asnap, lsnap, esum, thetaP, y32, fbterm, mfterm, logR, psnap, ldc, wflc, dstep, growth,
       thmax, thetaP64, glist, slist, ulist, gcount, part, psplit, pstart, total;
 };
@@ -127,7 +127,9 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.e1 = take(nw * nd * 2 * 16);
   L.logdet = take(nw * nd * 2 * 16);
   L.wflag = take(nw * nd * 2 * 4);
-  L.enew = take(nw * 16);
+  L.enew = take(nw * 16);   // comb scratch
+  L.wold = take(nw * 8);
+  L.wstat = take(nw * 4);
   L.y = take(nw * (S->f64_reg ? (size_t)S->Gp64 : G) * 16);
   // exponent A: block-packed Re and Im planes (FP32, FP64), else FP64 complex M x M
   L.A = take(S->f32_prop  ? nw * (size_t)apk_size((int)M) * 8
@@ -471,7 +473,8 @@ int launch_contraction(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L
 }
 
 // After the contraction: the precision guard's FP64 pass and the energy assembly.
-int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L) {
+int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L,
+                          const FinishArgs& fin) {
   void* ws = w->workspace;
   const int nz = exch_splits(S, w->n_walkers);
   const size_t xst = (size_t)w->n_walkers * S->n_det * 2;
@@ -498,46 +501,54 @@ int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout
                            1));
     }
   }
-  if (S->multi) {
-    Timer tm(S, KG_ASSEMBLE);
+  Timer tm(S, KG_ASSEMBLE);
+  if (S->multi)
     hipLaunchKernelGGL(k_energy_assemble_multi, dim3(w->n_walkers), dim3(256), 0, S->stream, S->G,
                        S->n_det, S->h0, (double)S->sf, S->coef, at<cd>(ws, L.tpart),
                        at<cd>(ws, L.exch), nz, xst, at<cd>(ws, L.e1), at<cd>(ws, L.logdet),
-                       at<unsigned>(ws, L.wflag), w->weight, 1, at<cd>(ws, L.tcur),
-                       at<cd>(ws, L.enew), at<cd>(ws, L.ldc), at<unsigned>(ws, L.wflc));
-    HIPCHK(hipGetLastError());
-  } else {
-    Timer tm(S, KG_ASSEMBLE);
+                       at<unsigned>(ws, L.wflag), at<cd>(ws, L.tcur), at<cd>(ws, L.ldc),
+                       at<unsigned>(ws, L.wflc), fin);
+  else
     hipLaunchKernelGGL(k_energy_assemble, dim3(w->n_walkers), dim3(256), 0, S->stream, S->G, S->h0,
-                       (double)S->sf,
-                       at<cd>(ws, L.tpart), at<cd>(ws, L.exch), nz, xst, at<cd>(ws, L.e1), w->weight, 1,
-                       at<cd>(ws, L.tcur), at<cd>(ws, L.enew));
-    HIPCHK(hipGetLastError());
-  }
+                       (double)S->sf, at<cd>(ws, L.tpart), at<cd>(ws, L.exch), nz, xst,
+                       at<cd>(ws, L.e1), at<cd>(ws, L.tcur), fin);
+  HIPCHK(hipGetLastError());
   return AFQMC_OK;
 }
 
-int launch_contract(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L, bool in_step) {
-  int rc = launch_guard_list(S, w, L, in_step);
+// What the assembly does with the walkers; mode 3 (a measurement) until the caller sets a step's.
+FinishArgs finish_args(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L) {
+  void* ws = w->workspace;
+  FinishArgs a{};
+  a.mode = 3;
+  a.sf = (double)S->sf;
+  a.growth = at<double>(ws, L.growth);
+  a.logdet = at<cd>(ws, S->multi ? L.ldc : L.logdet);
+  a.wflag = at<unsigned>(ws, S->multi ? L.wflc : L.wflag);
+  a.weight = w->weight;
+  a.arg_ovlp = w->arg_ovlp;
+  a.log_ovlp = w->log_ovlp;
+  a.e_loc = (cd*)w->e_loc;
+  a.phase = w->phase;
+  a.wold = at<double>(ws, L.wold);
+  a.wstat = at<unsigned>(ws, L.wstat);
+  a.status = S->status;
+  a.dstep = at<int64_t>(ws, L.dstep);
+  a.step = w->step;
+  return a;
+}
+
+int launch_contract(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L,
+                    const FinishArgs& fin) {
+  int rc = launch_guard_list(S, w, L, fin.mode != 3);
   if (!rc) rc = launch_contraction(S, w, L);
-  return rc ? rc : launch_guard_assemble(S, w, L);
+  return rc ? rc : launch_guard_assemble(S, w, L, fin);
 }
 
 int do_measure(afqmc_sys_s* S, afqmc_walkers* w) {
   const WsLayout L = layout(S, (size_t)w->n_walkers);
-  void* ws = w->workspace;
-  hipLaunchKernelGGL(k_step_set, dim3(1), dim3(1), 0, S->stream, at<int64_t>(ws, L.dstep), w->step);
-  int rc = launch_overlap(S, w, L, 1);
-  if (rc) return rc;
-  rc = launch_contract(S, w, L, false);
-  if (rc) return rc;
-  hipLaunchKernelGGL(k_measure_finish, dim3((w->n_walkers + 255) / 256), dim3(256), 0, S->stream,
-                     w->n_walkers, (double)S->sf, at<cd>(ws, S->multi ? L.ldc : L.logdet),
-                     at<unsigned>(ws, S->multi ? L.wflc : L.wflag),
-                     at<cd>(ws, L.enew), w->weight, w->arg_ovlp, w->log_ovlp, (cd*)w->e_loc,
-                     S->status);
-  HIPCHK(hipGetLastError());
-  return AFQMC_OK;
+  const int rc = launch_overlap(S, w, L, 1);
+  return rc ? rc : launch_contract(S, w, L, finish_args(S, w, L));
 }
 
 int launch_fields(afqmc_sys_s* S, const afqmc_walkers* w, const afqmc_fields* f, const WsLayout& L,
@@ -1376,34 +1387,29 @@ int step_post(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool grap
   const int64_t k = w->step;
   int64_t* dstep = at<int64_t>(ws, L.dstep);
   int rc;
-  // 6. the local energy of the new determinants
-  if ((rc = launch_contract(s, w, L, true))) return rc;
+  // 6-7. the local energy of the new determinants and the weights, then the growth-phase sums
+  // around them (App. B.1, B.2)
   const bool qr_due = s->p.qr_period > 0 && (k + 1) % s->p.qr_period == 0;
-  // 7. phaseless weights, with the growth-phase sums around them (App. B.1, B.2)
   const bool pop_due = s->p.pop_period > 0 && (k + 1) % s->p.pop_period == 0;
-  const bool growing = in_growth_phase(s, k);
-  double* growth = at<double>(ws, L.growth);
+  FinishArgs fin = finish_args(s, w, L);
+  fin.mode = (s->p.flags & AFQMC_FLAG_FREE_PROJECTION) ? 2 : (s->p.flags & AFQMC_FLAG_HYBRID) ? 1 : 0;
+  fin.nblk = (s->G + 3) / 4;
+  fin.dtau = s->p.dtau;
+  fin.h0 = s->h0p;
+  fin.ecap_half = sqrt(s->p.el_cap_C / s->p.dtau);
+  fin.w_max = std::isnan(s->p.w_max) ? std::max(100.0, nw / 10.0) : s->p.w_max;
+  fin.fbterm = fin.mode ? at<cd>(ws, L.fbterm) : nullptr;
+  fin.mfterm = (s->p.flags & AFQMC_FLAG_MEAN_FIELD) ? at<cd>(ws, L.mfterm) : nullptr;
+  fin.logR = qr_due ? at<double>(ws, L.logR) : nullptr;
+  if ((rc = launch_contract(s, w, L, fin))) return rc;
   {
     Timer tm(s, KG_WEIGHT);
-    const double wmax = std::isnan(s->p.w_max) ? std::max(100.0, nw / 10.0) : s->p.w_max;
-    const int mode = (s->p.flags & AFQMC_FLAG_FREE_PROJECTION) ? 2
-                     : (s->p.flags & AFQMC_FLAG_HYBRID) ? 1 : 0;
-    if (growing)
-      hipLaunchKernelGGL(k_growth_sum, dim3(1), dim3(256), 0, s->stream, nw, 0, 0, s->p.dtau,
-                         w->weight, (const cd*)w->e_loc, growth);
-    hipLaunchKernelGGL(k_weights, dim3((nw + 255) / 256), dim3(256), 0, s->stream, nw, mode,
-                       (double)s->sf, s->p.dtau, s->h0p, (const double*)growth,
-                       sqrt(s->p.el_cap_C / s->p.dtau), wmax,
-                       at<cd>(ws, s->multi ? L.ldc : L.logdet),
-                       at<unsigned>(ws, s->multi ? L.wflc : L.wflag), at<cd>(ws, L.enew),
-                       mode ? at<cd>(ws, L.fbterm) : nullptr,
-                       (s->p.flags & AFQMC_FLAG_MEAN_FIELD) ? at<cd>(ws, L.mfterm) : nullptr,
-                       (s->G + 3) / 4,
-                       qr_due ? at<double>(ws, L.logR) : nullptr, w->weight, w->arg_ovlp,
-                       w->log_ovlp, (cd*)w->e_loc, w->phase, s->status, s->capcount);
-    if (growing)
-      hipLaunchKernelGGL(k_growth_sum, dim3(1), dim3(256), 0, s->stream, nw, 1, pop_due ? 1 : 0,
-                         s->p.dtau, w->weight, (const cd*)w->e_loc, growth);
+    // the step counter moves on here, or after the comb, which reads it
+    hipLaunchKernelGGL(k_step_finish, dim3(1), dim3(nw > 256 ? 1024 : 256), 0, s->stream, nw,
+                       in_growth_phase(s, k) ? 1 : 0, pop_due ? 1 : 0, s->p.dtau, w->weight,
+                       (const cd*)w->e_loc, (const double*)fin.wold, (const unsigned*)fin.wstat,
+                       at<double>(ws, L.growth), s->status, s->capcount, dstep,
+                       pop_due ? 0 : graph ? 2 : 1, k + 1);
     HIPCHK(hipGetLastError());
   }
   // 8. population control
@@ -1426,9 +1432,9 @@ int step_post(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool grap
                        w->weight, w->walker_id);
     HIPCHK(hipGetLastError());
   }
-  if (graph)
+  if (pop_due && graph)
     hipLaunchKernelGGL(k_step_advance, dim3(1), dim3(1), 0, s->stream, dstep);
-  else
+  else if (pop_due)
     hipLaunchKernelGGL(k_step_set, dim3(1), dim3(1), 0, s->stream, dstep, k + 1);
   HIPCHK(hipGetLastError());
   w->step = k + 1;

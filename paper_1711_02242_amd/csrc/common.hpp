@@ -195,7 +195,7 @@ __device__ inline void wave_argmax(double& best, int& idx) {
   idx = hi_wins ? i63 : i31;
 }
 
-// Growth-phase state of a walker population (k_growth_sum), doubles in the workspace.
+// Growth-phase state of a walker population (k_step_finish), doubles in the workspace.
 enum { GR_ET = 0, GR_EBAR, GR_NUM, GR_DEN, GR_SWE, GR_SW, GR_COUNT = 8 };
 // Counters of the rare-event bounds (App. B.1), 64-bit, library-owned per system:
 // walker-steps with the local energy capped in the weight, with the weight capped,
@@ -237,4 +237,23 @@ __device__ inline double block_sum(double v, double* red) {
   double t = 0.0;
   for (int i = 0; i < nw; ++i) t += red[i];
   return t;
+}
+// N sums at once: their shuffles overlap and they share the barriers.  red: N doubles a wavefront.
+template <int N>
+__device__ inline void block_sums(double (&v)[N], double* red) {
+  const int lane = threadIdx.x % AFQMC_WAVE, wid = threadIdx.x / AFQMC_WAVE;
+  const int nw = (blockDim.x + AFQMC_WAVE - 1) / AFQMC_WAVE;
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
+  __syncthreads();
+  if (lane == 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) red[wid * N + i] = v[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = 0.0;
+  for (int k = 0; k < nw; ++k)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += red[k * N + i];
 }

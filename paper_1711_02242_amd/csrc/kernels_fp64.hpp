@@ -80,36 +80,212 @@ __global__ void __launch_bounds__(256) k_contract_fp64(
 }
 
 // ---------------------------------------------------------------------------
+// What the energy assembly does with a walker's new local energy, by one workgroup per walker.
+//   mode 0 phaseless local energy (eq:if_rle, eq:cap):
+//          W <- min(w_max, W exp(-dtau (Re E_L^cap(old) - E_T)) max(0, cos dtheta)),
+//          Re E_L capped to the centre +- ecap_half; E_T and the centre come from the
+//          population's growth state (k_step_finish)
+//   mode 1 phaseless hybrid (eq:hybrid-wt): W <- min(w_max, W |I| max(0, cos dtheta))
+//   mode 2 free projection (Sec. II.C): W e^{i theta} <- W e^{i theta} I
+//   mode 3 measurement: phase and log of the overlap, E_L; the weight only if the walker is lost
+// with log I = log(<Phi_T|Psi'>/<Phi_T|Psi>) - dtau (h0 - E_T) + sum_g (x xbar - xbar^2/2),
+// where <Phi_T|Psi'> is taken before this step's QR (log det R added back).
+// The old weight and the status bits of every walker go to scratch for k_step_finish.  Bound by
+// latency: everything that does not depend on the energy is read at the start, and the sums share
+// their barriers.  (As
+// launches of their own after the assembly, the weights and two growth sums took 4.7 us each,
+// and the hybrid mode's sums over the field blocks by one thread per walker 59 us.)
+// ---------------------------------------------------------------------------
+struct FinishArgs {
+  int mode, nblk;
+  double sf, dtau, h0, ecap_half, w_max;
+  const double* growth;
+  const cd* logdet;
+  const unsigned* wflag;
+  const cd* fbterm;        // [nw][nblk], modes 1 and 2
+  const cd* mfterm;        // [nw][nblk] or NULL: mean-field c-number on the overlap ratio
+  const double* logR;      // [nw][2] or NULL: this step's QR
+  double *weight, *arg_ovlp, *log_ovlp;
+  cd* e_loc;
+  double* phase;
+  double* wold;            // [nw] weight before the update, 0 for a dead walker
+  unsigned* wstat;         // [nw] status bits of the update
+  unsigned* status;        // sticky status word (mode 3)
+  int64_t* dstep;          // device copy of the step counter, set by a measurement
+  int64_t step;
+};
+
+// What of it can be read before the energy is known (one latency instead of two).
+struct FinishPre {
+  double W, e_trial, e_bar, e_old, arg, lovlp;
+  cd l0, l1;       // log overlap of the two spins
+  unsigned fl;
+};
+__device__ inline void finish_load_overlap(const FinishArgs& a, int w, FinishPre& p) {
+  p.l0 = a.logdet[2 * w];
+  p.l1 = a.logdet[2 * w + 1];
+  p.fl = a.wflag[2 * w] | a.wflag[2 * w + 1];
+}
+__device__ inline FinishPre finish_load(const FinishArgs& a, int w) {
+  FinishPre p;
+  p.W = a.weight[w];
+  p.e_trial = a.growth[GR_ET];
+  p.e_bar = a.growth[GR_EBAR];
+  p.e_old = a.e_loc[w].re;
+  p.arg = a.arg_ovlp[w];
+  p.lovlp = a.log_ovlp[w];
+  return p;
+}
+
+// For pre.W > 0; `red` as for block_sums<4>.
+__device__ inline void finish_walker(const FinishArgs& a, int w, const FinishPre& pre, cd en,
+                                     double* red) {
+  const int tid = threadIdx.x;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};   // mean-field and field sums over the blocks of fields
+  if (a.mode != 3 && (a.mfterm || a.mode != 0)) {
+    for (int b = tid; b < a.nblk; b += blockDim.x) {
+      if (a.mfterm) {
+        const cd f = a.mfterm[(size_t)w * a.nblk + b];
+        v[0] += f.re;
+        v[1] += f.im;
+      }
+      if (a.mode != 0) {
+        const cd f = a.fbterm[(size_t)w * a.nblk + b];
+        v[2] += f.re;
+        v[3] += f.im;
+      }
+    }
+    block_sums(v, red);
+  }
+  const double mre = v[0], mim = v[1], fr = v[2], fi = v[3];
+  if (tid != 0) return;
+  const double W = pre.W;
+  const cd l0 = pre.l0, l1 = pre.l1;
+  double ph = a.sf * l0.im + l1.im;
+  ph = ph - 2.0 * M_PI * floor((ph + M_PI) / (2.0 * M_PI));   // (-pi, pi]
+  if (ph <= -M_PI) ph += 2.0 * M_PI;
+  const double la = a.sf * l0.re + l1.re;
+  const unsigned fl = pre.fl;
+  if (a.mode == 3) {
+    a.arg_ovlp[w] = ph;
+    a.log_ovlp[w] = la;
+    a.e_loc[w] = en;
+    if ((fl & WFLAG_SINGULAR) || !cfinite(en)) {
+      a.weight[w] = 0.0;
+      atomicOr(a.status, (fl & WFLAG_SINGULAR) ? 0x2u : 0x1u);
+    }
+    return;
+  }
+  const double e_trial = pre.e_trial, e_bar = pre.e_bar;
+  unsigned st = 0u;
+  double Wn;
+  if (fl & WFLAG_SINGULAR) {
+    Wn = 0.0;
+    st |= 0x2u;
+  } else if (!cfinite(en) || !isfinite(ph) || !isfinite(la)) {
+    Wn = 0.0;
+    st |= 0x1u;
+  } else if (a.mode == 0) {
+    double ec = pre.e_old;
+    if (ec < e_bar - a.ecap_half) {
+      ec = e_bar - a.ecap_half;
+      st |= 0x4u;
+    } else if (ec > e_bar + a.ecap_half) {
+      ec = e_bar + a.ecap_half;
+      st |= 0x4u;
+    }
+    const double proj = fmax(0.0, cos(ph - pre.arg + mim));
+    if (!(proj > 0.0)) st |= 0x20u;
+    Wn = W * exp(-a.dtau * (ec - e_trial)) * proj;
+    if (Wn > a.w_max) {
+      Wn = a.w_max;
+      st |= 0x8u;
+    }
+  } else {
+    const double lr = a.logR ? a.sf * a.logR[2 * w] + a.logR[2 * w + 1] : 0.0;
+    const double lre = (la + lr - pre.lovlp) + mre - a.dtau * (a.h0 - e_trial) + fr;
+    const double lim = (ph - pre.arg) + mim + fi;
+    if (a.mode == 1) {
+      const double proj = fmax(0.0, cos(ph - pre.arg + mim));
+      if (!(proj > 0.0)) st |= 0x20u;
+      Wn = W * exp(lre) * proj;
+      if (Wn > a.w_max) {
+        Wn = a.w_max;
+        st |= 0x8u;
+      }
+    } else {
+      Wn = W * exp(lre);
+      double th = a.phase[w] + lim;
+      th = th - 2.0 * M_PI * floor((th + M_PI) / (2.0 * M_PI));
+      if (th <= -M_PI) th += 2.0 * M_PI;
+      a.phase[w] = th;
+      if (!isfinite(Wn)) {
+        Wn = 0.0;
+        st |= 0x1u;
+      }
+    }
+  }
+  a.wold[w] = W;
+  a.wstat[w] = st;
+  a.weight[w] = Wn;
+  a.arg_ovlp[w] = ph;
+  a.log_ovlp[w] = la;
+  a.e_loc[w] = en;
+}
+// The same for a dead walker (a measurement reports again why it was lost), and the
+// measurement's copy of the step counter.
+__device__ inline void finish_dead(const FinishArgs& a, int w) {
+  if (threadIdx.x != 0) return;
+  if (a.mode == 3) {
+    const unsigned fl = a.wflag[2 * w] | a.wflag[2 * w + 1];
+    if ((fl & WFLAG_SINGULAR) || !cfinite(a.e_loc[w]))
+      atomicOr(a.status, (fl & WFLAG_SINGULAR) ? 0x2u : 0x1u);
+    return;
+  }
+  a.wold[w] = 0.0;
+  a.wstat[w] = 0u;
+}
+__device__ inline void finish_counter(const FinishArgs& a, int w) {
+  if (w == 0 && threadIdx.x == 0 && a.mode == 3) *a.dstep = a.step;
+}
+
+// ---------------------------------------------------------------------------
 // Local-energy assembly: t_g = sum_s tpart, E_L = h0 + e1 + 1/2 (sum_g t_g^2 - exch)
-// (eq:localenergy2-3 with the 1/2 of eq:bo_ham2).  One block per walker.
+// (eq:localenergy2-3 with the 1/2 of eq:bo_ham2), then finish_walker.  One block per walker.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_energy_assemble(
     int G, double h0, double sf, const cd* __restrict__ tpart, const cd* __restrict__ exch, int nz,
     size_t xst /*exch holds nz partial sums, xst apart*/,
-    const cd* __restrict__ e1, const double* __restrict__ weight, int check_weight,
-    cd* __restrict__ tcur /*[nw][G]*/, cd* __restrict__ enew /*[nw]*/) {
-  __shared__ double red[8];
+    const cd* __restrict__ e1, cd* __restrict__ tcur /*[nw][G]*/, FinishArgs fin) {
+  __shared__ double red[16];
   const int w = blockIdx.x, tid = threadIdx.x;
-  if (check_weight && !(weight[w] > 0.0)) return;
-  double jr = 0.0, ji = 0.0;
-  for (int g = tid; g < G; g += blockDim.x) {
-    const cd t = cadd(cscale(tpart[((size_t)w * 2) * G + g], sf), tpart[((size_t)w * 2 + 1) * G + g]);
-    tcur[(size_t)w * G + g] = t;
-    jr += t.re * t.re - t.im * t.im;
-    ji += 2.0 * t.re * t.im;
+  FinishPre pre = finish_load(fin, w);
+  finish_load_overlap(fin, w, pre);
+  finish_counter(fin, w);
+  if (!(pre.W > 0.0)) {
+    finish_dead(fin, w);
+    return;
   }
-  jr = block_sum(jr, red);
-  ji = block_sum(ji, red);
-  if (tid == 0) {
+  cd x = mkc(0.0, 0.0), e = mkc(0.0, 0.0);
+  if (tid == 0) {   // read before the sums
     cd x0 = exch[2 * w], x1 = exch[2 * w + 1];
     for (int z = 1; z < nz; ++z) {
       x0 = cadd(x0, exch[z * xst + 2 * w]);
       x1 = cadd(x1, exch[z * xst + 2 * w + 1]);
     }
-    const cd x = cadd(cscale(x0, sf), x1);
-    const cd e = cadd(cscale(e1[2 * w], sf), e1[2 * w + 1]);
-    enew[w] = mkc(h0 + e.re + 0.5 * (jr - x.re), e.im + 0.5 * (ji - x.im));
+    x = cadd(cscale(x0, sf), x1);
+    e = cadd(cscale(e1[2 * w], sf), e1[2 * w + 1]);
   }
+  double j[2] = {0.0, 0.0};
+  for (int g = tid; g < G; g += blockDim.x) {
+    const cd t = cadd(cscale(tpart[((size_t)w * 2) * G + g], sf), tpart[((size_t)w * 2 + 1) * G + g]);
+    tcur[(size_t)w * G + g] = t;
+    j[0] += t.re * t.re - t.im * t.im;
+    j[1] += 2.0 * t.re * t.im;
+  }
+  block_sums(j, red);
+  const cd en = mkc(h0 + e.re + 0.5 * (j[0] - x.re), e.im + 0.5 * (j[1] - x.im));
+  finish_walker(fin, w, pre, en, red);
 }
 
 // Multi-determinant trial Psi_T = sum_d A_d Psi_d (Sec. II.B, eq:localenergy2, eq:precomputing2).
@@ -127,17 +303,21 @@ __global__ void __launch_bounds__(256) k_energy_assemble_multi(
     int G, int n_det, double h0, double sf, const double* __restrict__ coef /*[n_det][2]*/,
     const cd* __restrict__ tpart, const cd* __restrict__ exch, int nz, size_t xst,
     const cd* __restrict__ e1, const cd* __restrict__ logdet, const unsigned* __restrict__ wflag,
-    const double* __restrict__ weight, int check_weight, cd* __restrict__ tcur /*[nw][G]*/,
-    cd* __restrict__ enew /*[nw]*/, cd* __restrict__ ldc /*[nw][2]*/,
-    unsigned* __restrict__ wflc /*[nw][2]*/) {
-  __shared__ double red[8];
+    cd* __restrict__ tcur /*[nw][G]*/, cd* ldc /*[nw][2]*/, unsigned* wflc /*[nw][2]*/,
+    FinishArgs fin /*its logdet and wflag are ldc and wflc*/) {
+  __shared__ double red[16];
   __shared__ cd s_r[AFQMC_MAX_DETS];    // r_d / R
   __shared__ cd s_lg[AFQMC_MAX_DETS];   // log <Psi_d|Psi>
   __shared__ int s_ok[AFQMC_MAX_DETS];
   __shared__ cd s_esum;
   __shared__ int s_bad, s_first;
   const int w = blockIdx.x, tid = threadIdx.x;
-  if (check_weight && !(weight[w] > 0.0)) return;
+  FinishPre pre = finish_load(fin, w);
+  finish_counter(fin, w);
+  if (!(pre.W > 0.0)) {
+    finish_dead(fin, w);
+    return;
+  }
   for (int d = tid; d < n_det; d += blockDim.x) {
     const size_t wd = (size_t)w * n_det + d;
     const cd l0 = logdet[2 * wd], l1 = logdet[2 * wd + 1];
@@ -182,22 +362,20 @@ __global__ void __launch_bounds__(256) k_energy_assemble_multi(
     s_esum = mkc(0.0, 0.0);
   }
   __syncthreads();
-  if (s_bad) return;
   for (int d = 0; d < n_det; ++d) {
-    if (!s_ok[d]) continue;  // uniform over the block
+    if (s_bad || !s_ok[d]) continue;  // uniform over the block
     const size_t wd = (size_t)w * n_det + d;
     const cd rd = s_r[d];
-    double jr = 0.0, ji = 0.0;
+    double j[2] = {0.0, 0.0};
     for (int g = tid; g < G; g += blockDim.x) {
       const cd t = cadd(cscale(tpart[(wd * 2) * G + g], sf), tpart[(wd * 2 + 1) * G + g]);
       const cd c = cmul(rd, t);
       // the first usable determinant writes, later ones accumulate (same thread owns g)
       tcur[(size_t)w * G + g] = (d == s_first) ? c : cadd(tcur[(size_t)w * G + g], c);
-      jr += t.re * t.re - t.im * t.im;
-      ji += 2.0 * t.re * t.im;
+      j[0] += t.re * t.re - t.im * t.im;
+      j[1] += 2.0 * t.re * t.im;
     }
-    jr = block_sum(jr, red);
-    ji = block_sum(ji, red);
+    block_sums(j, red);
     if (tid == 0) {
       cd x0 = exch[2 * wd], x1 = exch[2 * wd + 1];
       for (int z = 1; z < nz; ++z) {
@@ -206,11 +384,12 @@ __global__ void __launch_bounds__(256) k_energy_assemble_multi(
       }
       const cd x = cadd(cscale(x0, sf), x1);
       const cd e = cadd(cscale(e1[2 * wd], sf), e1[2 * wd + 1]);
-      const cd ed = mkc(h0 + e.re + 0.5 * (jr - x.re), e.im + 0.5 * (ji - x.im));
+      const cd ed = mkc(h0 + e.re + 0.5 * (j[0] - x.re), e.im + 0.5 * (j[1] - x.im));
       s_esum = cadd(s_esum, cmul(rd, ed));
     }
   }
-  if (tid == 0) enew[w] = s_esum;
+  if (tid == 0) finish_load_overlap(fin, w, pre);   // written above by this thread
+  finish_walker(fin, w, pre, s_esum, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -550,115 +729,6 @@ __global__ void __launch_bounds__(256) k_mgs_reg(int M, int nup, int ndn, cd* __
 }
 
 // ---------------------------------------------------------------------------
-// Weight update, one thread per walker.
-//   mode 0 phaseless local energy (eq:if_rle, eq:cap):
-//          W <- min(w_max, W exp(-dtau (Re E_L^cap(old) - E_T)) max(0, cos dtheta)),
-//          Re E_L capped to the centre +- ecap_half; E_T and the centre come from the
-//          population's growth state (k_growth_sum)
-//   mode 1 phaseless hybrid (eq:hybrid-wt): W <- min(w_max, W |I| max(0, cos dtheta))
-//   mode 2 free projection (Sec. II.C): W e^{i theta} <- W e^{i theta} I
-// with log I = log(<Phi_T|Psi'>/<Phi_T|Psi>) - dtau (h0 - E_T) + sum_g (x xbar - xbar^2/2),
-// where <Phi_T|Psi'> is taken before this step's QR (log det R added back).
-// ---------------------------------------------------------------------------
-__global__ void k_weights(int nw, int mode, double sf, double dtau, double h0,
-                          const double* __restrict__ growth, double ecap_half, double w_max,
-                          const cd* __restrict__ logdet,
-                          const unsigned* __restrict__ wflag, const cd* __restrict__ enew,
-                          const cd* __restrict__ fbterm, const cd* __restrict__ mfterm, int nblk,
-                          const double* __restrict__ logR,
-                          double* __restrict__ weight, double* __restrict__ arg_ovlp,
-                          double* __restrict__ log_ovlp, cd* __restrict__ e_loc,
-                          double* __restrict__ phase, unsigned* __restrict__ status,
-                          unsigned long long* __restrict__ counts) {
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= nw) return;
-  const double W = weight[w];
-  if (!(W > 0.0)) return;
-  const double e_trial = growth[GR_ET];
-  const double e_bar = growth[GR_EBAR];
-  unsigned st = 0u;
-  const cd l0 = logdet[2 * w], l1 = logdet[2 * w + 1];
-  double a = sf * l0.im + l1.im;
-  a = a - 2.0 * M_PI * floor((a + M_PI) / (2.0 * M_PI));   // (-pi, pi]
-  if (a <= -M_PI) a += 2.0 * M_PI;
-  const double la = sf * l0.re + l1.re;
-  const cd en = enew[w];
-  const unsigned fl = wflag[2 * w] | wflag[2 * w + 1];
-  // mean-field c-number on the overlap ratio (zero without subtraction)
-  double mre = 0.0, mim = 0.0;
-  if (mfterm)
-    for (int b = 0; b < nblk; ++b) {
-      const cd f = mfterm[(size_t)w * nblk + b];
-      mre += f.re;
-      mim += f.im;
-    }
-  double Wn;
-  if (fl & WFLAG_SINGULAR) {
-    Wn = 0.0;
-    st |= 0x2u;
-  } else if (!cfinite(en) || !isfinite(a) || !isfinite(la)) {
-    Wn = 0.0;
-    st |= 0x1u;
-  } else if (mode == 0) {
-    const cd eo = e_loc[w];
-    double ec = eo.re;
-    if (ec < e_bar - ecap_half) {
-      ec = e_bar - ecap_half;
-      st |= 0x4u;
-    } else if (ec > e_bar + ecap_half) {
-      ec = e_bar + ecap_half;
-      st |= 0x4u;
-    }
-    const double proj = fmax(0.0, cos(a - arg_ovlp[w] + mim));
-    if (!(proj > 0.0)) st |= 0x20u;
-    Wn = W * exp(-dtau * (ec - e_trial)) * proj;
-    if (Wn > w_max) {
-      Wn = w_max;
-      st |= 0x8u;
-    }
-  } else {
-    double fr = 0.0, fi = 0.0;
-    for (int b = 0; b < nblk; ++b) {
-      const cd f = fbterm[(size_t)w * nblk + b];
-      fr += f.re;
-      fi += f.im;
-    }
-    const double lr = logR ? sf * logR[2 * w] + logR[2 * w + 1] : 0.0;
-    const double lre = (la + lr - log_ovlp[w]) + mre - dtau * (h0 - e_trial) + fr;
-    const double lim = (a - arg_ovlp[w]) + mim + fi;
-    if (mode == 1) {
-      const double proj = fmax(0.0, cos(a - arg_ovlp[w] + mim));
-      if (!(proj > 0.0)) st |= 0x20u;
-      Wn = W * exp(lre) * proj;
-      if (Wn > w_max) {
-        Wn = w_max;
-        st |= 0x8u;
-      }
-    } else {
-      Wn = W * exp(lre);
-      double th = phase[w] + lim;
-      th = th - 2.0 * M_PI * floor((th + M_PI) / (2.0 * M_PI));
-      if (th <= -M_PI) th += 2.0 * M_PI;
-      phase[w] = th;
-      if (!isfinite(Wn)) {
-        Wn = 0.0;
-        st |= 0x1u;
-      }
-    }
-  }
-  weight[w] = Wn;
-  arg_ovlp[w] = a;
-  log_ovlp[w] = la;
-  e_loc[w] = en;
-  if (st) atomicOr(status, st);
-  if (counts) {
-    wave_count(&counts[CAP_E], (st & 0x4u) != 0u);
-    wave_count(&counts[CAP_W], (st & 0x8u) != 0u);
-    wave_count(&counts[CAP_LIVE], true);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Growth phase (App. B.1, B.2): the trial energy E_T of the importance function and the
 // centre of the local-energy cap (eq:cap) of one walker population, in the workspace:
 //   g[GR_ET] E_T, g[GR_EBAR] cap centre, and the sums over the current population-control
@@ -677,58 +747,56 @@ __global__ void k_growth_init(double* __restrict__ g, double e_trial) {
   if (threadIdx.x < GR_COUNT) g[threadIdx.x] = threadIdx.x <= GR_EBAR ? e_trial : 0.0;
 }
 
-// after == 0: before the weight update, den += sum W.  after == 1: num += sum W,
-// swe += sum W Re E_L, sw += sum W, then the update at a block end.  One block of 256.
-__global__ void __launch_bounds__(256) k_growth_sum(int nw, int after, int block_end, double dtau,
-                                                    const double* __restrict__ weight,
-                                                    const cd* __restrict__ e_loc,
-                                                    double* __restrict__ g) {
-  __shared__ double red[4];
-  double a = 0.0, b = 0.0;
+// After the weight update of a step, one workgroup: the counters of the rare-event bounds and the
+// status word from every walker's bits; in the growth phase den += sum W (before the update),
+// num += sum W, swe += sum W Re E_L, sw += sum W (after it), and the update at a block end; the
+// device copy of the step counter (set_step: 1 set to `step`, 2 advanced, 0 left alone).
+__global__ void __launch_bounds__(1024) k_step_finish(
+    int nw, int growing, int block_end, double dtau, const double* __restrict__ weight,
+    const cd* __restrict__ e_loc, const double* __restrict__ wold,
+    const unsigned* __restrict__ wstat, double* __restrict__ g, unsigned* __restrict__ status,
+    unsigned long long* __restrict__ counts, int64_t* __restrict__ dstep, int set_step,
+    int64_t step) {
+  __shared__ double red[16 * 6];
+  double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};   // sums before and after, and three counts:
+  unsigned bits = 0u;                             // whole numbers, exact in double in any order
+  double old[GR_COUNT] = {};
+  if (growing)
+    for (int i = 0; i < GR_COUNT; ++i) old[i] = g[i];
   for (int w = threadIdx.x; w < nw; w += blockDim.x) {
-    const double W = weight[w];
+    const double Wo = wold[w], W = weight[w], e = e_loc[w].re;
+    const unsigned st = wstat[w];
+    if (!(Wo > 0.0)) continue;
+    bits |= st;
+    v[3] += 1.0;
+    v[4] += (st & 0x4u) ? 1.0 : 0.0;
+    v[5] += (st & 0x8u) ? 1.0 : 0.0;
+    v[0] += Wo;
     if (W > 0.0) {
-      a += W;
-      if (after) b += W * e_loc[w].re;
+      v[1] += W;
+      v[2] += W * e;
     }
   }
-  a = block_sum(a, red);
-  if (after) b = block_sum(b, red);
+  if (bits) atomicOr(status, bits);
+  block_sums(v, red);
   if (threadIdx.x != 0) return;
-  if (!after) {
-    g[GR_DEN] += a;
-    return;
+  counts[CAP_LIVE] += (unsigned long long)v[3];
+  counts[CAP_E] += (unsigned long long)v[4];
+  counts[CAP_W] += (unsigned long long)v[5];
+  if (growing) {
+    const double den = old[GR_DEN] + v[0], num = old[GR_NUM] + v[1], swe = old[GR_SWE] + v[2],
+                 sw = old[GR_SW] + v[1];
+    if (block_end) {
+      if (num > 0.0 && den > 0.0) g[GR_ET] = old[GR_ET] - log(num / den) / dtau;
+      if (sw > 0.0) g[GR_EBAR] = swe / sw;
+    }
+    g[GR_DEN] = block_end ? 0.0 : den;
+    g[GR_NUM] = block_end ? 0.0 : num;
+    g[GR_SWE] = block_end ? 0.0 : swe;
+    g[GR_SW] = block_end ? 0.0 : sw;
   }
-  g[GR_NUM] += a;
-  g[GR_SWE] += b;
-  g[GR_SW] += a;
-  if (block_end) {
-    if (g[GR_NUM] > 0.0 && g[GR_DEN] > 0.0) g[GR_ET] = g[GR_ET] - log(g[GR_NUM] / g[GR_DEN]) / dtau;
-    if (g[GR_SW] > 0.0) g[GR_EBAR] = g[GR_SWE] / g[GR_SW];
-    g[GR_NUM] = g[GR_DEN] = g[GR_SWE] = g[GR_SW] = 0.0;
-  }
-}
-
-// Initialization / measurement: phase and log of the overlap, E_L, from logdet and enew.
-__global__ void k_measure_finish(int nw, double sf, const cd* __restrict__ logdet,
-                                 const unsigned* __restrict__ wflag, const cd* __restrict__ enew,
-                                 double* __restrict__ weight, double* __restrict__ arg_ovlp,
-                                 double* __restrict__ log_ovlp, cd* __restrict__ e_loc,
-                                 unsigned* __restrict__ status) {
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= nw) return;
-  const cd l0 = logdet[2 * w], l1 = logdet[2 * w + 1];
-  double a = sf * l0.im + l1.im;
-  a = a - 2.0 * M_PI * floor((a + M_PI) / (2.0 * M_PI));
-  if (a <= -M_PI) a += 2.0 * M_PI;
-  const unsigned fl = wflag[2 * w] | wflag[2 * w + 1];
-  arg_ovlp[w] = a;
-  log_ovlp[w] = sf * l0.re + l1.re;
-  e_loc[w] = enew[w];
-  if ((fl & WFLAG_SINGULAR) || !cfinite(enew[w])) {
-    weight[w] = 0.0;
-    atomicOr(status, (fl & WFLAG_SINGULAR) ? 0x2u : 0x1u);
-  }
+  if (set_step == 1) *dstep = step;
+  if (set_step == 2) *dstep += 1;
 }
 
 // ---------------------------------------------------------------------------
