@@ -18,7 +18,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libafqmc.so")
-SOURCES = ["afqmc.hip", "contract_launch.hip", "contract_launch_flat.hip"]
+SOURCES = ["afqmc.hip", "contract_launch.hip", "contract_launch_flat.hip", "contract_launch_share.hip"]
 ARCH = os.environ.get("AFQMC_OFFLOAD_ARCH", "gfx950")
 
 

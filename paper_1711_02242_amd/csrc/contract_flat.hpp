@@ -24,6 +24,7 @@
 // is written out once at the end (no atomics: the result is the same on every run).  Rows
 // are read in place from the padded [g][N_P][K_P] table of the other kernels; rows past a
 // group's end read a valid row and are never used.
+// FP32 at N_g (N_up + N_dn) >= 49152: contract_share.hpp takes its place.
 #pragma once
 
 constexpr int FLAT_MAX_RT = 7;              // row tiles of a group (FP32; BF16x3 4: its A

@@ -48,6 +48,11 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
     tile = (size_t)((nw + 7) / 8) * spins * n_det * nz >= (size_t)device_cu_count() ? TILE_BX8
                                                                                       : TILE_BX;
   }
+  if (!plain) {
+    const ShareLaunch f = share_of(t, tile);
+    if (f.ok)
+      return mfma_contract_share(t, st, nw, n_det, G, thetaP, weight, tpart, exch, f, sel, nz);
+  }
   if (tile == TILE_FLAT || tile == TILE_STACK)
     return mfma_contract_flat(t, st, nw, n_det, G, thetaP, weight, tpart, exch, tile == TILE_STACK,
                               sel, nz, bf ? t.KP / 32 : nk16);

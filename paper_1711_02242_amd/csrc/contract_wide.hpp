@@ -15,6 +15,7 @@
 // Omega is written column-major to LDS so that each lane reads the partner
 // Omega_ji of every Omega_ij it holds; tr(Omega Omega) is summed per g in FP32 and
 // across g in FP64, and wave 0 / wave 1 form Re / Im tr Omega.
+// FP32 at N_g (N_up + N_dn) >= 49152: contract_share.hpp takes its place.
 #pragma once
 
 template <int NPW, bool BF16, int NK>

@@ -169,6 +169,7 @@ inline void mfma_free_tables(MfmaTables& t) {
 #include "contract_mfma.hpp"
 #include "contract_wide.hpp"
 #include "contract_flat.hpp"
+#include "contract_share.hpp"
 #include "contract_pp.hpp"
 #include "contract_bx.hpp"
 
@@ -403,12 +404,25 @@ inline size_t mfma_f64_contract_lds_bytes(const MfmaTables& t) {
 // takes whole rounds of the device's workgroup slots: the split with the least of the product, of
 // at least 8 vectors each.  Slots per CU: the kernels with a wavefront per walker-spin eight
 // wavefronts at N_P = 32 (the registers hold Theta), sixteen at N_P = 16; the wide kernel twelve
-// (eight at N_P = 64), the stacked-row kernels about two workgroups.  One function of the sizes
-// for all variants with a wavefront per walker-spin, so that those with the same arithmetic keep
-// the same sums.  M = 112, N = 28 closed shell, 1024 walkers: 128 workgroups of eight, 2 splits;
+// (eight at N_P = 64), the stacked-row kernels about two workgroups, the shared-row kernel one.  One
+// function of the sizes for all variants with a wavefront per walker-spin, so that those with the
+// same arithmetic keep the same sums.  M = 112, N = 28 closed shell, 1024 walkers: 128 workgroups of eight, 2 splits;
 // M = 64, N = 16, 512 walkers: 256 of four, 4 splits; M = 143, N = 35, 701 walkers: 1402 wide
 // workgroups for 1024 slots, 8 splits.
 constexpr int CONTRACT_MAX_SPLITS = 16;
+// Geometry of the shared-row kernel where it takes a variant's place: the FP32 wide, flattened and
+// stacked-row forms.  It groups the FP32 terms of the exchange otherwise, which shows as
+// 6e-8 / sqrt(4 N_g N) of the local energy (2e-10 at N_g N = 30 000); below N_g (N_up + N_dn) =
+// 49152 the variants keep their own kernels, and their sums (a contraction of 100 walkers there
+// takes 2 ms at most).
+inline ShareLaunch share_of(const MfmaTables& t, int tile) {
+  if (!t.enabled || t.precision != AFQMC_FP32) return ShareLaunch{};
+  if (!mfma_tile_valid(t, tile)) tile = TILE_DEFAULT;
+  if (tile == TILE_DEFAULT && t.wide) tile = TILE_WIDE;
+  if (tile != TILE_WIDE && tile != TILE_FLAT && tile != TILE_STACK) return ShareLaunch{};
+  if ((long long)t.G * (t.nup + t.ndn) < 49152) return ShareLaunch{};
+  return share_launch(t.nup, t.ndn, t.M, t.G);
+}
 inline bool mfma_splittable(const MfmaTables& t) {
   return t.enabled && t.precision != AFQMC_FP64;
 }
@@ -418,6 +432,8 @@ inline int mfma_splits(const MfmaTables& t, int nw, int n_det, int G, int tile) 
   long long per = t.NP == 32 ? 8 : 4, slots = t.NP == 32 ? 1 : 4;   // walkers per workgroup; per CU
   if (tile == TILE_FLAT || tile == TILE_STACK) per = 1, slots = 2;
   else if (t.wide || tile == TILE_WIDE) per = 1, slots = t.NP == 32 ? 6 : t.NP == 48 ? 4 : 2;
+  const ShareLaunch sh = share_of(t, tile);
+  if (sh.ok) per = sh.W, slots = 1;
   slots *= device_cu_count();
   const long long wgs = (nw + per - 1) / per * spins * n_det;
   int best = 1;
@@ -430,13 +446,17 @@ inline int mfma_splits(const MfmaTables& t, int nw, int n_det, int G, int tile) 
 }
 
 // The contraction of every walker by one of the variants, in nz splits (FP64: 1).
-// contract_launch.hip and contract_launch_flat.hip: translation units of their own, for their
-// many kernel instances.  `plain`:
-// whole steps of 32 k, as the autotuner compares the variants; else FP32 chunks of 16 k past M are
-// left out where the kernel has such an instance.
+// contract_launch*.hip: translation units of their own, for their many kernel instances.  `plain`:
+// the variants' own kernels, in whole steps of 32 k, as the autotuner compares them (the choice
+// says which order of FP32 products a system gets, so it does not move with their tuning); else
+// FP32 chunks of 16 k past M are left out where the kernel has such an instance.
 hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
                          const void* thetaP, const double* weight, cd* tpart, cd* exch, int tile,
                          ContractSel sel, int nz, bool plain = false);
+// Its shared-row part, f from share_of.
+hipError_t mfma_contract_share(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
+                               const void* thetaP, const double* weight, cd* tpart, cd* exch,
+                               const ShareLaunch& f, ContractSel sel, int nz);
 // The stacked-row kernels' part of it: nk chunks of 16 k (BF16x3: of 32).
 hipError_t mfma_contract_flat(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
                               const void* thetaP, const double* weight, cd* tpart, cd* exch,
