@@ -1210,20 +1210,26 @@ int step_pre(afqmc_sys_s* s, afqmc_walkers* w, const afqmc_fields* f, bool graph
     if (s->prop_wide) {
       Timer tm(s, KG_PROP);
       const int Kp = ((M + 15) / 16) * 16;
-      const size_t shm = (size_t)2 * 64 * (Kp + 4) * 4;
+      const int nrb = (std::max(s->nup, s->ndn) + 15) / 16;
+      const size_t shm = (size_t)2 * 16 * nrb * (Kp + 4) * 4;
+#define PROPW_R(NKCV, NRBV)                                                                    \
+  case NRBV:                                                                                   \
+    (void)hipFuncSetAttribute((const void*)k_propagate_f32_wide<NKCV, NRBV>,                   \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
+    hipLaunchKernelGGL((k_propagate_f32_wide<NKCV, NRBV>), dim3(nw, 2), dim3(64 * NKCV), shm,  \
+                       s->stream, M, s->nup, s->ndn, Kp, s->G > 0 ? s->p.n_taylor : 0,         \
+                       s->Eh32, Are, Aim, (cd*)w->U, w->weight);                               \
+    break;
 #define PROPW(NKCV)                                                                            \
   case NKCV:                                                                                   \
-    (void)hipFuncSetAttribute((const void*)k_propagate_f32_wide<NKCV>,                         \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);           \
-    hipLaunchKernelGGL(k_propagate_f32_wide<NKCV>, dim3(nw, 2), dim3(64 * NKCV), shm, s->stream, \
-                       M, s->nup, s->ndn, Kp, s->G > 0 ? s->p.n_taylor : 0, s->Eh32, Are, Aim, \
-                       (cd*)w->U, w->weight);                                                  \
+    switch (nrb) { PROPW_R(NKCV, 1) PROPW_R(NKCV, 2) PROPW_R(NKCV, 3) PROPW_R(NKCV, 4) }       \
     break;
       switch (Kp / 16) {
         PROPW(1) PROPW(2) PROPW(3) PROPW(4) PROPW(5) PROPW(6) PROPW(7)
         PROPW(8) PROPW(9) PROPW(10) PROPW(11) PROPW(12) PROPW(13) PROPW(14)
         default: return AFQMC_E_UNSUPPORTED;
       }
+#undef PROPW_R
 #undef PROPW
       HIPCHK(hipGetLastError());
     } else {

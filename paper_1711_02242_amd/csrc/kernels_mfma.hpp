@@ -413,8 +413,7 @@ constexpr int CONTRACT_MAX_SPLITS = 16;
 // Geometry of the shared-row kernel where it takes a variant's place: the FP32 wide, flattened and
 // stacked-row forms.  It groups the FP32 terms of the exchange otherwise, which shows as
 // 6e-8 / sqrt(4 N_g N) of the local energy (2e-10 at N_g N = 30 000); below N_g (N_up + N_dn) =
-// 49152 the variants keep their own kernels, and their sums (a contraction of 100 walkers there
-// takes 2 ms at most).
+// 49152 the variants keep their own kernels, and their sums.
 inline ShareLaunch share_of(const MfmaTables& t, int tile) {
   if (!t.enabled || t.precision != AFQMC_FP32) return ShareLaunch{};
   if (!mfma_tile_valid(t, tile)) tile = TILE_DEFAULT;

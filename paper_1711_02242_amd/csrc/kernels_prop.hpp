@@ -433,29 +433,37 @@ __global__ void __launch_bounds__(64 * NKC, 1) k_propagate_f32(
 // (grid: walkers x 2 spins).  As in k_propagate_f32, one wavefront per 16 output
 // columns q and the current term (rows c, FP32 Re/Im planes) in LDS as the A operand;
 // the B operands (columns q of E_h and of A, read as rows since both are symmetric)
-// are streamed from memory one 16-wide K chunk ahead instead of being held in
-// registers; a workgroup of NKC wavefronts gets 512 / ceil(NKC / 4) VGPRs per wave.
+// are E_h's a 16-wide K chunk ahead from memory, and A's in registers for the whole series where
+// they fit (prop_wide_reg: 8 NKC of the 512 / ceil(NKC / 4) VGPRs a wave has), else streamed too.
+// NRB = ceil(max(N_up, N_dn) / 16) row blocks.  The products of a row block wait for each other,
+// so those of RS row blocks alternate (two where the registers are short).  M = 143, N = 35+33,
+// 701 walkers, six terms: 0.95 ms, 49 TFLOP/s; with A streamed in every term, four scattered
+// loads above the diagonal: 1.50 ms.  M = 220, N = 60, 512 walkers (streamed): 2.51 against 2.83 ms
+// without the compile-time row blocks.
 // ---------------------------------------------------------------------------
-template <int NKC>
+constexpr bool prop_wide_reg(int nkc, int nrb) { return nkc <= 8 || (nkc <= 10 && nrb <= 3); }
+
+template <int NKC, int NRB>
 __global__ void __launch_bounds__(64 * NKC) k_propagate_f32_wide(
     int M, int nup, int ndn, int Kp, int n_taylor, const float* __restrict__ Eh32 /*[M][M]*/,
     const float* __restrict__ Are, const float* __restrict__ Aim, cd* __restrict__ U,
     const double* __restrict__ weight) {
   extern __shared__ __attribute__((aligned(16))) float tsm[];
-  constexpr int RB = 4;                         // row blocks of 16 (N_s <= 64)
+  constexpr int RB = NRB;                       // row blocks of 16
+  constexpr bool REG = prop_wide_reg(NKC, NRB);
+  constexpr int RS = NKC <= 8 || (NKC <= 12 && RB <= 3) ? RB : 2;   // row blocks that alternate
   const int w = blockIdx.x, s = blockIdx.y;
   const int N = s ? ndn : nup, off = s ? nup : 0, ntot = nup + ndn;
   if (N == 0 || !(weight[w] > 0.0)) return;     // uniform over the workgroup
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ldt = Kp + 4;
-  float* Tr = tsm;                  // [64][ldt]
-  float* Ti = tsm + 16 * RB * ldt;  // [64][ldt]
+  float* Tr = tsm;                  // [16 RB][ldt]
+  float* Ti = tsm + 16 * RB * ldt;  // [16 RB][ldt]
   const int j = lane & 15, q4 = lane >> 4;
   const int qcol = 16 * wave + j;   // output column owned by the lane
   const bool colok = qcol < M;
   const size_t MA = (size_t)apk_size(M);
-  const int nrb = (N + 15) / 16;
   const float* Eq = Eh32 + (size_t)(colok ? qcol : 0) * M;
   const float* Aw_re = Are + (size_t)w * MA;
   const float* Aw_im = Aim + (size_t)w * MA;
@@ -481,6 +489,14 @@ __global__ void __launch_bounds__(64 * NKC) k_propagate_f32_wide(
     Tr[c * ldt + p] = (float)v.re;
     Ti[c * ldt + p] = (float)v.im;
   }
+  f32x4 bar_[REG ? NKC : 1], bai[REG ? NKC : 1];
+  if constexpr (REG) {
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) {
+      bar_[kc] = lda4(Aw_re, kc);
+      bai[kc] = lda4(Aw_im, kc);
+    }
+  }
   __syncthreads();
 
   f32x4 yre[RB], yim[RB], cre[RB], cim[RB];
@@ -495,24 +511,27 @@ __global__ void __launch_bounds__(64 * NKC) k_propagate_f32_wide(
 #pragma unroll
     for (int kc = 0; kc < NKC; ++kc) {
       const f32x4 bn = kc + 1 < NKC ? ld4(Bq, kc + 1) : b;
+      f32x4 ar[RB], ai[RB];
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
-        if (rb >= nrb) break;
-        const f32x4 ar = *reinterpret_cast<const f32x4*>(&Tr[(16 * rb + j) * ldt + 16 * kc + 4 * q4]);
-        const f32x4 ai = *reinterpret_cast<const f32x4*>(&Ti[(16 * rb + j) * ldt + 16 * kc + 4 * q4]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          cre[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[e], b[e], cre[rb], 0, 0, 0);
-          cim[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[e], b[e], cim[rb], 0, 0, 0);
-        }
+        ar[rb] = *reinterpret_cast<const f32x4*>(&Tr[(16 * rb + j) * ldt + 16 * kc + 4 * q4]);
+        ai[rb] = *reinterpret_cast<const f32x4*>(&Ti[(16 * rb + j) * ldt + 16 * kc + 4 * q4]);
       }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          cre[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[rb][e], b[e], cre[rb], 0, 0, 0);
+          cim[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[rb][e], b[e], cim[rb], 0, 0, 0);
+        }
       b = bn;
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   auto store_planes = [&](const f32x4* pr, const f32x4* pi) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      if (rb < nrb && qcol < Kp) {
+      if (qcol < Kp) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           Tr[(16 * rb + 4 * q4 + v) * ldt + qcol] = pr[rb][v];
@@ -539,26 +558,57 @@ __global__ void __launch_bounds__(64 * NKC) k_propagate_f32_wide(
       cre[rb] = f32x4{};
       cim[rb] = f32x4{};
     }
-    f32x4 br = lda4(Aw_re, 0), bi = lda4(Aw_im, 0);
+    f32x4 br, bi;
+    const float *are = Aw_re, *aim = Aw_im;
+    if constexpr (!REG) {
+      asm volatile("" : "+s"(are), "+s"(aim));   // opaque: not the whole of A ahead of the series
+      br = lda4(are, 0);
+      bi = lda4(aim, 0);
+    }
 #pragma unroll
     for (int kc = 0; kc < NKC; ++kc) {
-      const f32x4 brn = kc + 1 < NKC ? lda4(Aw_re, kc + 1) : br;
-      const f32x4 bin = kc + 1 < NKC ? lda4(Aw_im, kc + 1) : bi;
+      f32x4 brn, bin;
+      if constexpr (REG) {
+        br = bar_[REG ? kc : 0];
+        bi = bai[REG ? kc : 0];
+      } else {
+        brn = kc + 1 < NKC ? lda4(are, kc + 1) : br;
+        bin = kc + 1 < NKC ? lda4(aim, kc + 1) : bi;
+      }
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        if (rb >= nrb) break;
-        const f32x4 ar = *reinterpret_cast<const f32x4*>(&Tr[(16 * rb + j) * ldt + 16 * kc + 4 * q4]);
-        const f32x4 ai = *reinterpret_cast<const f32x4*>(&Ti[(16 * rb + j) * ldt + 16 * kc + 4 * q4]);
+      for (int r0 = 0; r0 < RB; r0 += RS) {
+        f32x4 ar[RS], ai[RS], an[RS];
+#pragma unroll
+        for (int i = 0; i < RS; ++i) {
+          const int at = (16 * (r0 + i < RB ? r0 + i : r0) + j) * ldt + 16 * kc + 4 * q4;
+          ar[i] = *reinterpret_cast<const f32x4*>(&Tr[at]);
+          ai[i] = *reinterpret_cast<const f32x4*>(&Ti[at]);
+          an[i] = -ai[i];
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          cre[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[e], br[e], cre[rb], 0, 0, 0);
-          cre[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(-ai[e], bi[e], cre[rb], 0, 0, 0);
-          cim[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[e], bi[e], cim[rb], 0, 0, 0);
-          cim[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[e], br[e], cim[rb], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < RS; ++i) {
+            if (r0 + i >= RB) continue;
+            f32x4 &cr = cre[r0 + i < RB ? r0 + i : 0], &ci = cim[r0 + i < RB ? r0 + i : 0];
+            cr = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[i][e], br[e], cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[i][e], bi[e], ci, 0, 0, 0);
+          }
+#pragma unroll
+          for (int i = 0; i < RS; ++i) {
+            if (r0 + i >= RB) continue;
+            f32x4 &cr = cre[r0 + i < RB ? r0 + i : 0], &ci = cim[r0 + i < RB ? r0 + i : 0];
+            cr = __builtin_amdgcn_mfma_f32_16x16x4f32(an[i][e], bi[e], cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[i][e], br[e], ci, 0, 0, 0);
+          }
         }
+        if (RS < RB) __builtin_amdgcn_sched_barrier(0);
       }
-      br = brn;
-      bi = bin;
+      if constexpr (!REG) {
+        br = brn;
+        bi = bin;
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
     const float inv = 1.0f / (float)n;
     __syncthreads();
@@ -579,7 +629,7 @@ __global__ void __launch_bounds__(64 * NKC) k_propagate_f32_wide(
   cd* Uo = U + ((size_t)w * ntot + off) * M;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    if (rb >= nrb || !colok) continue;
+    if (!colok) continue;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int c = 16 * rb + 4 * q4 + v;
