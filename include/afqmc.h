@@ -130,11 +130,11 @@ typedef struct {
  * contraction grows with the size of Theta = U (V^T U)^-1, which grows as a walker's overlap
  * with the trial becomes ill-conditioned far into a run.  With the guard, every live walker
  * whose largest |Theta_pc| (over both spins and every determinant) exceeds theta_guard has its
- * force-bias traces and exchange sums computed again on the FP64 MFMA contraction, in the same
- * step, and those FP64 values are the ones used.  theta_guard NaN -> 4.0 in AFQMC_FP32 and
+ * force-bias traces and exchange sums computed on FP64 MFMA, in the same step, for the spins
+ * above the bound, and those FP64 values are the ones used.  theta_guard NaN -> 4.0 in AFQMC_FP32 and
  * 0.75 in AFQMC_BF16X3 (measured: at these bounds the local energy stays within 1e-4 Ha of
- * FP64 on the 128-orbital workload); +inf turns the guard off.  The guard needs the FP64
- * MFMA contraction's shapes (max(n_up, n_dn) <= 32, M <= 128): elsewhere it is off.  The
+ * FP64 on the 128-orbital workload); +inf turns the guard off.  The guard covers
+ * max(n_up, n_dn) <= 32, M <= 128: elsewhere it is off.  The
  * FP64 mode ignores theta_guard. */
 
 /* Growth phase (App. B.1, App. B.2).  Every walker population (its workspace) carries the
@@ -276,7 +276,7 @@ AFQMC_API int afqmc_step(afqmc_sys s, afqmc_walkers* w, const afqmc_fields* f);
 
 /* Autotuner: times every variant valid for the system's shape on these walkers (initialized
  * or measured; one untimed and three timed launches each, on the system's stream, writing only
- * workspace partial sums), keeps the fastest for every later step and returns it in *tile
+ * workspace partial sums; each variant's own kernel over all Cholesky vectors), keeps the fastest for every later step and returns it in *tile
  * (and its time per launch in *ms if ms != NULL).  With reuse != 0 a shape tuned before in the
  * process (same device, precision, M, N_up, N_dn, N_g, determinants and walker count) takes
  * the stored choice without timing (*ms = -1).  Synchronizes the stream. */
@@ -389,8 +389,8 @@ AFQMC_API int afqmc_get_status(afqmc_sys s, uint32_t* status, int clear);
  * (and resets the totals), 0 stops.  afqmc_kernel_time returns the accumulated time in
  * milliseconds and the number of launches of one kernel group, synchronizing the stream:
  *   0 = local-energy contraction, 1 = overlap / inverse, 2 = fields and force bias,
- *   3 = propagator build, 4 = Taylor propagation, 5 = QR, 6 = weights, 7 = comb,
- *   8 = energy assembly, 9 = the precision guard (walker list and FP64 redo). */
+ *   3 = propagator build, 4 = Taylor propagation, 5 = QR, 6 = growth sums and
+ *   bound counts, 7 = comb, 8 = energy assembly and weights, 9 = the precision guard (walker list and FP64 redo). */
 AFQMC_API int afqmc_kernel_timing(afqmc_sys s, int enable);
 AFQMC_API int afqmc_kernel_time(afqmc_sys s, int kernel, double* ms, int64_t* launches);
 
