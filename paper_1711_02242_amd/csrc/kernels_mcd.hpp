@@ -83,10 +83,12 @@ __global__ void __launch_bounds__(1024) k_mcd_vector(int M, int n, double delta,
   __shared__ McdBest s_b[16];
   const int MM = M * M, nb = mcd_blocks(MM);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (st->done) return;   // set by an earlier launch (or by this one: then every block stops below)
-  // ---- the pivot
+  // ---- the pivot, from what the launch before left: the same for every wavefront of every block.
+  // `st` is not asked (a block of this launch may be writing it): a launch past the end finds the
+  // maxima that the last one handed on.
+  const McdBest* in = best + (size_t)(n & 1) * nb;
+  McdBest* out = best + (size_t)((n + 1) & 1) * nb + blockIdx.x;
   {
-    const McdBest* in = best + (size_t)(n & 1) * nb;
     double d = -INFINITY;
     int mu = MM;
     for (int b = tid; b < nb; b += 1024) {
@@ -108,8 +110,9 @@ __global__ void __launch_bounds__(1024) k_mcd_vector(int M, int n, double delta,
       nu0 = x.mu;
     }
   }
-  if (!(dmax >= delta) || n >= max_vectors) {   // the same for every block
-    if (blockIdx.x == 0 && tid == 0) {
+  if (!(dmax >= delta) || n >= max_vectors) {
+    if (tid == 0) *out = in[blockIdx.x];
+    if (blockIdx.x == 0 && tid == 0 && !st->done) {
       st->count = n;
       st->dmax = dmax;
       st->done = 1;
@@ -152,6 +155,5 @@ __global__ void __launch_bounds__(1024) k_mcd_vector(int M, int n, double delta,
   }
   const unsigned long long bits = __ballot(gone);
   if (lane == 0) dead[blockIdx.x] = bits;
-  mcd_best_of_wave(d > -INFINITY ? d : -INFINITY, d > -INFINITY ? mu : MM,
-                   &best[(size_t)((n + 1) & 1) * nb + blockIdx.x], lane);
+  mcd_best_of_wave(d > -INFINITY ? d : -INFINITY, d > -INFINITY ? mu : MM, out, lane);
 }
