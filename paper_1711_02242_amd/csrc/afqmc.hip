@@ -601,10 +601,14 @@ double guard_threshold(const afqmc_params* p) {
   return p->precision == AFQMC_BF16X3 ? 0.75 : 4.0;
 }
 
-// Rows a (Mp apart) of the orthonormal complement of the N rows of V (of length M): Householder
-// reflections that take V's columns to a triangle, applied to the unit vectors N .. M - 1.
-void host_complement(const double* V, int N, int M, int Mp, double* Qt) {
-  std::vector<double> H((size_t)N * M), beta(N, 0.0);
+// From the N rows of V (of length M; the columns of a matrix), by Householder reflections that
+// take them to a triangle R: the rows a (Mp apart) of their orthonormal complement, the
+// reflections applied to the unit vectors N .. M - 1; and V0t [q][c] = (V (V^T V)^-1)_qc =
+// (Q1 R^-T)_qc, Q1 the same of the unit vectors 0 .. N - 1, by back substitution (the inverse of
+// V^T V would square the condition of a trial that is far from orthonormal).  False if V's rows
+// are linearly dependent (V0t is then not set).
+bool host_complement(const double* V, int N, int M, int Mp, double* Qt, double* V0t) {
+  std::vector<double> H((size_t)N * M), beta(N, 0.0), diag(N);
   std::vector<double> A(V, V + (size_t)N * M);   // row i: column i of the matrix
   for (int k = 0; k < N; ++k) {
     double* v = H.data() + (size_t)k * M;
@@ -612,6 +616,7 @@ void host_complement(const double* V, int N, int M, int Mp, double* Qt) {
     for (int p = k; p < M; ++p) nn += A[(size_t)k * M + p] * A[(size_t)k * M + p];
     const double x0 = A[(size_t)k * M + k], al = x0 > 0.0 ? -sqrt(nn) : sqrt(nn);
     for (int p = k; p < M; ++p) v[p] = A[(size_t)k * M + p];
+    diag[k] = al;
     v[k] -= al;
     double vv = 0.0;
     for (int p = k; p < M; ++p) vv += v[p] * v[p];
@@ -623,9 +628,8 @@ void host_complement(const double* V, int N, int M, int Mp, double* Qt) {
       for (int p = k; p < M; ++p) A[(size_t)j * M + p] -= dt * v[p];
     }
   }
-  for (int a = 0; a < M - N; ++a) {
-    double* x = Qt + (size_t)a * Mp;
-    for (int p = 0; p < M; ++p) x[p] = p == N + a ? 1.0 : 0.0;
+  auto unit = [&](int e, double* x) {
+    for (int p = 0; p < M; ++p) x[p] = p == e ? 1.0 : 0.0;
     for (int k = N - 1; k >= 0; --k) {
       const double* v = H.data() + (size_t)k * M;
       double dt = 0.0;
@@ -633,7 +637,23 @@ void host_complement(const double* V, int N, int M, int Mp, double* Qt) {
       dt *= beta[k];
       for (int p = k; p < M; ++p) x[p] -= dt * v[p];
     }
+  };
+  for (int a = 0; a < M - N; ++a) unit(N + a, Qt + (size_t)a * Mp);
+  // rows of R^-1 Q1^T, from the last; A[j][i] = R_ij for i < j
+  std::vector<double> Y((size_t)N * M);
+  for (int i = N - 1; i >= 0; --i) {
+    double* y = Y.data() + (size_t)i * M;
+    unit(i, y);
+    for (int j = i + 1; j < N; ++j)
+      for (int p = 0; p < M; ++p) y[p] -= A[(size_t)j * M + i] * Y[(size_t)j * M + p];
+    for (int p = 0; p < M; ++p) {
+      y[p] /= diag[i];
+      if (!std::isfinite(y[p])) return false;
+    }
   }
+  for (int p = 0; p < M; ++p)
+    for (int c = 0; c < N; ++c) V0t[(size_t)p * N + c] = Y[(size_t)c * M + p];
+  return true;
 }
 
 // The tables of the virtual-space contraction from V and Lh (host, n_det blocks; Lh also on the
@@ -661,21 +681,9 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
         c0[2 * d + 1] = c0[2 * d];
         continue;
       }
-      host_complement(V, N, M, p.Mp, Q);
-      std::vector<double> T((size_t)N * N);
-      for (int i = 0; i < N; ++i)
-        for (int j = 0; j < N; ++j) {
-          double acc = 0.0;
-          for (int q = 0; q < M; ++q) acc += V[(size_t)i * M + q] * V[(size_t)j * M + q];
-          T[(size_t)i * N + j] = acc;
-        }
+      std::vector<double> V0t((size_t)M * N);   // V (V^T V)^-1, [q][c]
       // linearly dependent orbitals (a later determinant) have no overlap with any walker
-      if (!host_inverse(T, N)) continue;
-      std::vector<double> V0t((size_t)M * N, 0.0);   // V (V^T V)^-1, [q][c]
-      for (int i = 0; i < N; ++i)
-        for (int q = 0; q < M; ++q)
-          for (int c = 0; c < N; ++c)
-            V0t[(size_t)q * N + c] += T[(size_t)i * N + c] * V[(size_t)i * M + q];
+      if (!host_complement(V, N, M, p.Mp, Q, V0t.data())) continue;
       std::vector<std::vector<double>> F(nthr, std::vector<double>((size_t)N * M, 0.0));
       std::vector<double> cg(G, 0.0);
       parallel_for(G, [&](int g, int th) {
