@@ -732,21 +732,24 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
     (void)hipGetLastError();
     return rc == AFQMC_E_NOMEM ? AFQMC_OK : rc;
   }
-  bool ok = hipMemset(t.B, 0, bel * 8) == hipSuccess && hipMemset(t.K, 0, kel * 8) == hipSuccess;
+  // on the system's stream, before whatever uses the tables, and without waiting: other streams'
+  // work (other systems' steps, a capture in another thread) is none of this system's business
+  bool ok = hipMemsetAsync(t.B, 0, bel * 8, S->stream) == hipSuccess &&
+            hipMemsetAsync(t.K, 0, kel * 8, S->stream) == hipSuccess;
   for (int d = 0; d < nd && ok; ++d)
     for (int s = 0; s < 2; ++s) {
       if (p.N[s] == 0) continue;
       double* Bs = t.B + (size_t)d * G * dps + (s ? (size_t)G * p.dp[0] : 0);
       const long long rows = (long long)G * p.N[s];
       hipLaunchKernelGGL(k_pair_b, dim3((unsigned)((rows + 15) / 16), (p.nv[s] + 63) / 64), dim3(64),
-                         0, 0, M, p.Mp, p.N[s], p.nv[s], G, p.dp[s], (size_t)nt * M,
+                         0, S->stream, M, p.Mp, p.N[s], p.nv[s], G, p.dp[s], (size_t)nt * M,
                          S->Lh + ((size_t)d * G * nt + (s ? p.N[0] : 0)) * M,
                          t.Qt + ((size_t)d * nv + (s ? p.nv[0] : 0)) * p.Mp, Bs);
-      hipLaunchKernelGGL(k_pair_build, dim3(p.dp[s] / 64, p.dp[s] / 64), dim3(256), 0, 0, p.d[s],
-                         p.dp[s], p.nv[s], G, (const double*)Bs,
+      hipLaunchKernelGGL(k_pair_build, dim3(p.dp[s] / 64, p.dp[s] / 64), dim3(256), 0, S->stream,
+                         p.d[s], p.dp[s], p.nv[s], G, (const double*)Bs,
                          t.K + ((size_t)d * (p.P[0] + p.P[1]) + (s ? p.P[0] : 0)) * PAIR_B * PAIR_B);
     }
-  ok = ok && hipGetLastError() == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+  ok = ok && hipGetLastError() == hipSuccess;
   return ok ? AFQMC_OK : AFQMC_E_HIP;
 }
 

@@ -1,0 +1,51 @@
+"""Setting a system up is a matter of its own stream: work of other streams is not waited for, and
+what setup leaves queued on the stream is done before the first use of it."""
+
+import numpy as np
+import pytest
+
+from oracle import afqmc as A
+from synthetic import config_system, random_walkers
+from tests.parity_helpers import log, oracle_U_to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_setup_does_not_wait_for_other_streams(precision):
+    import torch
+
+    import paper_1711_02242_amd as afq
+    s = config_system("medium")
+    nw = 6
+    U = random_walkers(s, nw, seed=1, amplitude=0.4)
+    S = A.setup(s.h0, s.h1, s.L, s.phi_up, s.phi_dn, 0.005)
+    ref = A.init_walkers(S, nw, *U).e_loc
+    Ug = torch.from_numpy(oracle_U_to_gpu(*U)).cuda()
+    kw = dict(dtau=0.005, precision=precision, theta_guard=1e-12)   # every walker in FP64
+    afq.System.from_synthetic(s, **kw).close()   # kernels loaded
+    a = torch.ones((8192, 8192), device="cuda")
+    b = torch.empty_like(a)
+    torch.mm(a, a, out=b)
+    torch.cuda.synchronize()
+    other, mine = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(other):
+        for _ in range(300):   # about two seconds
+            torch.mm(a, a, out=b)
+        end = torch.cuda.Event()
+        end.record()
+    with torch.cuda.stream(mine):
+        gs = afq.System.from_synthetic(s, **kw)
+    waited = end.query()
+    with torch.cuda.stream(mine):
+        wk = gs.walkers(nw)
+        gs.init(wk)
+        wk.U.copy_(Ug)
+        gs.measure(wk)
+        mine.synchronize()
+    e = wk.e_loc.cpu().numpy()
+    torch.cuda.synchronize()
+    d = np.abs(e - ref).max() / np.abs(ref).max()
+    log(f"setup beside another stream's work ({precision}): dE {d:.1e}")
+    assert not waited
+    assert d < 1e-10
