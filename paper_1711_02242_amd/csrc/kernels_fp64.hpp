@@ -780,9 +780,10 @@ __global__ void __launch_bounds__(1024) k_step_finish(
   if (bits) atomicOr(status, bits);
   block_sums(v, red);
   if (threadIdx.x != 0) return;
-  counts[CAP_LIVE] += (unsigned long long)v[3];
-  counts[CAP_E] += (unsigned long long)v[4];
-  counts[CAP_W] += (unsigned long long)v[5];
+  // atomic: the counters are the system's, whose populations may be stepped at the same time
+  atomicAdd(&counts[CAP_LIVE], (unsigned long long)v[3]);
+  if (v[4] > 0.0) atomicAdd(&counts[CAP_E], (unsigned long long)v[4]);
+  if (v[5] > 0.0) atomicAdd(&counts[CAP_W], (unsigned long long)v[5]);
   if (growing) {
     const double den = old[GR_DEN] + v[0], num = old[GR_NUM] + v[1], swe = old[GR_SWE] + v[2],
                  sw = old[GR_SW] + v[1];

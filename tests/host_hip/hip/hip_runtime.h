@@ -73,6 +73,9 @@ struct Wave {
   Barrier bar{64};
   uint64_t slot[64];
 };
+// Where set, atomic additions are put here and made later: the memory that other workgroups see
+// at the same time is then changed by plain stores alone.
+inline std::vector<std::pair<unsigned long long*, unsigned long long>>* deferred = nullptr;
 inline thread_local Wave* wave;
 inline thread_local Barrier* block;
 
@@ -137,7 +140,11 @@ inline double __shfl_xor(double v, int o, int = 64) {
   const int src = (threadIdx.x % 64) ^ o;
   return __builtin_bit_cast(double, host_hip::exchange(u, [=](const uint64_t* s) { return s[src]; }));
 }
-inline void atomicAdd(unsigned long long* p, unsigned long long v) { __atomic_fetch_add(p, v, 5); }
+inline void atomicAdd(unsigned long long* p, unsigned long long v) {
+  if (host_hip::deferred) host_hip::deferred->emplace_back(p, v);   // one thread's, in the kernels used
+  else __atomic_fetch_add(p, v, 5);
+}
+inline void atomicOr(unsigned* p, unsigned v) { __atomic_fetch_or(p, v, 5); }
 
 // Row shifts and row_bcast:15 of the data-parallel primitives; a source outside the row or a row
 // outside the mask leaves `old` (0 with bound_ctrl).
