@@ -296,11 +296,13 @@ bool host_inverse(std::vector<double>& a, int n) {
   return true;
 }
 
-// Runs body(i, thread) for i in [0, n) on up to 16 host threads (setup precompute only).
+// Runs body(i, thread) for i in [0, n) on up to 16 host threads (setup precompute only), on this
+// one alone where the whole is fewer than 2^18 multiply-adds or copies (`each` per i): starting
+// and joining 16 threads takes 0.1 - 0.2 ms.
 template <class F>
-void parallel_for(int n, F body) {
+void parallel_for(int n, F body, double each = 1e18) {
   const unsigned hw = std::thread::hardware_concurrency();
-  const int nt = std::max(1, std::min({n, 16, (int)(hw ? hw : 1)}));
+  const int nt = n * each < 262144.0 ? 1 : std::max(1, std::min({n, 16, (int)(hw ? hw : 1)}));
   if (nt == 1) {
     for (int i = 0; i < n; ++i) body(i, 0);
     return;
@@ -663,16 +665,22 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
   const PairDims& p = t.dim;
   const int M = S->M, G = S->G, nt = S->ntot, nd = S->n_det;
   const size_t nv = (size_t)p.nv[0] + p.nv[1], dps = (size_t)p.dp[0] + p.dp[1];
-  std::vector<double> Qt((size_t)nd * nv * p.Mp, 0.0), f(nd * dps, 0.0), t0((size_t)nd * 2 * G, 0.0),
-      c0((size_t)nd * 2, 0.0);
+  // one allocation, in the order K, B, then what the host forms: Qt, f, t0, c0 (K, B, Qt and f are
+  // multiples of 16 doubles)
+  const size_t kel = pair_k_elems(p), bel = pair_b_elems(p);
+  std::vector<double> host(t.bytes / 8 - kel - bel, 0.0);
+  double* const Qt = host.data();
+  double* const f = Qt + (size_t)nd * nv * p.Mp;
+  double* const t0 = f + nd * dps;
+  double* const c0 = t0 + (size_t)nd * 2 * G;
   const int nthr = setup_threads(G);
   for (int d = 0; d < nd; ++d)
     for (int s = 0; s < 2; ++s) {
       const int N = p.N[s], off = s ? p.N[0] : 0;
       if (N == 0) continue;
       const double* V = Vr.data() + ((size_t)d * nt + off) * M;
-      double* Q = Qt.data() + ((size_t)d * nv + (s ? p.nv[0] : 0)) * p.Mp;
-      double* fs = f.data() + d * dps + (s ? p.dp[0] : 0);
+      double* Q = Qt + ((size_t)d * nv + (s ? p.nv[0] : 0)) * p.Mp;
+      double* fs = f + d * dps + (s ? p.dp[0] : 0);
       if (s == 1 && p.N[0] == N && memcmp(V, V - (size_t)N * M, sizeof(double) * N * M) == 0) {
         // the same orbitals as spin up
         memcpy(Q, Q - (size_t)p.nv[0] * p.Mp, sizeof(double) * p.nv[0] * p.Mp);
@@ -708,7 +716,7 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
         }
         t0[((size_t)d * 2 + s) * G + g] = tr;
         cg[g] = x;
-      });
+      }, 2.0 * N * N * M);
       for (int g = 0; g < G; ++g) c0[2 * d + s] += cg[g];
       for (int th = 1; th < nthr; ++th)
         for (size_t e = 0; e < (size_t)N * M; ++e) F[0][e] += F[th][e];
@@ -719,23 +727,22 @@ int build_pair(afqmc_sys_s* S, const std::vector<double>& Vr, const std::vector<
           fs[(size_t)c * p.nv[s] + a] = acc;
         }
     }
-  int rc;
-  const size_t before = S->device_bytes, kel = pair_k_elems(p), bel = pair_b_elems(p);
-  if ((rc = dev_upload(S, &t.Qt, Qt.data(), Qt.size())) ||
-      (rc = dev_upload(S, &t.f, f.data(), f.size())) ||
-      (rc = dev_upload(S, &t.t0, t0.data(), t0.size())) ||
-      (rc = dev_upload(S, &t.c0, c0.data(), c0.size())) ||
-      (rc = dev_upload<double>(S, &t.B, nullptr, bel)) ||
-      (rc = dev_upload<double>(S, &t.K, nullptr, kel))) {
+  if (hipMalloc(&t.K, t.bytes) != hipSuccess) {
     pair_free_tables(t);
-    S->device_bytes = before;
     (void)hipGetLastError();
-    return rc == AFQMC_E_NOMEM ? AFQMC_OK : rc;
+    return AFQMC_OK;
   }
-  // on the system's stream, before whatever uses the tables, and without waiting: other streams'
-  // work (other systems' steps, a capture in another thread) is none of this system's business
-  bool ok = hipMemsetAsync(t.B, 0, bel * 8, S->stream) == hipSuccess &&
-            hipMemsetAsync(t.K, 0, kel * 8, S->stream) == hipSuccess;
+  S->device_bytes += t.bytes;
+  t.B = t.K + kel;
+  t.Qt = t.B + bel;
+  t.f = t.Qt + (f - Qt);
+  t.t0 = t.Qt + (t0 - Qt);
+  t.c0 = t.Qt + (c0 - Qt);
+  // the clear and the kernels on the system's stream, before whatever uses the tables, and without
+  // waiting: other streams' work (other systems' steps, a capture in another thread) is none of
+  // this system's business
+  bool ok = hipMemcpy(t.Qt, Qt, host.size() * 8, hipMemcpyHostToDevice) == hipSuccess &&
+            hipMemsetAsync(t.K, 0, (kel + bel) * 8, S->stream) == hipSuccess;
   for (int d = 0; d < nd && ok; ++d)
     for (int s = 0; s < 2; ++s) {
       if (p.N[s] == 0) continue;
@@ -1027,7 +1034,7 @@ int setup_impl(const afqmc_params* p, double h0, const double* h1, const double*
       if (q < M && pp < M)
         for (int g = 0; g < G; ++g)
           lt[(size_t)k * gp + g] = L_chol[(size_t)g * M * M + (size_t)q * M + pp];
-    });
+    }, G);
     if ((rc = dev_upload(S, &S->Lt64, lt.data(), lt.size()))) {
       free_sys(S);
       return rc;

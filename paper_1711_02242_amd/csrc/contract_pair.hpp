@@ -50,8 +50,8 @@ struct PairTables {
   double* t0 = nullptr;   // [n_det][2][G]: tr Om0^g
   double* c0 = nullptr;   // [n_det][2]
   double* B = nullptr;    // [n_det][s][G][dp_s], then 128 rows of slack (trace tiles past G)
-  double* K = nullptr;    // [n_det][s][P_s][128][128]
-  size_t bytes = 0;
+  double* K = nullptr;    // [n_det][s][P_s][128][128]; the start of the one allocation
+  size_t bytes = 0;       // of all of them
 };
 
 inline size_t pair_b_elems(const PairDims& p) {
@@ -106,7 +106,7 @@ inline void pair_plan(PairTables& t, int M, int nup, int ndn, int G, int n_det) 
 }
 
 inline void pair_free_tables(PairTables& t) {
-  for (double* q : {t.Qt, t.f, t.t0, t.c0, t.B, t.K}) (void)hipFree(q);
+  (void)hipFree(t.K);
   t = PairTables();
 }
 

@@ -49,3 +49,23 @@ def test_setup_does_not_wait_for_other_streams(precision):
     log(f"setup beside another stream's work ({precision}): dE {d:.1e}")
     assert not waited
     assert d < 1e-10
+
+
+def test_guard_tables_of_a_small_system_cost_little():
+    """The guard's tables of a tiny system are one allocation, one copy and four launches: setup
+    with them takes at most 1.3 times as long as without (the fastest of many, in turn)."""
+    import time
+
+    import paper_1711_02242_amd as afq
+    s = config_system("tiny")
+    best = {}
+    for i in range(120):
+        for guard in (None, np.inf):
+            t = time.perf_counter()
+            gs = afq.System.from_synthetic(s, dtau=0.01, precision="fp32", theta_guard=guard)
+            t = time.perf_counter() - t
+            gs.close()
+            if i >= 5:
+                best[guard] = min(best.get(guard, t), t)
+    log(f"setup {best[None] * 1e3:.3f} ms, without the guard {best[np.inf] * 1e3:.3f} ms")
+    assert best[None] <= 1.3 * best[np.inf]
