@@ -263,6 +263,8 @@ AFQMC_API int afqmc_step(afqmc_sys s, afqmc_walkers* w, const afqmc_fields* f);
  *                  (N <= 32, M <= 128)
  *   AFQMC_TILE_BX  W = 4 with Omega as four 16 x 16 blocks, the off-diagonal exchange
  *                  lane-local (16 < N <= 32, M <= 128); AFQMC_TILE_BX8 the same with W = 8
+ * In FP32 at N_g (N_up + N_dn) >= 49152 one kernel with the rows shared by a workgroup's walkers
+ * stands in for the wide, the flattened and the stacked-row kernel.
  * The FP64 mode has one contraction kernel per shape and accepts only the default. */
 #define AFQMC_TILE_DEFAULT 0
 #define AFQMC_TILE_W4 1
@@ -276,8 +278,10 @@ AFQMC_API int afqmc_step(afqmc_sys s, afqmc_walkers* w, const afqmc_fields* f);
 
 /* Autotuner: times every variant valid for the system's shape on these walkers (initialized
  * or measured; one untimed and three timed launches each, on the system's stream, writing only
- * workspace partial sums; each variant's own kernel over all Cholesky vectors), keeps the fastest for every later step and returns it in *tile
- * (and its time per launch in *ms if ms != NULL).  With reuse != 0 a shape tuned before in the
+ * workspace partial sums), each as a step launches it but for walkers that the precision guard
+ * would take, keeps the fastest for every later step and returns it in *tile (and its time per
+ * launch in *ms if ms != NULL).  Variants for which one kernel stands in (see above) are timed
+ * once, under the first of them.  With reuse != 0 a shape tuned before in the
  * process (same device, precision, M, N_up, N_dn, N_g, determinants and walker count) takes
  * the stored choice without timing (*ms = -1).  Synchronizes the stream. */
 AFQMC_API int afqmc_autotune(afqmc_sys s, afqmc_walkers* w, int32_t reuse, int32_t* tile,

@@ -408,11 +408,11 @@ int launch_overlap(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L, in
   return AFQMC_OK;
 }
 
-// Exchange partial sums of the contraction in use (splits of the Cholesky vectors).  Without
+// Exchange partial sums of the contraction with a tile (splits of the Cholesky vectors).  Without
 // the virtual-space form the guard's FP64 kernel overwrites a whole sum: no splits then.
-int exch_splits(const afqmc_sys_s* S, int nw) {
+int exch_splits(const afqmc_sys_s* S, int nw, int tile) {
   if (S->guard_on && !S->pr.on) return 1;
-  return mfma_splits(S->mt, nw, S->n_det, S->G, S->tile);
+  return mfma_splits(S->mt, nw, S->n_det, S->G, tile);
 }
 
 // Before the contraction: the precision guard's lists of walkers.  `in_step` counts the walkers
@@ -469,7 +469,7 @@ int launch_contraction(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L
     sel.stride = (size_t)w->n_walkers * S->n_det * 2;
     HIPCHK(mfma_contract(S->mt, S->stream, w->n_walkers, S->n_det, S->G, at<void>(ws, L.thetaP),
                          w->weight, at<cd>(ws, L.tpart), at<cd>(ws, L.exch), S->tile, sel,
-                         exch_splits(S, w->n_walkers)));
+                         exch_splits(S, w->n_walkers, S->tile)));
   }
   return AFQMC_OK;
 }
@@ -478,7 +478,7 @@ int launch_contraction(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L
 int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L,
                           const FinishArgs& fin) {
   void* ws = w->workspace;
-  const int nz = exch_splits(S, w->n_walkers);
+  const int nz = exch_splits(S, w->n_walkers, S->tile);
   const size_t xst = (size_t)w->n_walkers * S->n_det * 2;
   if (S->mt.enabled && S->guard_on) {
     // walkers far from the trial (large Theta) in FP64: of a listed walker, the spins whose
@@ -2049,17 +2049,24 @@ int afqmc_autotune(afqmc_sys s, afqmc_walkers* w, int32_t reuse, int32_t* tile, 
   double best_ms = 0.0;
   bool any = false;
   constexpr int REPS = 3;
-  // every walker in whole launches (no splits, nothing left to the guard): what is compared, and
-  // with it the arithmetic of a run, does not depend on how far the walkers are
+  // each variant as a step launches it, but for the walkers that the guard would take: what is
+  // compared does not depend on how far the walkers are
+  ContractSel sel{};
+  sel.stride = (size_t)w->n_walkers * s->n_det * 2;
+  bool shared = false;   // one kernel stands in for several variants: timed under the first
   for (int t = TILE_W4; t < TILE_COUNT && rc == AFQMC_OK; ++t) {
     if (!mfma_tile_valid(s->mt, t)) continue;
+    if (share_of(s->mt, t).ok) {
+      if (shared) continue;
+      shared = true;
+    }
     // one untimed launch, then REPS timed ones; only the workspace partial sums are written
     for (int r = 0; r <= REPS && rc == AFQMC_OK; ++r) {
       if (r == 1 && hipEventRecord(a, s->stream) != hipSuccess) rc = AFQMC_E_HIP;
       if (rc == AFQMC_OK &&
           mfma_contract(s->mt, s->stream, w->n_walkers, s->n_det, s->G, at<void>(ws, L.thetaP),
-                        w->weight, at<cd>(ws, L.tpart), at<cd>(ws, L.exch), t, ContractSel{},
-                        1, true) != hipSuccess)
+                        w->weight, at<cd>(ws, L.tpart), at<cd>(ws, L.exch), t, sel,
+                        exch_splits(s, w->n_walkers, t)) != hipSuccess)
         rc = AFQMC_E_HIP;
     }
     float el = 0.f;

@@ -7,7 +7,7 @@
 
 hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
                          const void* thetaP, const double* weight, cd* tpart, cd* exch, int tile,
-                         ContractSel sel, int nz, bool plain) {
+                         ContractSel sel, int nz) {
   if (t.precision == AFQMC_FP64) {
     const size_t shm = mfma_f64_contract_lds_bytes(t);
     dim3 grid((nw + 1) / 2, 2 * n_det);
@@ -39,7 +39,7 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
   const bool bf = t.precision == AFQMC_BF16X3;
   if (!mfma_tile_valid(t, tile)) tile = TILE_DEFAULT;
   // FP32 chunks of 16 k past M hold only zeros and are left out (the same bits)
-  const int nk16 = plain ? t.KP / 16 : (t.M + 15) / 16;
+  const int nk16 = (t.M + 15) / 16;
   // default at N_P = 32: the block-exchange kernel (fewest LDS and vector instructions per g),
   // eight walkers per workgroup when the workgroups with work (walkers, active spins,
   // determinants) still cover every CU
@@ -48,11 +48,8 @@ hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det,
     tile = (size_t)((nw + 7) / 8) * spins * n_det * nz >= (size_t)device_cu_count() ? TILE_BX8
                                                                                       : TILE_BX;
   }
-  if (!plain) {
-    const ShareLaunch f = share_of(t, tile);
-    if (f.ok)
-      return mfma_contract_share(t, st, nw, n_det, G, thetaP, weight, tpart, exch, f, sel, nz);
-  }
+  if (const ShareLaunch f = share_of(t, tile); f.ok)
+    return mfma_contract_share(t, st, nw, n_det, G, thetaP, weight, tpart, exch, f, sel, nz);
   if (tile == TILE_FLAT || tile == TILE_STACK)
     return mfma_contract_flat(t, st, nw, n_det, G, thetaP, weight, tpart, exch, tile == TILE_STACK,
                               sel, nz, bf ? t.KP / 32 : nk16);

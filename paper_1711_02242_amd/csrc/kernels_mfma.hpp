@@ -444,14 +444,12 @@ inline int mfma_splits(const MfmaTables& t, int nw, int n_det, int G, int tile) 
   return best;
 }
 
-// The contraction of every walker by one of the variants, in nz splits (FP64: 1).
-// contract_launch*.hip: translation units of their own, for their many kernel instances.  `plain`:
-// the variants' own kernels, in whole steps of 32 k, as the autotuner compares them (the choice
-// says which order of FP32 products a system gets, so it does not move with their tuning); else
-// FP32 chunks of 16 k past M are left out where the kernel has such an instance.
+// The contraction of every walker by one of the variants, in nz splits (FP64: 1).  FP32 chunks of
+// 16 k past M are left out where the kernel has such an instance.  contract_launch*.hip:
+// translation units of their own, for their many kernel instances.
 hipError_t mfma_contract(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
                          const void* thetaP, const double* weight, cd* tpart, cd* exch, int tile,
-                         ContractSel sel, int nz, bool plain = false);
+                         ContractSel sel, int nz);
 // Its shared-row part, f from share_of.
 hipError_t mfma_contract_share(const MfmaTables& t, hipStream_t st, int nw, int n_det, int G,
                                const void* thetaP, const double* weight, cd* tpart, cd* exch,
