@@ -163,10 +163,9 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.slist = take(S->guard_on ? nw * 8 : 0);
   L.ulist = take(S->guard_on ? nw * 8 : 0);
   L.gcount = take(S->guard_on ? 32 : 0);
-  const int cus = device_cu_count();
-  L.part = take(S->pr.on ? pair_part_elems(S->pr.dim, (int)nw, cus) * 16 : 0);
+  L.part = take(S->pr.on ? pair_part_elems(S->pr.dim, (int)nw) * 16 : 0);
   L.psplit = take(S->pr.on ? pair_split_elems(S->pr.dim) * 16 : 0);
-  L.pstart = take(S->pr.on ? (size_t)(2 * cus + 1) * 8 : 0);
+  L.pstart = take(S->pr.on ? (size_t)(PAIR_WG + 1) * 8 : 0);
   L.total = o;
   return L;
 }

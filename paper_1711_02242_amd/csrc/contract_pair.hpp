@@ -362,16 +362,18 @@ __host__ __device__ inline long long pair_tile_unit(const PairDims& p, const Pai
 __host__ __device__ inline int pair_tile_index(const PairSched& r, int d, int s, int c) {
   return d * (r.C[0] + r.C[1]) + (s ? r.C[0] : 0) + c;
 }
-// Workgroups of a launch: two per compute unit, no more than there is work for.
+// Workgroups of a launch: two per compute unit, no more than there is work for and at most two for
+// each of the MI355X's 256, for which the scratch is laid out (its size is host arithmetic alone).
+constexpr int PAIR_WG = 512;
 inline int pair_grid(const PairDims& p, int nw, int cus) {
   const int C = (nw + PAIR_W - 1) / PAIR_W;
   const PairSched r = pair_sched(p, C, C, 1);   // one workgroup: r.b is all there is to do
-  const long long n = 2LL * cus, most = r.b > 0 ? r.b + r.tr * std::max(p.T[0], p.T[1]) : 1;
+  const long long n = std::min(2 * cus, PAIR_WG), most = r.b > 0 ? r.b + r.tr * std::max(p.T[0], p.T[1]) : 1;
   return (int)(most < n ? most : n);
 }
-inline size_t pair_part_elems(const PairDims& p, int nw, int cus) {
+inline size_t pair_part_elems(const PairDims& p, int nw) {
   const int C = (nw + PAIR_W - 1) / PAIR_W;
-  return ((size_t)2 * cus + (size_t)p.n_det * 2 * C) * PAIR_W;
+  return ((size_t)PAIR_WG + (size_t)p.n_det * 2 * C) * PAIR_W;
 }
 
 struct PairArgs {
@@ -829,7 +831,7 @@ __global__ void __launch_bounds__(1024) k_guard_list(int nw, int nd, double limi
 }
 
 // k_pair and the sums of its partials (part: pair_part_elems, split: pair_split_elems, start:
-// 2 cus + 1).
+// PAIR_WG + 1).
 inline size_t pair_split_elems(const PairDims& p) { return (size_t)PAIR_SPLIT * PAIR_W * p.G; }
 inline hipError_t pair_contract(const PairTables& t, hipStream_t st, int nw, int cus,
                                 const double* X, cd* tpart, cd* exch, cd* part, cd* split,
