@@ -55,7 +55,7 @@ struct TimedLaunch {
 struct WsLayout {
   size_t thetaT, tcur, tpart, exch, e1, logdet, wflag, enew, wold, wstat, y, A, X0, X1, Y, parent, csum,
       wnew, asnap, lsnap, esum, thetaP, y32, fbterm, mfterm, logR, psnap, ldc, wflc, dstep, growth,
-      thmax, thetaP64, glist, slist, ulist, gcount, part, psplit, pstart, total;
+      thmax, thetaP64, glist, slist, ulist, gcount, pairX, part, psplit, pstart, total;
 };
 
 }  // namespace
@@ -138,15 +138,25 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.X0 = take(nw * nt * M * 16);
   L.X1 = take(nw * nt * M * 16);
   L.Y = take(nw * nt * M * 16);
+  if (S->pr.on) {
+    // the amplitudes X and the scratch of the virtual-space contraction, over A .. Y: those are the
+    // propagation's before it and the comb's after it
+    const size_t end = o;
+    o = L.A;
+    L.pairX = take(nw * nd * pair_x_elems(S->pr.dim) * 8);
+    L.part = take(pair_part_elems(S->pr.dim, (int)nw) * 16);
+    L.psplit = take(pair_split_elems(S->pr.dim, (int)nw, S->guard_on) * 16);
+    L.pstart = take((size_t)(PAIR_WG + 1) * 8);
+    o = std::max(o, end);
+  }
   L.parent = take(nw * 4);
   L.csum = take(nw * 8);
   L.wnew = take(64);
   L.asnap = take(nw * 8);
   L.lsnap = take(nw * 8);
   L.esum = take(64);
-  // the contraction's operand: the amplitudes X, or Theta packed for the per-vector kernels
-  const size_t xb = S->pr.on ? nw * nd * pair_x_elems(S->pr.dim) * 8 : 0;
-  L.thetaP = take(pair_mode(S) ? xb : mfma_theta_bytes(S->mt, nw));
+  // Theta packed for the per-vector kernels
+  L.thetaP = take(pair_mode(S) ? 0 : mfma_theta_bytes(S->mt, nw));
   L.y32 = take(S->f32_prop ? nw * 2 * (size_t)S->Gp * 4 : 0);
   const size_t nblk = (size_t)((S->G + 3) / 4);
   L.fbterm = take((S->p.flags & (AFQMC_FLAG_HYBRID | AFQMC_FLAG_FREE_PROJECTION)) ? nw * nblk * 16 : 0);
@@ -158,14 +168,11 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.dstep = take(8);
   L.growth = take(GR_COUNT * 8);
   L.thmax = take(S->guard_on ? nw * nd * 2 * 8 : 0);
-  L.thetaP64 = take(!S->guard_on ? 0 : S->pr.on ? xb : mfma_theta_bytes(S->mt64, nw));
+  L.thetaP64 = take(S->guard_on && !S->pr.on ? mfma_theta_bytes(S->mt64, nw) : 0);
   L.glist = take(S->guard_on ? nw * 4 : 0);
   L.slist = take(S->guard_on ? nw * 8 : 0);
   L.ulist = take(S->guard_on ? nw * 8 : 0);
   L.gcount = take(S->guard_on ? 32 : 0);
-  L.part = take(S->pr.on ? pair_part_elems(S->pr.dim, (int)nw) * 16 : 0);
-  L.psplit = take(S->pr.on ? pair_split_elems(S->pr.dim) * 16 : 0);
-  L.pstart = take(S->pr.on ? (size_t)(PAIR_WG + 1) * 8 : 0);
   L.total = o;
   return L;
 }
@@ -434,10 +441,10 @@ int launch_contraction(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout& L
   if (pair_mode(S)) {
     Timer tm(S, KG_CONTRACT);
     pair_virtual(S->pr, S->stream, w->n_walkers, S->M, at<cd>(ws, L.thetaT), w->weight,
-                 at<double>(ws, L.thetaP), nullptr, 0.0);
+                 at<double>(ws, L.pairX), nullptr, 0.0);
     HIPCHK(hipGetLastError());
     HIPCHK(pair_contract(S->pr, S->stream, w->n_walkers, device_cu_count(),
-                         at<double>(ws, L.thetaP), at<cd>(ws, L.tpart), at<cd>(ws, L.exch),
+                         at<double>(ws, L.pairX), at<cd>(ws, L.tpart), at<cd>(ws, L.exch),
                          at<cd>(ws, L.part), at<cd>(ws, L.psplit), at<long long>(ws, L.pstart)));
   } else if (!S->mt.enabled) {
     Timer tm(S, KG_CONTRACT);
@@ -486,10 +493,10 @@ int launch_guard_assemble(afqmc_sys_s* S, const afqmc_walkers* w, const WsLayout
     if (S->pr.on) {
       const double* thmax = at<double>(ws, L.thmax);
       pair_virtual(S->pr, S->stream, w->n_walkers, S->M, at<cd>(ws, L.thetaT), w->weight,
-                   at<double>(ws, L.thetaP64), thmax, S->guard);
+                   at<double>(ws, L.pairX), thmax, S->guard);
       HIPCHK(hipGetLastError());
       HIPCHK(pair_contract(S->pr, S->stream, w->n_walkers, device_cu_count(),
-                           at<double>(ws, L.thetaP64), at<cd>(ws, L.tpart), at<cd>(ws, L.exch),
+                           at<double>(ws, L.pairX), at<cd>(ws, L.tpart), at<cd>(ws, L.exch),
                            at<cd>(ws, L.part), at<cd>(ws, L.psplit), at<long long>(ws, L.pstart),
                            at<int>(ws, L.slist), at<int>(ws, L.gcount) + 1, thmax, S->guard, nz,
                            xst));

@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(256, 2) k_pair_virtual(
 // tile, unit), are cut into contiguous runs in proportion to what each workgroup has left of an
 // equal share.  Where a whole trace tile is more than that share (few walkers: at M = 150,
 // N = 37, 64 walkers it was 33 units against 3, and 0.64 ms instead of 0.17), its k range is
-// split ts ways, the parts go to scratch of PAIR_SPLIT column tiles and k_pair_reduce adds them.
+// split ts ways, the parts go to scratch (at most PAIR_SPLIT of them) and k_pair_reduce adds them.
 // ---------------------------------------------------------------------------
 constexpr int PAIR_SPLIT = 64;
 
@@ -375,6 +375,29 @@ inline size_t pair_part_elems(const PairDims& p, int nw) {
   const int C = (nw + PAIR_W - 1) / PAIR_W;
   return ((size_t)PAIR_WG + (size_t)p.n_det * 2 * C) * PAIR_W;
 }
+// Scratch of split traces: column tiles times splits of what pair_sched makes of all nw walkers, or
+// (any) of any part of them.  There ts < per / cap + 1 with per <= T and cap >= cols (P + Gt T) / nwg,
+// so cols ts is at most T nwg / (P + Gt T) + cols, and ts > 1 needs cols <= PAIR_SPLIT / 2.
+inline size_t pair_split_elems(const PairDims& p, int nw, bool any) {
+  const int C = (nw + PAIR_W - 1) / PAIR_W, nwg = pair_grid(p, nw, PAIR_WG / 2);
+  long long tiles = 0;
+  if (any) {
+    long long cols = 0, T = 1, unit = 0;
+    for (int s = 0; s < 2; ++s) {
+      if (p.N[s] == 0) continue;
+      const long long u = p.P[s] + (long long)p.Gt * p.T[s];
+      cols += (long long)p.n_det * C;
+      unit = unit == 0 ? u : std::min(unit, u);
+      T = std::max(T, (long long)p.T[s]);
+    }
+    cols = std::min(cols, (long long)PAIR_SPLIT / 2);
+    if (T > 1) tiles = std::min({(long long)PAIR_SPLIT, cols * T, T * nwg / unit + cols});
+  } else {
+    const PairSched r = pair_sched(p, C, C, nwg);
+    if (r.ts > 1) tiles = (long long)p.n_det * (r.C[0] + r.C[1]) * r.ts;
+  }
+  return (size_t)tiles * PAIR_W * p.G;
+}
 
 struct PairArgs {
   PairDims p;
@@ -382,7 +405,7 @@ struct PairArgs {
   const double *K, *B, *f, *t0, *X;
   cd* tpart;                 // [nw][n_det][2][G]
   cd* part;                  // [workgroup + column tile][64] partial sums
-  cd* split;                 // [PAIR_SPLIT][64][G] parts of split traces
+  cd* split;                 // [column tile][split][64][G] parts of split traces
   long long* start;          // [workgroups + 1] first K unit of each workgroup's run
   // the precision guard: walkers list[s][0 .. cnt[s]) instead of 0 .. nw, of which only the
   // determinants with thmax above guard are written
@@ -832,7 +855,6 @@ __global__ void __launch_bounds__(1024) k_guard_list(int nw, int nd, double limi
 
 // k_pair and the sums of its partials (part: pair_part_elems, split: pair_split_elems, start:
 // PAIR_WG + 1).
-inline size_t pair_split_elems(const PairDims& p) { return (size_t)PAIR_SPLIT * PAIR_W * p.G; }
 inline hipError_t pair_contract(const PairTables& t, hipStream_t st, int nw, int cus,
                                 const double* X, cd* tpart, cd* exch, cd* part, cd* split,
                                 long long* start, const int* list = nullptr, const int* cnt = nullptr,
