@@ -236,7 +236,8 @@ AFQMC_API int afqmc_walkers_init(afqmc_sys s, afqmc_walkers* w);
 
 /* Recompute, from the current U, everything cached per walker: arg_ovlp, log_ovlp, e_loc
  * and the force-bias traces (Theorem 1.1-1.2, eq:precomputing2, eq:localenergy3).  Weights
- * and step are untouched.  Used after writing U directly (restart, tests).  Asynchronous. */
+ * and step are untouched, but for a walker found lost, whose weight becomes 0; a dead walker's
+ * values stay as they are.  Used after writing U directly (restart, tests).  Asynchronous. */
 AFQMC_API int afqmc_measure(afqmc_sys s, afqmc_walkers* w);
 
 /* One step of the random walk for every walker with W > 0 (Sec. III.E), then w->step++.
@@ -352,7 +353,9 @@ AFQMC_API int afqmc_energy_enqueue(afqmc_sys s, const afqmc_walkers* w, double* 
  * device memory afqmc_setup (n_det == 1) or afqmc_setup_multidet would hold for these
  * parameters (the value afqmc_get_info reports), *walker_bytes = afqmc_workspace_bytes for
  * n_walkers plus the walker arrays of afqmc_walkers (U, weight, arg_ovlp, log_ovlp, e_loc,
- * phase, walker_id) and 256 bytes of workspace alignment.  Host arithmetic only; returns
+ * phase, walker_id) and 256 bytes of workspace alignment.  A setup that finds no
+ * room on the device for the FP64 contraction's tables does with the per-vector ones, and then
+ * holds other sizes (afqmc_get_info, afqmc_workspace_bytes).  Host arithmetic only; returns
  * AFQMC_E_UNSUPPORTED for shapes afqmc_setup would refuse for their size. */
 AFQMC_API int afqmc_footprint_bytes(const afqmc_params* p, int32_t n_det, int32_t n_walkers,
                                     size_t* system_bytes, size_t* walker_bytes);

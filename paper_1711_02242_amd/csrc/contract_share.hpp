@@ -18,9 +18,9 @@
 //             is read once.
 // One workgroup of 12 to 16 wavefronts per CU, so that the four SIMDs get the same number (ten
 // wavefronts: three on two of them, and a second workgroup does not fit beside).  The exchange
-// sums of a group run beside the next group's matrix products, a part in each step but the last
-// (one barrier a step orders them and the stores of Omega'), between the products of the step's two
-// halves of k: the matrix core has another wavefront's products meanwhile.
+// sums of a group run in the first step of the next one, after the first set of its products: the
+// matrix core has another wavefront's products meanwhile, and the barriers of the later steps (there
+// is at least one) come between these reads of Omega' and the stores of the next.
 //
 // Each element of Omega, and each trace, is the same chain of v_mfma_f32_16x16x4_f32 over k (and sum
 // over lanes) as in those kernels; the FP32 terms of the exchange are grouped otherwise.

@@ -14,7 +14,7 @@
 // ...; L^g_nu0 is gathered into LDS by all threads at once; and each workgroup leaves the
 // argmax of its 64 new D for the next launch, where every workgroup reduces all of them.  (One
 // thread per mu running over all g, and a pivot launch of its own: 66 us per vector at M = 64
-// and up to 512 vectors, 33.7 ms in all; now 8.2 us per vector.)
+// and up to 512 vectors, 33.7 ms in all; now 9.1 us per vector, 4.65 ms.)
 #pragma once
 
 #include "common.hpp"
@@ -22,8 +22,7 @@
 struct McdState {
   int done;       // 1 once converged or out of vectors
   int count;      // number of vectors when done
-  int piv;        // unused
-  int pad;
+  int piv, pad;   // unused
   double dmax;    // largest residual diagonal when done
 };
 

@@ -411,9 +411,14 @@ inline size_t mfma_f64_contract_lds_bytes(const MfmaTables& t) {
 // workgroups for 1024 slots, 8 splits.
 constexpr int CONTRACT_MAX_SPLITS = 16;
 // Geometry of the shared-row kernel where it takes a variant's place: the FP32 wide, flattened and
-// stacked-row forms.  It groups the FP32 terms of the exchange otherwise, which shows as
-// 6e-8 / sqrt(4 N_g N) of the local energy (2e-10 at N_g N = 30 000); below N_g (N_up + N_dn) =
-// 49152 the variants keep their own kernels, and their sums.
+// stacked-row forms.  It groups the FP32 terms of the exchange otherwise, which shows as a few
+// 6e-8 / sqrt(4 N_g N) of the local energy.  The line is one of results, not of speed: at
+// N_g (N_up + N_dn) = 49152 that is up to 9.5e-10 (random walkers), so above it a system's energies
+// keep nine digits from one kernel to the other, and below it the variants keep their own kernels,
+// and their sums.  The shared-row kernel would be the faster one there too, but for the widest N:
+// 300 walkers, best variant against shared rows, ms: M = 140, N = 34, N_g = 700 4.95 / 3.22 (just
+// below), N_g = 100 0.75 / 0.50; M = 160, N = 20, N_g = 960 2.17 / 1.67; M = 200, N = 20, N_g = 1200
+// 3.30 / 2.42; M = 100, N = 64, N_g = 300 2.92 / 3.04.
 inline ShareLaunch share_of(const MfmaTables& t, int tile) {
   if (!t.enabled || t.precision != AFQMC_FP32) return ShareLaunch{};
   if (!mfma_tile_valid(t, tile)) tile = TILE_DEFAULT;
