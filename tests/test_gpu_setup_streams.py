@@ -69,3 +69,27 @@ def test_guard_tables_of_a_small_system_cost_little():
                 best[guard] = min(best.get(guard, t), t)
     log(f"setup {best[None] * 1e3:.3f} ms, without the guard {best[np.inf] * 1e3:.3f} ms")
     assert best[None] <= 1.3 * best[np.inf]
+
+
+def test_guard_tables_of_many_determinants_cost_little():
+    """No pool of host threads for each of many small determinants: setup of 1024 of them with the
+    guard's tables takes at most 2.5 times as long as without (the fastest of a few, in turn)."""
+    import time
+
+    import paper_1711_02242_amd as afq
+    from synthetic import gen_system
+    s = gen_system(16, 4, 96, seed=7)
+    rng = np.random.default_rng(8)
+    nd = 1024
+    ups, dns = (p + 0.1 * rng.standard_normal((nd, 16, 4)) for p in (s.phi_up, s.phi_dn))
+    best = {}
+    for i in range(5):
+        for guard in (None, np.inf):
+            t = time.perf_counter()
+            gs = afq.System.multidet(s.h0, s.h1, s.L, np.ones(nd, dtype=complex), ups, dns, dtau=0.01,
+                                     precision="fp32", theta_guard=guard)
+            t = time.perf_counter() - t
+            gs.close()
+            best[guard] = min(best.get(guard, t), t)
+    log(f"setup of {nd} determinants {best[None] * 1e3:.0f} ms, without the guard {best[np.inf] * 1e3:.0f}")
+    assert best[None] <= 2.5 * best[np.inf]
