@@ -139,10 +139,11 @@ WsLayout layout(const afqmc_sys_s* S, size_t nw) {
   L.X1 = take(nw * nt * M * 16);
   L.Y = take(nw * nt * M * 16);
   if (S->pr.on) {
-    // the amplitudes X and the scratch of the virtual-space contraction, over A .. Y: those are the
-    // propagation's before it and the comb's after it
+    // the amplitudes X and the scratch of the virtual-space contraction, over X0, X1 and Y: those are
+    // the comb's after it, and before it the propagation's beyond M = 224 or N = 64 (over A too, which
+    // every step writes, the small FP64 step is 1 % slower)
     const size_t end = o;
-    o = L.A;
+    o = L.X0;
     L.pairX = take(nw * nd * pair_x_elems(S->pr.dim) * 8);
     L.part = take(pair_part_elems(S->pr.dim, (int)nw) * 16);
     L.psplit = take(pair_split_elems(S->pr.dim, (int)nw, S->guard_on) * 16);

@@ -1,6 +1,6 @@
 """Workspace of the virtual-space contraction: the scratch of split traces holds what the schedule
 asks for, for lists of any length, and a population's workspace grows by no more than Theta in FP64
-(which the guard's FP64 pass reads) where the amplitudes and the scratch fit over the propagation's
+(which the guard's FP64 pass reads) where the amplitudes and the scratch fit over the Taylor
 buffers, and by tens of megabytes less than its largest size for a handful of walkers."""
 
 import ctypes as C
